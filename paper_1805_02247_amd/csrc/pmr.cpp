@@ -568,6 +568,11 @@ uint32_t* invslot(pmr_ctx* c, int s) {
 }
 uint32_t* rowslot(pmr_ctx* c, int s) { return c->rows + (size_t)s * (c->B * c->nm * c->nm + 1); }
 int fs_of(pmr_ctx* c, int i) { return c->k == 0 ? i : i % c->k; }
+// The counters of the sort on the nm^3 mesh, for the kernel that writes its keys to clear.
+SortClear sort_counters(pmr_ctx* c, int nm) {
+  return cell_sort_clear(c->sort_scratch, (int)(c->B * c->np3), (size_t)c->B * nm * nm,
+                         ilog2((size_t)nm));
+}
 
 // One forward PM step i: sort x_i, paint, force, kick + drift (keys of x_{i+1} emitted on
 // the force mesh, or on the output mesh after the last step). `order`: the sorted ids of
@@ -656,7 +661,8 @@ void pm_step(pmr_ctx* c, int i, bool advance = true, const uint32_t* order = nul
     float* pck = (c->k > 0 && (i + 1) % c->k == 0 && i + 1 < c->n) ? ckpt_p(c, (i + 1) / c->k)
                                                                       : nullptr;
     launch_kick_drift(x, xn, p_in, c->p, pck, F, c->keys, c->frac_id, B, c->log_np3, c->nm,
-                      c->cfg.box, (float)c->kick[i], c->drift[i], key_nm, c->stream);
+                      c->cfg.box, (float)c->kick[i], c->drift[i], key_nm, sort_counters(c, key_nm),
+                      c->stream);
   }
 }
 
@@ -869,7 +875,8 @@ int pmr_forward(pmr_ctx* c, const void* modes, float* mass_out, double* loss_out
                    0.5 * (c->cfg.box / c->nm), c->D0, (float)c->Gp0,
                    second ? kLpt2 * c->D0 * c->D0 : 0.0,
                    second ? (float)(2.0 * kLpt2 * c->D0 * c->Gp0) : 0.f, xpos(c, 0), c->p,
-                   c->k > 0 ? ckpt_p(c, 0) : nullptr, c->keys, c->frac_id, key_nm, s);
+                   c->k > 0 ? ckpt_p(c, 0) : nullptr, c->keys, c->frac_id, key_nm,
+                   sort_counters(c, key_nm), s);
   }
   // H2-H7: the PM steps
   pm_run(c, 0, c->n);
@@ -1019,7 +1026,7 @@ int pmr_adjoint(pmr_ctx* c, const double* loss_bar, const float* mass_bar, void*
       // the segment starts from its checkpoint, read in place (x) and as the first kick's
       // input (p)
       launch_keys(xpos(c, j), c->log_np3, (int)(B * c->np3), scale_m, c->nm, c->keys,
-                  c->frac_id, s);
+                  c->frac_id, sort_counters(c, c->nm), s);
       const int end = j + c->k < c->n ? j + c->k : c->n;
       // the adjoint of steps j .. end-1 needs x, the sort and F of each step, not the
       // positions the last kick and drift would produce (the next checkpoint)
@@ -1327,8 +1334,11 @@ int pmr_cic_sort(int n_part, int n_mesh, int batch, double box, const double* x,
   hipStream_t s = (hipStream_t)stream;
   uint32_t* keys = (uint32_t*)scratch;
   void* rest = (char*)scratch + align256((size_t)total * sizeof(uint32_t));
-  launch_keys(x, ilog2(np3), total, (double)n_mesh / box, n_mesh, keys, nullptr, s);
-  launch_cell_sort(keys, nullptr, total, ilog2((size_t)n_mesh), (size_t)batch * n_mesh * n_mesh,
+  const size_t rows = (size_t)batch * n_mesh * n_mesh;
+  const int log_nm = ilog2((size_t)n_mesh);
+  launch_keys(x, ilog2(np3), total, (double)n_mesh / box, n_mesh, keys, nullptr,
+              cell_sort_clear(rest, total, rows, log_nm), s);
+  launch_cell_sort(keys, nullptr, total, log_nm, rows,
                    keys_sorted, ids_sorted, row_start, rest, nullptr, nullptr, nullptr, s);
   return hipGetLastError() == hipSuccess ? PMR_OK : PMR_E_HIP;
 }

@@ -229,15 +229,23 @@ int fft_slab_columns(int n);
 // row index row_start [rows + 1] (rows = key >> shift), pay_out[pos] = pay_in[id] and
 // inv[id] = pos when given. `order` (nullable) is the order in which the particles are
 // visited (a permutation of the ids, e.g. the previous step's sorted ids; it changes only
-// the speed). Scratch of cell_sort_scratch_bytes(n, rows) bytes.
+// the speed). Scratch of cell_sort_scratch_bytes(n, rows) bytes. The
+// sort's counters in it must be zero: the kernel that writes the keys clears them on the way
+// (a SortClear of the same scratch, n, rows and shift), which spares the sort a launch.
+struct SortClear {
+  uint32_t* p;
+  size_t n;
+};
+SortClear cell_sort_clear(void* scratch, int n, size_t rows, int shift);
 size_t cell_sort_scratch_bytes(int n, size_t rows, int shift);
 void launch_cell_sort(const uint32_t* keys, const uint32_t* order, int n, int shift,
                       size_t rows, uint32_t* keys_sorted, uint32_t* ids_sorted,
                       uint32_t* row_start, void* scratch, const Vec3* pay_in, Vec3* pay_out,
                       uint32_t* inv, hipStream_t s);
 // cic.hip
+// (the kernels that write keys also clear the counters of the sort that follows)
 void launch_keys(const double* x, int log_np3, int total, double scale, int nm, uint32_t* keys,
-                 Vec3* frac, hipStream_t s);
+                 Vec3* frac, SortClear clear, hipStream_t s);
 void launch_stream_frac(const uint32_t* ids, const double* x, int total, int log_np3, int nm,
                         double box, Vec3* frac, hipStream_t s);
 void launch_stream_gather(const uint32_t* ids, const Vec3* src, int total, Vec3* dst,
@@ -249,7 +257,7 @@ void launch_paint_mass(const uint32_t* keys, const Vec3* frac, const uint32_t* r
 void launch_kick_drift(const double* x, double* x_next, const float* p_in, float* p,
                        float* p_ck, const Vec3* F, uint32_t* keys, Vec3* frac, int batch,
                        int log_np3, int nm, double box, float kick, double drift, int key_nm,
-                       hipStream_t s);
+                       SortClear clear, hipStream_t s);
 // Position gradient of a step adjoint (or of the final paint: fbar = F = nullptr), computed in
 // sort order and written to g_out in id order:
 //   g = sum_corners dW/dx * (Fbar . F(corner) + mass * dbar(corner)).
@@ -267,7 +275,7 @@ void launch_adjoint_update(float* xbar, float* pbar, const Vec3* gpos, int batch
 void launch_za_init(const float* psi, const float* psi2, int batch, int np, int log_np3,
                     double box, double half_cell, double D0, float Gp0, double c2x, float c2p,
                     double* x, float* p, float* p_ck, uint32_t* keys, Vec3* frac, int key_nm,
-                    hipStream_t s);
+                    SortClear clear, hipStream_t s);
 // Two-network halo model (halo2.hip). Prepared weight block of HALO2_WEIGHT_FLOATS floats.
 constexpr int HALO2_WEIGHT_FLOATS = 448 + (4 * 21 + 2 * 16 + 4 * 8 + 6 * 16) * 64;
 void launch_halo2_prepare(const float* nnp, const float* nnm, float* w, hipStream_t s);

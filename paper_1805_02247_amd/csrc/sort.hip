@@ -3,20 +3,22 @@
 //
 //   1. row_count:  particles per row segment (item, ix, iy and the top bits of iz: a row or
 //                  a part of it, cell_sort_split) = key >> (log2(nm) - split), with one
-//                  atomic per distinct segment per wavefront.
-//   2. row_scan:   exclusive scan of the counts -> row_start (the row index the paints and
-//                  gathers use) and a cursor per row.
-//   3. bucket:     every particle id into its row's range, at a slot taken from the row's
-//                  cursor (the order inside a row depends on the timing of the atomics).
-//   4. row sort:   each row's entries sorted by the 64-bit composite (iz << 32 | id), which
-//                  is unique per particle, so the result is the (key, id) order whatever the
-//                  bucket order was: a wavefront sorts rows of up to 256 entries in registers
-//                  (bitonic network across lanes), a workgroup rows of up to 4096 in LDS, and
-//                  a workgroup runs a stable LSD radix sort in global memory for larger rows
-//                  (which only occur in very dense layouts). Every sorted entry is written
-//                  with its payload (gathered by id) and its inverse permutation entry.
+//                  atomic per distinct segment per wavefront. The counters are cleared by the
+//                  kernel that writes the keys (SortClear).
+//   2. scan:       exclusive scan of the counts -> row_start (the row index the paints and
+//                  gathers use) and a cursor per segment.
+//   3. bucket:     every particle into its segment's range, at a slot taken from the segment's
+//                  cursor (the order inside a segment depends on the timing of the atomics),
+//                  as its composite (iz within the segment, id) in one word.
+//   4. row sort:   each segment's composites sorted; they are unique per particle, so the
+//                  result is the (key, id) order whatever the bucket order was. One launch: a
+//                  wavefront sorts segments of up to 256 entries in registers (bitonic network
+//                  across lanes), the first workgroups of the grid those of up to 4096 in LDS,
+//                  or larger ones (which only occur in very dense layouts) with a stable LSD
+//                  radix sort in global memory. Every sorted entry is written with its
+//                  payload (gathered by id) and its inverse permutation entry.
 //
-// Compulsory traffic: the id-order keys read twice (count, bucket), one id written and read
+// Compulsory traffic: the id-order keys read twice (count, bucket), one word written and read
 // per particle in the buckets, the sorted keys, ids and payload written; no pass over
 // 8-bit digits of the whole key array.
 #include "pmr_internal.h"
@@ -27,8 +29,11 @@ namespace {
 constexpr int TB = 256;
 constexpr int WAVE_ROW_MAX = 256;    // tier 1: one wavefront, 4 entries per lane
 constexpr int BLOCK_ROW_MAX = 4096;  // tier 2: one workgroup, 16 entries per thread in LDS
+constexpr size_t LONG_BLOCKS = 1024;  // workgroups that take the rows beyond tier 1
 constexpr int SCAN_ITEMS = 16;
 constexpr int SCAN_TILE = TB * SCAN_ITEMS;  // counts per scan block
+constexpr int SCAN1_TB = 1024;              // threads of the one-launch scan
+constexpr int SCAN1_MAX_BLOCKS = 64;        // scan blocks up to which it is used
 
 __device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
 
@@ -37,43 +42,127 @@ __device__ __forceinline__ uint64_t lanes_below() {
   return l == 0 ? 0ull : (~0ull >> (64 - l));
 }
 
-// The value of lane (lane ^ J). Distances 1 and 2 are DPP quad permutations and 4 and 8
-// DPP row shifts (row_shl:J reads lane + J, row_shr:J lane - J, inside a row of 16 lanes,
-// where lane ^ J stays for these J): VALU moves with no LDS round trip. The moves carry no
-// old operand (the bound control reads 0 out of range, and the shift whose source is out of
-// range is the one not selected), so no register is cleared before them. 16 and 32 use the
-// row swaps of gfx950 on two copies of the value: permlane16_swap leaves the first copy
-// with rows (0, 0, 2, 2) and the second with (1, 1, 3, 3) of the original, permlane32_swap
-// the halves (lo, lo) and (hi, hi), so each lane picks the copy that holds its partner.
+// ---------------------------------------------------------------- wavefront sorting network
+// Ascending bitonic sort of 64 K values, element e * 64 + lane in v[e], by lane moves on the
+// vector units. The kernels that use it are bound by its instructions, so each compare and
+// exchange is written to need as few as possible (two at most distances):
+//   * the element a lane keeps, the smaller or the larger of its own and its partner's, is
+//     the median of the two and a bound (0 or ~0) that is constant per lane and distance;
+//   * the first stage of a level up to 16 compares with the mirrored lane (i ^ (k - 1)), which
+//     leaves both halves ascending, so no stage needs a direction;
+//   * larger levels take their descending halves as complemented values sorted ascending;
+//   * lane ^ 1, ^ 2, ^ 3 are quad permutations, ^ 7 and ^ 15 the mirrors of half rows and rows,
+//     ^ 8 the rotation of a row by 8, ^ 4 two moves (^ 7, ^ 3); for ^ 16 and ^ 32 the gfx950 row
+//     swap of two copies of the value leaves own and partner's value in the pair, in either
+//     order, which is all the median needs.
+__device__ __forceinline__ uint32_t med3(uint32_t x, uint32_t y, uint32_t z) {
+  const uint32_t lo = x < y ? x : y, hi = x < y ? y : x;
+  const uint32_t m = hi < z ? hi : z;
+  return lo < m ? m : lo;
+}
+
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_mov(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xF, 0xF, true);
+}
+
+// Bound of the compare and exchange whose upper elements are the lanes with bit J set.
 template <int J>
-__device__ __forceinline__ uint32_t xor_lane(uint32_t v) {
-  if constexpr (J == 1) {
-    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, true);  // [1,0,3,2]
-  } else if constexpr (J == 2) {
-    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xF, 0xF, true);  // [2,3,0,1]
-  } else if constexpr (J == 4 || J == 8) {
-    const uint32_t up = (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x100 + J, 0xF, 0xF, true);
-    const uint32_t dn = (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x110 + J, 0xF, 0xF, true);
-    return (lane_id() & J) ? dn : up;
-  } else if constexpr (J == 16) {
+__device__ __forceinline__ uint32_t bound() {
+  return (lane_id() & J) ? ~0u : 0u;
+}
+
+// Compare and exchange with lane ^ X; the lanes with bit UP set keep the larger value.
+template <int X, int UP>
+__device__ __forceinline__ uint32_t exchange(uint32_t v) {
+  if constexpr (X == 16) {
     const auto p = __builtin_amdgcn_permlane16_swap(v, v, false, false);
-    return (lane_id() & 16) ? p[0] : p[1];
-  } else {
+    return med3(p[0], p[1], bound<UP>());
+  } else if constexpr (X == 32) {
     const auto p = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-    return (lane_id() & 32) ? p[0] : p[1];
+    return med3(p[0], p[1], bound<UP>());
+  } else {
+    uint32_t o;
+    if constexpr (X == 1) o = dpp_mov<0xB1>(v);
+    if constexpr (X == 2) o = dpp_mov<0x4E>(v);
+    if constexpr (X == 3) o = dpp_mov<0x1B>(v);
+    if constexpr (X == 4) o = dpp_mov<0x1B>(dpp_mov<0x141>(v));
+    if constexpr (X == 7) o = dpp_mov<0x141>(v);
+    if constexpr (X == 8) o = dpp_mov<0x128>(v);
+    if constexpr (X == 15) o = dpp_mov<0x140>(v);
+    return med3(v, o, bound<UP>());
   }
 }
 
-template <int J>
-__device__ __forceinline__ uint64_t xor_lane64(uint64_t v) {
-  const uint32_t lo = xor_lane<J>((uint32_t)v);
-  const uint32_t hi = xor_lane<J>((uint32_t)(v >> 32));
-  return ((uint64_t)hi << 32) | lo;
+template <int X, int UP, int K>
+__device__ __forceinline__ void exchange_all(uint32_t (&v)[K]) {
+#pragma unroll
+  for (int e = 0; e < K; ++e) v[e] = exchange<X, UP>(v[e]);
 }
 
-__global__ void fill_u32_kernel(uint32_t* __restrict__ p, size_t n, uint32_t v) {
-  for (size_t i = (size_t)blockIdx.x * TB + threadIdx.x; i < n; i += (size_t)gridDim.x * TB)
-    p[i] = v;
+// Half-cleaners of distances J, J / 2, ..., 1 across the lanes.
+template <int J, int K>
+__device__ __forceinline__ void clean(uint32_t (&v)[K]) {
+  exchange_all<J, J>(v);
+  if constexpr (J > 1) clean<J / 2>(v);
+}
+
+// Each of K independent registers ascending across its 64 lanes (together, so that one's lane
+// moves fill the wait states of the other's).
+template <int K>
+__device__ __forceinline__ void wave_sort_each(uint32_t (&v)[K]) {
+  const uint32_t b16 = bound<16>(), b32 = bound<32>();
+  // descending runs as complements: of 16 (bit 4) and of 32 (bit 5)
+#pragma unroll
+  for (int e = 0; e < K; ++e) v[e] ^= b16 ^ b32;
+  exchange_all<1, 1>(v);
+  exchange_all<3, 2>(v);
+  clean<1>(v);
+  exchange_all<7, 4>(v);
+  clean<2>(v);
+  exchange_all<15, 8>(v);
+  clean<4>(v);
+#pragma unroll
+  for (int e = 0; e < K; ++e) v[e] ^= b16;
+  clean<16>(v);
+#pragma unroll
+  for (int e = 0; e < K; ++e) v[e] ^= b32;
+  clean<32>(v);
+}
+
+// The 64 K values of K registers ascending, element e * 64 + lane in v[e].
+template <int K>
+__device__ __forceinline__ void wave_sort(uint32_t (&v)[K]) {
+  static_assert(K == 1 || K == 2 || K == 4, "64, 128 or 256 values");
+  // descending runs as complements: of 64 (odd e) and of 128 (e & 2); e = 3 is both
+  if constexpr (K >= 2) v[1] = ~v[1];
+  if constexpr (K == 4) v[2] = ~v[2];
+  wave_sort_each<K>(v);
+  if constexpr (K >= 2) {
+#pragma unroll
+    for (int e = 1; e < K; e += 2) v[e] = ~v[e];
+#pragma unroll
+    for (int e = 0; e < K; e += 2) {
+      const uint32_t x = v[e], y = v[e + 1];
+      v[e] = x < y ? x : y;
+      v[e + 1] = x < y ? y : x;
+    }
+    clean<32>(v);
+  }
+  if constexpr (K == 4) {
+#pragma unroll
+    for (int e = 2; e < 4; ++e) v[e] = ~v[e];
+#pragma unroll
+    for (int d = 2; d >= 1; --d)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if ((e & d) == 0) {
+          const uint32_t x = v[e], y = v[e + d];
+          v[e] = x < y ? x : y;
+          v[e + d] = x < y ? y : x;
+        }
+    clean<32>(v);
+  }
 }
 
 // ---------------------------------------------------------------- 1. counts
@@ -81,27 +170,6 @@ __global__ void fill_u32_kernel(uint32_t* __restrict__ p, size_t n, uint32_t v) 
 // equal rows form runs: the first lane of each run then issues one atomic for the whole run,
 // all runs at once (instead of one round trip per distinct row). Rows must be <= 2^25 (the
 // caller checks), so that no entry equals the end marker ~0 that lanes past the end carry.
-template <int K, int J>
-__device__ __forceinline__ void sort64_stage(uint32_t& v) {
-  const int lane = lane_id();
-  const uint32_t o = xor_lane<J>(v);
-  const bool keep_min = ((lane & J) == 0) == ((lane & K) == 0);
-  v = keep_min ? (v < o ? v : o) : (v < o ? o : v);
-  if constexpr (J > 1) sort64_stage<K, J / 2>(v);
-}
-
-template <int K>
-__device__ __forceinline__ void sort64_level(uint32_t& v) {
-  sort64_stage<K, K / 2>(v);
-  if constexpr (K < 64) sort64_level<2 * K>(v);
-}
-
-// Ascending bitonic sort of one value per lane across the 64 lanes.
-__device__ __forceinline__ uint32_t wave_sort64(uint32_t v) {
-  sort64_level<2>(v);
-  return v;
-}
-
 // Runs of equal rows among the sorted (row << 6 | lane) values: for each lane the row, the
 // first lane of its run and the run's length (valid only for real entries).
 struct WaveRuns {
@@ -158,9 +226,10 @@ __global__ __launch_bounds__(TB) void row_count_kernel(const uint32_t* __restric
     const int g = group_base(q) + lane;
     v[q] = g < n ? ((keys[id[q]] >> shift) << 6) | (uint32_t)lane : ~0u;
   }
+  wave_sort_each<GROUPS>(v);
 #pragma unroll
   for (int q = 0; q < GROUPS; ++q) {
-    const WaveRuns w = wave_runs(wave_sort64(v[q]));
+    const WaveRuns w = wave_runs(v[q]);
     if (w.ok && w.head == lane) atomicAdd(&cnt[w.row], (uint32_t)w.len);
   }
 }
@@ -276,12 +345,78 @@ __global__ __launch_bounds__(TB) void scan_write_kernel(const uint32_t* __restri
   }
 }
 
+// The whole scan in one launch, for up to SCAN1_MAX_BLOCKS tiles: a workgroup sums every count
+// before its tile (at most 1 MB, from L2) instead of waiting for two more launches to reduce
+// and scan the tiles' totals.
+__global__ __launch_bounds__(SCAN1_TB) void scan_one_kernel(const uint32_t* __restrict__ cnt,
+                                                            size_t rows, uint32_t n,
+                                                            uint32_t* __restrict__ row_start,
+                                                            uint32_t* __restrict__ cursor,
+                                                            uint32_t* __restrict__ seg_start,
+                                                            int split) {
+  constexpr int WAVES = SCAN1_TB / 64;
+  static_assert(SCAN_TILE == 4 * SCAN1_TB, "four counts per thread");
+  __shared__ uint32_t wsum[2][WAVES];
+  const int t = threadIdx.x, lane = lane_id(), w = t >> 6;
+  const uint4* c4 = reinterpret_cast<const uint4*>(cnt);  // rows is a multiple of 4
+  const size_t tile = (size_t)blockIdx.x * SCAN1_TB + t;  // this thread's four counts
+  uint32_t before = 0;
+#pragma unroll 8
+  for (int b = 0; b < (int)blockIdx.x; ++b) {
+    const uint4 c = c4[(size_t)b * SCAN1_TB + t];
+    before += c.x + c.y + c.z + c.w;
+  }
+  uint4 v = make_uint4(0u, 0u, 0u, 0u);
+  if (4 * tile < rows) v = c4[tile];
+  const uint32_t own = v.x + v.y + v.z + v.w;
+  uint32_t x = own;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t y = __shfl_up(x, d, 64);
+    if (lane >= d) x += y;
+    before += __shfl_xor(before, d, 64);
+  }
+  if (lane == 63) {
+    wsum[0][w] = x;
+    wsum[1][w] = before;
+  }
+  __syncthreads();
+  uint32_t run = x - own;
+#pragma unroll
+  for (int i = 0; i < WAVES; ++i) run += (i < w ? wsum[0][i] : 0u) + wsum[1][i];
+  if (4 * tile < rows) {
+    const uint4 o = make_uint4(run, run + v.x, run + v.x + v.y, run + v.x + v.y + v.z);
+    reinterpret_cast<uint4*>(cursor)[tile] = o;
+    reinterpret_cast<uint4*>(seg_start)[tile] = o;
+    const uint32_t e[4] = {o.x, o.y, o.z, o.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const size_t r = 4 * tile + i;
+      if ((r & (((size_t)1 << split) - 1)) == 0) row_start[r >> split] = e[i];
+    }
+  }
+  if (blockIdx.x == 0 && t == 0) {
+    seg_start[rows] = n;
+    row_start[rows >> split] = n;
+  }
+}
+
 // ---------------------------------------------------------------- 3. buckets
+// One word per particle: its cell within the segment above its id, which the row sort can
+// order without another look at the keys (the gather of the keys by id was its second
+// dependent load).
+__device__ __forceinline__ uint32_t composite(uint32_t key, uint32_t zmask, int idbits,
+                                              uint32_t id) {
+  return ((key & zmask) << idbits) | id;
+}
+
 __global__ __launch_bounds__(TB) void bucket_kernel(const uint32_t* __restrict__ keys,
                                                     const uint32_t* __restrict__ order, int n,
-                                                    int shift, uint32_t* __restrict__ cursor,
+                                                    int shift, int idbits,
+                                                    uint32_t* __restrict__ cursor,
                                                     uint32_t* __restrict__ bucket) {
   const int lane = lane_id();
+  const uint32_t zmask = (1u << shift) - 1u;
   uint32_t id[GROUPS], v[GROUPS];
 #pragma unroll
   for (int q = 0; q < GROUPS; ++q) {
@@ -291,29 +426,35 @@ __global__ __launch_bounds__(TB) void bucket_kernel(const uint32_t* __restrict__
 #pragma unroll
   for (int q = 0; q < GROUPS; ++q) {
     const int g = group_base(q) + lane;
-    v[q] = g < n ? ((keys[id[q]] >> shift) << 6) | (uint32_t)lane : ~0u;
+    const uint32_t key = g < n ? keys[id[q]] : 0u;
+    v[q] = g < n ? ((key >> shift) << 6) | (uint32_t)lane : ~0u;
+    id[q] = composite(key, zmask, idbits, id[q]);
   }
+  uint32_t sorted[GROUPS];
+#pragma unroll
+  for (int q = 0; q < GROUPS; ++q) sorted[q] = v[q];
+  wave_sort_each<GROUPS>(sorted);
 #pragma unroll
   for (int q = 0; q < GROUPS; ++q) {
-    const uint32_t sorted = wave_sort64(v[q]);
-    const WaveRuns w = wave_runs(sorted);
+    const WaveRuns w = wave_runs(sorted[q]);
     uint32_t base = 0;
     if (w.ok && w.head == lane) base = atomicAdd(&cursor[w.row], (uint32_t)w.len);
     base = __shfl(base, w.ok ? w.head : lane, 64);
-    const uint32_t src_id = __shfl(id[q], (int)(sorted & 63u), 64);
-    if (w.ok) bucket[base + (uint32_t)(lane - w.head)] = src_id;
+    const uint32_t src = __shfl(id[q], (int)(sorted[q] & 63u), 64);
+    if (w.ok) bucket[base + (uint32_t)(lane - w.head)] = src;
   }
 }
 
 __global__ __launch_bounds__(TB) void bucket_loop_kernel(const uint32_t* __restrict__ keys,
                                                          const uint32_t* __restrict__ order,
-                                                         int n, int shift,
+                                                         int n, int shift, int idbits,
                                                          uint32_t* __restrict__ cursor,
                                                          uint32_t* __restrict__ bucket) {
   const int g = blockIdx.x * TB + threadIdx.x;
   const bool ok = g < n;
   const uint32_t id = ok ? visit(order, g) : 0u;
-  const uint32_t r = ok ? keys[id] >> shift : 0u;
+  const uint32_t key = ok ? keys[id] : 0u;
+  const uint32_t r = key >> shift;
   uint64_t todo = __ballot(ok);
   uint32_t pos = 0;
   while (todo) {
@@ -327,14 +468,13 @@ __global__ __launch_bounds__(TB) void bucket_loop_kernel(const uint32_t* __restr
     if (mine) pos = base + (uint32_t)__popcll(same & lanes_below());
     todo &= ~same;
   }
-  if (ok) bucket[pos] = id;
+  if (ok) bucket[pos] = composite(key, (1u << shift) - 1u, idbits, id);
 }
 
 // ---------------------------------------------------------------- 4. row sorts
 struct RowSortArgs {
-  const uint32_t* keys;       // id-order keys
   const uint32_t* row_start;  // [rows + 1]
-  const uint32_t* bucket;     // ids bucketed by row
+  const uint32_t* bucket;     // composites (iz << idbits | id) bucketed by row
   uint32_t* keys_sorted;
   uint32_t* ids_sorted;
   const Vec3* pay_in;  // nullable
@@ -343,36 +483,18 @@ struct RowSortArgs {
   uint32_t* tmp_hi;    // global radix scratch [n] x 2 (rows beyond the LDS tier)
   uint32_t* tmp_lo;
   int shift;
-  uint32_t zmask;      // nm - 1
-  int idbits;          // bits of the largest id (32-bit composites: iz << idbits | id)
+  int idbits;          // bits of the largest id
   size_t rows;
-  int block_rows;      // rows a workgroup of the long-row tiers tests per step (<= TB)
+  int long_blocks;     // workgroups at the start of the grid that take the long rows
+  int block_rows;      // rows such a workgroup tests per step (<= TB)
 };
-
-// Composite sort value of a particle within its row: (iz, id) as iz << 32 | id in 64 bits,
-// or iz << idbits | id in 32 bits where the two fit (the order is the same).
-template <typename T>
-__device__ __forceinline__ T composite_t(const RowSortArgs& a, uint32_t id) {
-  if constexpr (sizeof(T) == 8)
-    return ((uint64_t)(a.keys[id] & a.zmask) << 32) | id;
-  else
-    return ((a.keys[id] & a.zmask) << a.idbits) | id;
-}
 
 // Writes one sorted entry at sorted position pos of row `row`, with its payload
 // (non-temporal: read once, by the paint after the sort) and inverse permutation entry.
 // (A separate streaming pass over the sorted ids for these measured no faster at 256^3 on
 // 512^3 and 2% slower for the sort at 128^3 x 4: the gather by id costs the same in either.)
-template <typename T>
-__device__ __forceinline__ void emit_t(const RowSortArgs& a, uint32_t row, uint32_t pos, T v) {
-  uint32_t iz, id;
-  if constexpr (sizeof(T) == 8) {
-    iz = (uint32_t)(v >> 32);
-    id = (uint32_t)v;
-  } else {
-    iz = v >> a.idbits;
-    id = v & ((1u << a.idbits) - 1u);
-  }
+__device__ __forceinline__ void emit(const RowSortArgs& a, uint32_t row, uint32_t pos,
+                                     uint32_t iz, uint32_t id) {
   a.keys_sorted[pos] = (row << a.shift) | iz;
   a.ids_sorted[pos] = id;
   if (a.pay_out) {
@@ -384,119 +506,74 @@ __device__ __forceinline__ void emit_t(const RowSortArgs& a, uint32_t row, uint3
   if (a.inv) a.inv[id] = pos;
 }
 
-__device__ __forceinline__ void emit(const RowSortArgs& a, uint32_t row, uint32_t pos, uint64_t v) {
-  emit_t<uint64_t>(a, row, pos, v);
+__device__ __forceinline__ uint32_t id_of(const RowSortArgs& a, uint32_t v) {
+  return v & ((1u << a.idbits) - 1u);
+}
+__device__ __forceinline__ uint32_t iz_of(const RowSortArgs& a, uint32_t v) {
+  return v >> a.idbits;
 }
 
-template <typename T, int J>
-__device__ __forceinline__ T xor_lane_t(T v) {
-  if constexpr (sizeof(T) == 8)
-    return xor_lane64<J>(v);
-  else
-    return xor_lane<J>(v);
+__device__ __forceinline__ void emit_composite(const RowSortArgs& a, uint32_t row, uint32_t pos,
+                                               uint32_t v) {
+  emit(a, row, pos, iz_of(a, v), id_of(a, v));
 }
 
-// Bitonic sort of 64 K values, element e * 64 + lane in v[e], ascending: level k merges
-// runs of k, stage j compares elements j apart (across lanes for j < 64, across the
-// registers of one lane for j >= 64).
-template <typename T, int K, int k, int j>
-__device__ __forceinline__ void bitonic_stage(T (&v)[K]) {
-  const int lane = lane_id();
-  if constexpr (j >= 64) {
-    constexpr int je = j >> 6;
-#pragma unroll
-    for (int e = 0; e < K; ++e) {
-      if ((e & je) == 0) {
-        const int p = e | je;
-        const bool up = ((e * 64 + lane) & k) == 0;
-        const T x = v[e], y = v[p];
-        const bool sw = (x > y) == up;
-        v[e] = sw ? y : x;
-        v[p] = sw ? x : y;
-      }
-    }
-  } else {
-    const bool lower = (lane & j) == 0;
-#pragma unroll
-    for (int e = 0; e < K; ++e) {
-      const T o = xor_lane_t<T, j>(v[e]);
-      const bool up = ((e * 64 + lane) & k) == 0;
-      v[e] = (lower == up) ? (v[e] < o ? v[e] : o) : (v[e] < o ? o : v[e]);
-    }
-  }
-  if constexpr (j > 1) bitonic_stage<T, K, k, j / 2>(v);
-}
-
-template <typename T, int K, int k>
-__device__ __forceinline__ void bitonic_level(T (&v)[K]) {
-  bitonic_stage<T, K, k, k / 2>(v);
-  if constexpr (k < 64 * K) bitonic_level<T, K, 2 * k>(v);
-}
-
-template <typename T, int K>
-__device__ __forceinline__ void wave_bitonic(T (&v)[K]) {
-  bitonic_level<T, K, 2>(v);
-}
-
-// Tier 1: each wavefront takes two rows at a time (r and r + W for W wavefronts), loading
-// both before sorting either, so that their dependent loads (row start, bucket, key
-// gather) overlap; rows of 1..256 entries are sorted here. (Two rows per step measured
-// 2-3% faster for the sort than one or four, and eight 13% slower: more rows in flight
-// cost resident waves.)
+// Tier 1: each wavefront takes two rows at a time, loading both before sorting either, so
+// that their dependent loads (row start, bucket) overlap; rows of 1..256 entries are sorted
+// here. (Two rows per step measured 2-3% faster for the sort than one or four, and eight 13%
+// slower: more rows in flight cost resident waves.)
 constexpr int WAVE_ROWS = 2;
 
-template <typename T>
-__global__ __launch_bounds__(TB) void row_sort_wave_kernel(RowSortArgs a) {
-  constexpr T PADT = (T)~(T)0;  // sorts after (or ties with) every real entry
-  const size_t waves = (size_t)gridDim.x * (TB / 64);
+// Rows r0 .. r0 + WAVE_ROWS - 1 by one wavefront.
+__device__ __forceinline__ void sort_wave_rows(const RowSortArgs& a, size_t r0) {
+  constexpr uint32_t PAD = ~0u;  // sorts after (or ties with) every real entry
   const int lane = lane_id();
-  for (size_t r0 = (size_t)blockIdx.x * (TB / 64) + (threadIdx.x >> 6); r0 < a.rows;
-       r0 += WAVE_ROWS * waves) {
-    uint32_t start[WAVE_ROWS], cnt[WAVE_ROWS];
+  uint32_t start[WAVE_ROWS], cnt[WAVE_ROWS];
 #pragma unroll
-    for (int q = 0; q < WAVE_ROWS; ++q) {
-      const size_t r = r0 + q * waves;
-      start[q] = r < a.rows ? a.row_start[r] : 0u;
-      cnt[q] = r < a.rows ? a.row_start[r + 1] - start[q] : 0u;
-      if (cnt[q] > WAVE_ROW_MAX) cnt[q] = 0;  // the workgroup tiers take it
+  for (int q = 0; q < WAVE_ROWS; ++q) {
+    const size_t r = r0 + q;
+    start[q] = r < a.rows ? a.row_start[r] : 0u;
+    cnt[q] = r < a.rows ? a.row_start[r + 1] - start[q] : 0u;
+    if (cnt[q] > WAVE_ROW_MAX) cnt[q] = 0;  // the workgroup tiers take it
+  }
+  uint32_t v[WAVE_ROWS][4];
+#pragma unroll
+  for (int q = 0; q < WAVE_ROWS; ++q)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const uint32_t i = e * 64 + lane;
+      v[q][e] = i < cnt[q] ? a.bucket[start[q] + i] : PAD;
     }
-    uint32_t id[WAVE_ROWS][4];
+  if (cnt[0] <= 64 && cnt[1] <= 64) {
+    static_assert(WAVE_ROWS == 2, "two rows sorted together");
+    uint32_t w[2] = {v[0][0], v[1][0]};
+    wave_sort_each<2>(w);
 #pragma unroll
-    for (int q = 0; q < WAVE_ROWS; ++q)
+    for (int q = 0; q < 2; ++q)
+      if (lane < (int)cnt[q]) emit_composite(a, (uint32_t)(r0 + q), start[q] + lane, w[q]);
+    return;
+  }
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const uint32_t i = e * 64 + lane;
-        id[q][e] = i < cnt[q] ? a.bucket[start[q] + i] : 0u;
-      }
-    T v[WAVE_ROWS][4];
+  for (int q = 0; q < WAVE_ROWS; ++q) {
+    if (cnt[q] == 0) continue;
+    const uint32_t row = (uint32_t)(r0 + q);
+    if (cnt[q] <= 64) {
+      uint32_t w1[1] = {v[q][0]};
+      wave_sort<1>(w1);
+      if (lane < (int)cnt[q]) emit_composite(a, row, start[q] + lane, w1[0]);
+    } else if (cnt[q] <= 128) {
+      uint32_t w2[2] = {v[q][0], v[q][1]};
+      wave_sort<2>(w2);
 #pragma unroll
-    for (int q = 0; q < WAVE_ROWS; ++q)
+      for (int e = 0; e < 2; ++e)
+        if ((uint32_t)(e * 64 + lane) < cnt[q])
+          emit_composite(a, row, start[q] + e * 64 + lane, w2[e]);
+    } else {
+      wave_sort<4>(v[q]);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const uint32_t i = e * 64 + lane;
-        v[q][e] = i < cnt[q] ? composite_t<T>(a, id[q][e]) : PADT;
-      }
-#pragma unroll
-    for (int q = 0; q < WAVE_ROWS; ++q) {
-      if (cnt[q] == 0) continue;
-      const uint32_t row = (uint32_t)(r0 + q * waves);
-      if (cnt[q] <= 64) {
-        T w1[1] = {v[q][0]};
-        wave_bitonic<T, 1>(w1);
-        if (lane < (int)cnt[q]) emit_t<T>(a, row, start[q] + lane, w1[0]);
-      } else if (cnt[q] <= 128) {
-        T w2[2] = {v[q][0], v[q][1]};
-        wave_bitonic<T, 2>(w2);
-#pragma unroll
-        for (int e = 0; e < 2; ++e)
-          if ((uint32_t)(e * 64 + lane) < cnt[q]) emit_t<T>(a, row, start[q] + e * 64 + lane, w2[e]);
-      } else {
-        wave_bitonic<T, 4>(v[q]);
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if ((uint32_t)(e * 64 + lane) < cnt[q])
-            emit_t<T>(a, row, start[q] + e * 64 + lane, v[q][e]);
-      }
+      for (int e = 0; e < 4; ++e)
+        if ((uint32_t)(e * 64 + lane) < cnt[q])
+          emit_composite(a, row, start[q] + e * 64 + lane, v[q][e]);
     }
   }
 }
@@ -559,26 +636,22 @@ __device__ void block_radix_pass(const uint32_t* shi, const uint32_t* slo, uint3
 // takes block_rows consecutive rows at a time (blocks strided over the row range); its
 // threads test those rows' lengths together and the workgroup then sorts the long ones one
 // after the other (rows are independent, so the order in which they are done does not
-// matter). block_rows is chosen so that every resident workgroup gets rows to test.
-template <typename T>
-__global__ __launch_bounds__(TB) void row_sort_block_kernel(RowSortArgs a) {
-  constexpr T PADT = (T)~(T)0;
-  __shared__ T s[BLOCK_ROW_MAX];
-  __shared__ uint32_t base[256];
-  __shared__ uint32_t wcnt[TB / 64][256];
+// matter).
+__device__ __forceinline__ void sort_long_rows(const RowSortArgs& a, uint32_t* s, uint32_t* found,
+                                               int* nfound) {
   __shared__ uint32_t red[2][TB / 64];
-  __shared__ uint32_t found[TB];
-  __shared__ int nfound;
+  uint32_t* base = s;  // tier 3 has no use for the LDS tile itself
+  uint32_t(*wcnt)[256] = reinterpret_cast<uint32_t(*)[256]>(s + 256);
   const int t = threadIdx.x;
   const size_t br = (size_t)a.block_rows;
-  for (size_t r0 = (size_t)blockIdx.x * br; r0 < a.rows; r0 += (size_t)gridDim.x * br) {
-    if (t == 0) nfound = 0;
+  for (size_t r0 = (size_t)blockIdx.x * br; r0 < a.rows; r0 += (size_t)a.long_blocks * br) {
+    if (t == 0) *nfound = 0;
     __syncthreads();
     if ((size_t)t < br && r0 + t < a.rows &&
         a.row_start[r0 + t + 1] - a.row_start[r0 + t] > WAVE_ROW_MAX)
-      found[atomicAdd(&nfound, 1)] = (uint32_t)t;
+      found[atomicAdd(nfound, 1)] = (uint32_t)t;
     __syncthreads();
-    const int nf = nfound;
+    const int nf = *nfound;
     for (int f = 0; f < nf; ++f) {
       const size_t r = r0 + found[f];
       const uint32_t start = a.row_start[r];
@@ -587,8 +660,7 @@ __global__ __launch_bounds__(TB) void row_sort_block_kernel(RowSortArgs a) {
       if (c <= BLOCK_ROW_MAX) {
         uint32_t p2 = 512;
         while (p2 < c) p2 <<= 1;
-        for (uint32_t i = t; i < p2; i += TB)
-          s[i] = i < c ? composite_t<T>(a, a.bucket[start + i]) : PADT;
+        for (uint32_t i = t; i < p2; i += TB) s[i] = i < c ? a.bucket[start + i] : ~0u;
         __syncthreads();
         for (uint32_t k = 2; k <= p2; k <<= 1) {
           for (uint32_t j = k >> 1; j > 0; j >>= 1) {
@@ -596,7 +668,7 @@ __global__ __launch_bounds__(TB) void row_sort_block_kernel(RowSortArgs a) {
               const uint32_t i = ((q & ~(j - 1)) << 1) | (q & (j - 1));
               const uint32_t p = i | j;
               const bool up = (i & k) == 0;
-              const T x = s[i], y = s[p];
+              const uint32_t x = s[i], y = s[p];
               if ((x > y) == up) {
                 s[i] = y;
                 s[p] = x;
@@ -605,7 +677,7 @@ __global__ __launch_bounds__(TB) void row_sort_block_kernel(RowSortArgs a) {
             __syncthreads();
           }
         }
-        for (uint32_t i = t; i < c; i += TB) emit_t<T>(a, row, start + i, s[i]);
+        for (uint32_t i = t; i < c; i += TB) emit_composite(a, row, start + i, s[i]);
         __syncthreads();
         continue;
       }
@@ -617,8 +689,8 @@ __global__ __launch_bounds__(TB) void row_sort_block_kernel(RowSortArgs a) {
       uint32_t* blo = a.tmp_lo + start;
       uint32_t orv[2] = {0u, 0u}, andv[2] = {~0u, ~0u};
       for (uint32_t i = t; i < c; i += TB) {
-        const uint32_t id = a.bucket[start + i];
-        const uint32_t hi = a.keys[id] & a.zmask;
+        const uint32_t v = a.bucket[start + i];
+        const uint32_t hi = iz_of(a, v), id = id_of(a, v);
         ahi[i] = hi;
         alo[i] = id;
         orv[0] |= hi;
@@ -630,7 +702,7 @@ __global__ __launch_bounds__(TB) void row_sort_block_kernel(RowSortArgs a) {
       uint32_t var[2];
       for (int h = 0; h < 2; ++h) {
         uint32_t o = orv[h], n = andv[h];
-  #pragma unroll
+#pragma unroll
         for (int d = 1; d < 64; d <<= 1) {
           o |= __shfl_xor(o, d, 64);
           n &= __shfl_xor(n, d, 64);
@@ -665,12 +737,27 @@ __global__ __launch_bounds__(TB) void row_sort_block_kernel(RowSortArgs a) {
       const uint32_t* flo = in_a ? alo : blo;
       // each thread reads and rewrites only its own indices of A (in place when the last pass
       // landed there)
-      for (uint32_t i = t; i < c; i += TB)
-        emit(a, row, start + i, ((uint64_t)fhi[i] << 32) | flo[i]);
+      for (uint32_t i = t; i < c; i += TB) emit(a, row, start + i, fhi[i], flo[i]);
       __syncthreads();
     }
     __syncthreads();  // every thread has read nfound before it is reset
   }
+}
+
+// Both tiers in one launch: the long rows' workgroups come first in the grid, so that their
+// longer work runs beside the wavefront tier instead of after it (as a launch of its own it
+// cost 10-24 us per sort), and the wavefront tier's blocks are mapped so that neighbouring
+// rows, whose payload lines overlap, share an L2.
+__global__ __launch_bounds__(TB) void row_sort_kernel(RowSortArgs a) {
+  __shared__ uint32_t s[BLOCK_ROW_MAX];
+  __shared__ uint32_t found[TB];
+  __shared__ int nfound;
+  if ((int)blockIdx.x < a.long_blocks) {
+    sort_long_rows(a, s, found, &nfound);
+    return;
+  }
+  const int b = xcd_block(blockIdx.x - a.long_blocks, gridDim.x - a.long_blocks);
+  sort_wave_rows(a, ((size_t)b * (TB / 64) + (threadIdx.x >> 6)) * WAVE_ROWS);
 }
 
 int grid_for(size_t n, int per_block) {
@@ -699,6 +786,10 @@ size_t cell_sort_scratch_bytes(int n, size_t rows, int shift) {
   return (3 * segs + 1 + nb + 64 + 3 * (size_t)n) * sizeof(uint32_t) + 4 * 256;
 }
 
+SortClear cell_sort_clear(void* scratch, int n, size_t rows, int shift) {
+  return SortClear{(uint32_t*)scratch, rows << cell_sort_split(n, rows, shift)};
+}
+
 void launch_cell_sort(const uint32_t* keys, const uint32_t* order, int n, int shift,
                       size_t rows, uint32_t* keys_sorted, uint32_t* ids_sorted,
                       uint32_t* row_start, void* scratch, const Vec3* pay_in, Vec3* pay_out,
@@ -707,32 +798,42 @@ void launch_cell_sort(const uint32_t* keys, const uint32_t* order, int n, int sh
   const int sshift = shift - split;  // key >> sshift = segment
   const size_t segs = rows << split;
   const size_t nb = (segs + SCAN_TILE - 1) / SCAN_TILE;
-  uint32_t* cnt = (uint32_t*)scratch;
+  uint32_t* cnt = (uint32_t*)scratch;  // zero: cleared by the kernel that wrote the keys
   uint32_t* cursor = cnt + segs;
   uint32_t* seg_start = cursor + segs;
-  uint32_t* partial = seg_start + segs + 1;
+  uint32_t* partial = seg_start + segs + 4;
   uint32_t* bucket = partial + nb + 64;
   uint32_t* tmp_hi = bucket + n;
   uint32_t* tmp_lo = tmp_hi + n;
+  int idbits = 0;
+  while (((size_t)1 << idbits) < (size_t)n) ++idbits;  // at most 31: n is an int
   // (segment << 6 | lane) fits 32 bits below the end marker ~0 for the wavefront sort of
   // the segment numbers
   const bool packed = segs <= ((size_t)1 << 25);
-  fill_u32_kernel<<<grid_for(segs, TB * 8) < 1024 ? grid_for(segs, TB * 8) : 1024, TB, 0, s>>>(
-      cnt, segs, 0u);
   if (packed)
     row_count_kernel<<<grid_for(n, TB * GROUPS), TB, 0, s>>>(keys, order, n, sshift, cnt);
   else
     row_count_loop_kernel<<<grid_for(n, TB), TB, 0, s>>>(keys, order, n, sshift, cnt);
-  scan_reduce_kernel<<<(int)nb, TB, 0, s>>>(cnt, segs, partial);
-  scan_partials_kernel<<<1, TB, 0, s>>>(partial, (int)nb);
-  scan_write_kernel<<<(int)nb, TB, 0, s>>>(cnt, segs, partial, (uint32_t)n, row_start, cursor,
-                                            seg_start, split);
+  // The one-launch scan reads every count before a tile, so its last workgroup's share grows
+  // with the tiles, while three launches cost ~18-20 us up to there: 5.3 us at 8 tiles (128^3
+  // particles), 9.2 at 32 (4 items of them), 14 at 64 (512^2 segments). It needs the counts on
+  // 16 bytes.
+  if (nb <= SCAN1_MAX_BLOCKS && ((uintptr_t)scratch & 15) == 0) {
+    scan_one_kernel<<<(int)nb, SCAN1_TB, 0, s>>>(cnt, segs, (uint32_t)n, row_start, cursor,
+                                                 seg_start, split);
+  } else {
+    scan_reduce_kernel<<<(int)nb, TB, 0, s>>>(cnt, segs, partial);
+    scan_partials_kernel<<<1, TB, 0, s>>>(partial, (int)nb);
+    scan_write_kernel<<<(int)nb, TB, 0, s>>>(cnt, segs, partial, (uint32_t)n, row_start, cursor,
+                                              seg_start, split);
+  }
   if (packed)
-    bucket_kernel<<<grid_for(n, TB * GROUPS), TB, 0, s>>>(keys, order, n, sshift, cursor, bucket);
+    bucket_kernel<<<grid_for(n, TB * GROUPS), TB, 0, s>>>(keys, order, n, sshift, idbits, cursor,
+                                                          bucket);
   else
-    bucket_loop_kernel<<<grid_for(n, TB), TB, 0, s>>>(keys, order, n, sshift, cursor, bucket);
+    bucket_loop_kernel<<<grid_for(n, TB), TB, 0, s>>>(keys, order, n, sshift, idbits, cursor,
+                                                      bucket);
   RowSortArgs a{};
-  a.keys = keys;
   a.row_start = seg_start;
   a.bucket = bucket;
   a.keys_sorted = keys_sorted;
@@ -743,30 +844,17 @@ void launch_cell_sort(const uint32_t* keys, const uint32_t* order, int n, int sh
   a.tmp_hi = tmp_hi;
   a.tmp_lo = tmp_lo;
   a.shift = sshift;
-  a.zmask = (1u << sshift) - 1u;
-  a.idbits = 0;
-  while (a.idbits < 32 && ((size_t)1 << a.idbits) < (size_t)n) ++a.idbits;
+  a.idbits = idbits;
   a.rows = segs;
-  // one wavefront per WAVE_ROWS segments (the grid is not capped at the resident count: waiting
-  // workgroups start as others finish)
-  const size_t need = (segs + WAVE_ROWS * (TB / 64) - 1) / (WAVE_ROWS * (TB / 64));
-  const bool narrow = sshift + a.idbits <= 32;
-  if (narrow)
-    row_sort_wave_kernel<uint32_t><<<(int)need, TB, 0, s>>>(a);
-  else
-    row_sort_wave_kernel<uint64_t><<<(int)need, TB, 0, s>>>(a);
-  const int blk = narrow ? resident_grid<row_sort_block_kernel<uint32_t>, TB>()
-                         : resident_grid<row_sort_block_kernel<uint64_t>, TB>();
-  // rows tested per workgroup step: TB, halved (down to 32) while that leaves resident
-  // workgroups without rows
+  // rows tested per workgroup step of the long tier: TB, halved (down to 32) while that leaves
+  // workgroups of it without rows, so that the long rows spread over the chip
   a.block_rows = TB;
-  while (a.block_rows > 32 && segs / (size_t)a.block_rows < (size_t)blk) a.block_rows /= 2;
+  while (a.block_rows > 32 && segs / (size_t)a.block_rows < LONG_BLOCKS) a.block_rows /= 2;
   const size_t chunks = (segs + a.block_rows - 1) / a.block_rows;
-  const int grid = chunks < (size_t)blk ? (int)chunks : blk;
-  if (narrow)
-    row_sort_block_kernel<uint32_t><<<grid, TB, 0, s>>>(a);
-  else
-    row_sort_block_kernel<uint64_t><<<grid, TB, 0, s>>>(a);
+  a.long_blocks = chunks < LONG_BLOCKS ? (int)chunks : (int)LONG_BLOCKS;
+  // one wavefront per WAVE_ROWS segments
+  const size_t need = (segs + WAVE_ROWS * (TB / 64) - 1) / (WAVE_ROWS * (TB / 64));
+  row_sort_kernel<<<a.long_blocks + (int)need, TB, 0, s>>>(a);
 }
 
 }  // namespace pmr
