@@ -68,7 +68,7 @@ __global__ __launch_bounds__(TB) void stream_frac_kernel(const uint32_t* __restr
                                                          const double* __restrict__ x, int total,
                                                          int log_np3, double scale, int nm,
                                                          Vec3* __restrict__ frac) {
-  const int j = blockIdx.x * TB + threadIdx.x;
+  const int j = xcd_block(blockIdx.x, gridDim.x) * TB + threadIdx.x;
   if (j >= total) return;
   const size_t np3 = (size_t)1 << log_np3;
   const uint32_t g = ids[j];
@@ -106,7 +106,7 @@ __global__ __launch_bounds__(TB) void stream_gather_kernel(const uint32_t* __res
 template <int C, int TY>
 __global__ __launch_bounds__(TB) void paint_kernel(PaintArgs a) {
   extern __shared__ float acc_all[];
-  const int w = threadIdx.x >> 6;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform: a scalar walk
   const int lane = threadIdx.x & 63;
   const int nm = a.nm;
   const int seg = xcd_block(blockIdx.x, gridDim.x) * (TB / 64) + w;  // (item, ix, segment)
@@ -435,8 +435,9 @@ static void paint_launch(const PaintArgs& a, int batch, hipStream_t s) {
 }
 
 template <int C>
-static void paint_dispatch(const PaintArgs& a, int batch, hipStream_t s) {
-  switch (paint_ty(a.nm, C)) {
+static void paint_dispatch(PaintArgs a, int batch, hipStream_t s) {
+  a.group = paint_ty(a.nm, C);
+  switch (paint_share(a.group, (size_t)batch * a.nm * a.nm)) {
     case 1: paint_launch<C, 1>(a, batch, s); break;
     case 2: paint_launch<C, 2>(a, batch, s); break;
     case 4: paint_launch<C, 4>(a, batch, s); break;

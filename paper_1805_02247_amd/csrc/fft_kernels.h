@@ -330,7 +330,8 @@ __global__ __launch_bounds__(NT) void paint_r2c_kernel(PaintArgs a, float2* __re
   __shared__ __attribute__((aligned(16))) float acc_all[LINES * RP];
   __shared__ float2 tw[N];
   make_twiddles<N>(tw);
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform: a scalar walk
+  const int lane = threadIdx.x & 63;
   const int blk = xcd_block(blockIdx.x, gridDim.x);
   const int item = blk / (N * BPX);
   const int rr = blk - item * N * BPX;
@@ -390,20 +391,27 @@ void paint_r2c_launch(const PaintArgs& a, int batch, float2* out, FieldMap om, h
   paint_r2c_kernel<C, TY, N><<<blocks, NT, 0, s>>>(a, out, om);
 }
 
-// TY from the tuned table (0: the default rule paint_r2c_ty), falling back to the default
-// when the tuned value is not a valid shape.
+// The chunking group from the tuned table (0: the default rule paint_r2c_ty), falling back to
+// the default when the tuned value is not a valid shape; rows per wavefront from paint_share
+// (every power of two up to a valid shape is valid).
 template <int C, int N>
-void paint_r2c(const PaintArgs& a, int batch, float2* out, FieldMap om, hipStream_t s) {
+void paint_r2c(PaintArgs a, int batch, float2* out, FieldMap om, hipStream_t s) {
   const int want = get_paint_rows(N, C);
+  a.group = paint_r2c_ty<N>(C);
+#define TYCASE(T)                           \
+  if constexpr (paint_r2c_ty_ok<N, C, T>()) \
+    if (want == T) a.group = T;
+  TYCASE(1) TYCASE(2) TYCASE(4) TYCASE(8) TYCASE(16)
+#undef TYCASE
+  const int ty = paint_share(a.group, (size_t)batch * N * N);
 #define TYCASE(T)                                                  \
   if constexpr (paint_r2c_ty_ok<N, C, T>())                        \
-    if (want == T) {                                               \
+    if (ty == T) {                                                 \
       paint_r2c_launch<C, T, N>(a, batch, out, om, s);             \
       return;                                                      \
     }
   TYCASE(1) TYCASE(2) TYCASE(4) TYCASE(8) TYCASE(16)
 #undef TYCASE
-  paint_r2c_launch<C, paint_r2c_ty<N>(C), N>(a, batch, out, om, s);
 }
 
 // Row pairs (k, H - k) of a c2r tile held in registers: pair e = threadIdx + m NT of the

@@ -61,6 +61,33 @@ __device__ __forceinline__ void seg_scan(float (&v)[NV], uint32_t key) {
   if (eq & (1ull << 32)) seg_step<NV, 0x143, 0xC>(v, key);  // row_bcast:31
 }
 
+// The streams of one 64-particle chunk as they come from memory (one lane's particle).
+template <int C>
+struct RawChunk {
+  uint32_t key;
+  Vec3 f;
+  Vec3 u;  // C = 3
+  bool ok;
+};
+
+// Particles c0 .. c0 + 63 of the sorted stream, those in [beg, end) only.
+template <int C>
+__device__ __forceinline__ RawChunk<C> load_raw(const PaintArgs& a, uint32_t c0, uint32_t beg,
+                                                uint32_t end) {
+  const uint32_t j = c0 + (threadIdx.x & 63);
+  RawChunk<C> r;
+  r.ok = j >= beg && j < end;
+  r.key = 0u;
+  r.f = Vec3{0.f, 0.f, 0.f};
+  r.u = Vec3{0.f, 0.f, 0.f};
+  if (r.ok) {
+    r.key = a.keys[j];
+    r.f = a.frac[j];
+    if constexpr (C == 3) r.u = a.val[j];
+  }
+  return r;
+}
+
 // One 64-particle chunk of a source run: per lane the four (oy, oz) weights of each channel.
 template <int C>
 struct Chunk {
@@ -71,19 +98,19 @@ struct Chunk {
 };
 
 template <int C>
-__device__ __forceinline__ void load_chunk(const PaintArgs& a, uint32_t j, uint32_t end, int ox,
-                                           Chunk<C>& ch) {
+__device__ __forceinline__ void weigh_chunk(const PaintArgs& a, const RawChunk<C>& r, int ox,
+                                            Chunk<C>& ch) {
   const int lane = threadIdx.x & 63;
   const int nm = a.nm;
-  ch.ok = j < end;
+  ch.ok = r.ok;
   ch.key = 0xffffffffu - lane;  // never equal across lanes when invalid
   ch.sy = 0;
   ch.iz = 0;
 #pragma unroll
   for (int q = 0; q < 4 * C; ++q) ch.v[q] = 0.f;
   if (ch.ok) {
-    const uint32_t key = a.keys[j];
-    const Vec3 f = a.frac[j];
+    const uint32_t key = r.key;
+    const Vec3 f = r.f;
     ch.key = key;
     ch.iz = (int)(key & (uint32_t)(nm - 1));
     ch.sy = (int)((key >> a.log_nm) & (uint32_t)(nm - 1));
@@ -92,10 +119,9 @@ __device__ __forceinline__ void load_chunk(const PaintArgs& a, uint32_t j, uint3
     if constexpr (C == 1) {
       val[0] = a.mass * wx;
     } else {
-      const Vec3 u = a.val[j];
-      val[0] = u.x * wx;
-      val[1] = u.y * wx;
-      val[2] = u.z * wx;
+      val[0] = r.u.x * wx;
+      val[1] = r.u.y * wx;
+      val[2] = r.u.z * wx;
     }
     const float wy0 = 1.f - f.y, wy1 = f.y, wz0 = 1.f - f.z, wz1 = f.z;
 #pragma unroll
@@ -113,7 +139,9 @@ __device__ __forceinline__ void load_chunk(const PaintArgs& a, uint32_t j, uint3
 // distinct words, so a plain read-add-write is race-free inside a phase. Different phases
 // (and chunks) may touch the same word from different lanes: a compiler barrier keeps the
 // phases in program order, and LDS instructions of one wavefront execute in issue order,
-// so every word receives its additions in one fixed order.
+// so every word receives its additions in one fixed order. (LDS float atomics without a
+// return, in the same phases, would spare the read's wait; they measured 2-4.5 times slower
+// for the whole paint.)
 #define PMR_PHASE_FENCE() asm volatile("" ::: "memory")
 
 // Float slot of cell iz in an LDS row: plain (iz), or, for rows that the z-pass FFT then
@@ -165,19 +193,19 @@ struct Chunk1 {
 };
 
 template <int C>
-__device__ __forceinline__ void load_chunk1(const PaintArgs& a, uint32_t j, uint32_t end, int ox,
-                                            int iy0, Chunk1<C>& ch) {
+__device__ __forceinline__ void weigh_chunk1(const PaintArgs& a, const RawChunk<C>& r, int ox,
+                                             int iy0, Chunk1<C>& ch) {
   const int lane = threadIdx.x & 63;
   const int nm = a.nm;
-  ch.ok = j < end;
+  ch.ok = r.ok;
   ch.key = 0xffffffffu - lane;  // never equal across lanes when invalid
   ch.iz = 0;
   ch.oy = 0;
 #pragma unroll
   for (int q = 0; q < 2 * C; ++q) ch.v[q] = 0.f;
   if (ch.ok) {
-    const uint32_t key = a.keys[j];
-    const Vec3 f = a.frac[j];
+    const uint32_t key = r.key;
+    const Vec3 f = r.f;
     ch.key = key;
     ch.iz = (int)(key & (uint32_t)(nm - 1));
     const int sy = (int)((key >> a.log_nm) & (uint32_t)(nm - 1));
@@ -187,10 +215,9 @@ __device__ __forceinline__ void load_chunk1(const PaintArgs& a, uint32_t j, uint
     if constexpr (C == 1) {
       val[0] = a.mass * wx;
     } else {
-      const Vec3 u = a.val[j];
-      val[0] = u.x * wx;
-      val[1] = u.y * wx;
-      val[2] = u.z * wx;
+      val[0] = r.u.x * wx;
+      val[1] = r.u.y * wx;
+      val[2] = r.u.z * wx;
     }
     const float wy = ch.oy ? f.y : 1.f - f.y, wz0 = 1.f - f.z, wz1 = f.z;
 #pragma unroll
@@ -222,72 +249,82 @@ __device__ __forceinline__ void deposit1(const Chunk1<C>& ch, float* acc, int nm
   }
 }
 
-// Chunks of 64 particles loaded together before their scans and deposits (memory-level
-// parallelism of a wave's walk over its source rows). One at a time measured 1-3% faster
-// for the paints than two (fewer live registers; the loads of other resident waves cover
-// the latency) and four 6-20% slower.
-#ifndef PMR_PAINT_CHUNKS
-#define PMR_PAINT_CHUNKS 1
-#endif
-
 // Deposits of all particles that reach the TY target rows [iy0, iy0 + TY) of plane ix of one
 // item, into the wavefront's rows acc (zeroed by the caller): the two source planes ix - 1
 // and ix, each as one or two contiguous runs of source rows. Chunks are deposited in stream
-// order, so the result does not depend on how many are in flight.
+// order; the streams of the next one are loaded before the current one is scanned, also from
+// one run to the next, so that a wavefront's walk does not wait for memory at every chunk.
+//
+// The chunks are cut as if the wavefront owned the whole group of a.group (>= TY, a power of
+// two) target rows that its rows lie in: the scan of a run of equal cells depends on where in
+// its chunk the run lies, so a group's rows come out bitwise the same whether one wavefront
+// owns them all or several share them. Sharing shortens each wavefront's serial walk of
+// dependent chunks at the price of reading the chunks at the seams more than once.
 template <int C, int TY, bool PAD = false>
 __device__ __forceinline__ void paint_rows(const PaintArgs& a, int item, int ix, int iy0,
                                            float* acc, int rp) {
-  constexpr int CH = PMR_PAINT_CHUNKS;
-  const int lane = threadIdx.x & 63;
   const int nm = a.nm;
   const int rows_item = item * nm * nm;
   // main runs of source rows [iy0 - 1, iy0 + TY - 1] of both planes (from row 0 when iy0 - 1
-  // wraps; row nm - 1 is then a second run)
+  // wraps; row nm - 1 is then a second run), and the first source row of the group's run
   const int lo0 = iy0 == 0 ? 0 : iy0 - 1, hi0 = iy0 + TY - 1;
-  uint32_t beg0[2], end0[2];
-#pragma unroll
-  for (int ox = 0; ox < 2; ++ox) {
-    const int rbase = rows_item + ((ix - ox + nm) & (nm - 1)) * nm;
-    beg0[ox] = a.row_start[rbase + lo0];
-    end0[ox] = a.row_start[rbase + hi0 + 1];
+  const int g0 = iy0 & ~(a.group - 1);
+  const int glo = g0 == 0 ? 0 : g0 - 1;
+  const uint32_t* rs0 = a.row_start + rows_item + ix * nm;
+  const uint32_t* rs1 = a.row_start + rows_item + ((ix - 1 + nm) & (nm - 1)) * nm;
+  // one run of the walk: its first chunk, its particles [beg, end); scalar registers, so that
+  // the walk itself costs no vector instructions
+  struct Run {
+    uint32_t cut, beg, end;
+  };
+  auto uni = [](uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); };
+  uint32_t v[10] = {rs0[glo], rs0[lo0], rs0[hi0 + 1], rs1[glo], rs1[lo0], rs1[hi0 + 1], 0, 0, 0, 0};
+  if (iy0 == 0) {
+    v[6] = rs0[nm - 1];
+    v[7] = rs0[nm];
+    v[8] = rs1[nm - 1];
+    v[9] = rs1[nm];
   }
+#pragma unroll
+  for (int i = 0; i < 10; ++i) v[i] = uni(v[i]);
+  auto main_run = [](uint32_t g, uint32_t b, uint32_t e) {
+    return Run{b == e ? e : g + ((b - g) & ~63u), b, e};
+  };
+  Run now = main_run(v[0], v[1], v[2]), n1 = Run{v[6], v[6], v[7]};
+  Run n2 = main_run(v[3], v[4], v[5]), n3 = Run{v[8], v[8], v[9]};
+  int run = 0;  // 0, 1: source plane ix; 2, 3: ix - 1
+  uint32_t c0 = now.cut;
+  auto settle = [&]() {  // on to the next run while this one is done; false after the last
+    while (c0 >= now.end) {
+      if (run == 3) return false;
+      ++run;
+      now = n1;
+      n1 = n2;
+      n2 = n3;
+      c0 = now.cut;
+    }
+    return true;
+  };
+  bool more = settle();
+  RawChunk<C> next;
+  if (more) next = load_raw<C>(a, c0, now.beg, now.end);
 #pragma unroll 1
-  for (int ox = 0; ox < 2; ++ox) {
-    const int rbase = rows_item + ((ix - ox + nm) & (nm - 1)) * nm;
-#pragma unroll 1
-    for (int run = 0; run < 2; ++run) {
-      uint32_t beg, end;
-      if (run == 0) {
-        beg = ox == 0 ? beg0[0] : beg0[1];
-        end = ox == 0 ? end0[0] : end0[1];
-      } else {
-        if (iy0 != 0) continue;
-        beg = a.row_start[rbase + nm - 1];
-        end = a.row_start[rbase + nm];
-      }
-#pragma unroll 1
-      for (uint32_t c0 = beg; c0 < end; c0 += 64 * CH) {
-        if constexpr (TY == 1) {
-          Chunk1<C> ch[CH];
-#pragma unroll
-          for (int q = 0; q < CH; ++q)
-            load_chunk1<C>(a, c0 + 64 * q + lane, end, ox, iy0, ch[q]);
-#pragma unroll
-          for (int q = 0; q < CH; ++q) seg_scan<2 * C>(ch[q].v, ch[q].key);
-#pragma unroll
-          for (int q = 0; q < CH; ++q)
-            if (q == 0 || c0 + 64 * q < end) deposit1<C, PAD>(ch[q], acc, nm, rp);
-        } else {
-          Chunk<C> ch[CH];
-#pragma unroll
-          for (int q = 0; q < CH; ++q) load_chunk<C>(a, c0 + 64 * q + lane, end, ox, ch[q]);
-#pragma unroll
-          for (int q = 0; q < CH; ++q) seg_scan<4 * C>(ch[q].v, ch[q].key);
-#pragma unroll
-          for (int q = 0; q < CH; ++q)
-            if (q == 0 || c0 + 64 * q < end) deposit<C, TY, PAD>(ch[q], acc, nm, iy0, rp);
-        }
-      }
+  while (more) {
+    const RawChunk<C> cur = next;
+    const int ox = run >> 1;
+    c0 += 64;
+    more = settle();
+    if (more) next = load_raw<C>(a, c0, now.beg, now.end);
+    if constexpr (TY == 1) {
+      Chunk1<C> ch;
+      weigh_chunk1<C>(a, cur, ox, iy0, ch);
+      seg_scan<2 * C>(ch.v, ch.key);
+      deposit1<C, PAD>(ch, acc, nm, rp);
+    } else {
+      Chunk<C> ch;
+      weigh_chunk<C>(a, cur, ox, ch);
+      seg_scan<4 * C>(ch.v, ch.key);
+      deposit<C, TY, PAD>(ch, acc, nm, iy0, rp);
     }
   }
 }

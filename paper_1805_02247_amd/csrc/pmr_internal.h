@@ -119,9 +119,22 @@ struct PaintArgs {
   const Vec3* val;        // sorted values (C = 3), or nullptr (C = 1, constant mass)
   const uint32_t* row_start;
   int nm, log_nm;
+  int group;                // target rows per chunking group (set by the launchers)
   float mass, bias;
   float* out;               // [B][C][nm^3]
 };
+
+// Rows per wavefront for a paint whose chunks are cut for `group` rows and whose target rows
+// number `rows` in all: the group, halved while that leaves the launch fewer than 8192
+// wavefronts (256 CUs x 32), since a launch that does not fill the chip lasts as long as its
+// longest walk. 128^3 on 128^3, one item (2048 groups of 8 rows): 56 us with whole groups, 33-36
+// with 2 rows each, 38 with 1; 32^3: 19 -> 10 us. Where the chip is full sharing only adds the
+// chunks read twice: 128^3 x 4 (8192 groups) 80 us whole, 90 with 4 rows each.
+inline int paint_share(int group, size_t rows) {
+  int ty = group;
+  while (ty > 1 && rows / (size_t)ty < 8192) ty /= 2;
+  return ty;
+}
 
 // Kinds of fused k-space operation performed in the outermost-axis pass.
 enum XOp : int {
