@@ -16,14 +16,20 @@ namespace {
 constexpr int TB = 256;
 constexpr int DOT_BLOCKS = 1024;  // partial sums per inner product (at most)
 
+// Sum over the block in a fixed tree (pairs 128 apart, then 64, 32, ... 1), on every thread;
+// the last six levels stay in the lanes of the first wavefront.
 __device__ __forceinline__ double block_sum(double v, double* sh) {
   const int t = threadIdx.x;
+  static_assert(TB == 256, "four wavefronts");
   sh[t] = v;
   __syncthreads();
-  for (int d = TB / 2; d > 0; d >>= 1) {
-    if (t < d) sh[t] += sh[t + d];
-    __syncthreads();
+  if (t < 64) {
+    double x = (sh[t] + sh[t + 128]) + (sh[t + 64] + sh[t + 192]);
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) x += __shfl_down(x, d, 64);
+    if (t == 0) sh[0] = x;
   }
+  __syncthreads();
   const double r = sh[0];
   __syncthreads();
   return r;
@@ -45,6 +51,7 @@ __device__ __forceinline__ void dot_partial_body(const float* __restrict__ a,
   __shared__ double sh[TB];
   double acc = 0.0;
   const size_t stride = (size_t)gridDim.x * TB;
+#pragma unroll 4
   for (size_t i = (size_t)blockIdx.x * TB + threadIdx.x; i < n; i += stride)
     acc += (double)a[i] * (double)b[i];
   const double s = block_sum(acc, sh);
@@ -60,18 +67,6 @@ __device__ __forceinline__ void dot_final_body(const double* __restrict__ partia
   for (int i = threadIdx.x; i < np; i += TB) acc += partial[i];
   const double s = block_sum(acc, sh);
   if (threadIdx.x == 0) out[0] = den ? s / den[0] : s;
-}
-
-__device__ __forceinline__ void axpy_body(size_t n, float c, const float* __restrict__ x,
-                                          float* __restrict__ y) {
-  const size_t stride = (size_t)gridDim.x * TB;
-  for (size_t i = (size_t)blockIdx.x * TB + threadIdx.x; i < n; i += stride)
-    y[i] = __fmaf_rn(c, x[i], y[i]);
-}
-
-__device__ __forceinline__ void scale_body(size_t n, float c, float* __restrict__ x) {
-  const size_t stride = (size_t)gridDim.x * TB;
-  for (size_t i = (size_t)blockIdx.x * TB + threadIdx.x; i < n; i += stride) x[i] *= c;
 }
 
 __device__ __forceinline__ void axpby_body(size_t n, float alpha, const float* a, float beta,
@@ -93,19 +88,131 @@ __global__ __launch_bounds__(TB) void dot_final_kernel(const double* __restrict_
   dot_final_body(partial, np, den, out);
 }
 
-// y += sign * (A - B) * x with A, B device scalars (B nullable).
-__global__ __launch_bounds__(TB) void axpy_dev_kernel(size_t n, const double* __restrict__ A,
-                                                      const double* __restrict__ B, double sign,
-                                                      const float* __restrict__ x,
-                                                      float* __restrict__ y) {
-  axpy_body(n, (float)(sign * (A[0] - (B ? B[0] : 0.0))), x, y);
+// sum of the partials, on every thread of the block, in the fixed tree of dot_final_body.
+__device__ __forceinline__ double dot_total(const double* __restrict__ partial, int np) {
+  __shared__ double sh[TB];
+  double acc = 0.0;
+  for (int i = threadIdx.x; i < np; i += TB) acc += partial[i];
+  return block_sum(acc, sh);
 }
 
-// x *= sign * num / den (device scalars).
-__global__ __launch_bounds__(TB) void scale_dev_kernel(size_t n, const double* __restrict__ num,
-                                                       const double* __restrict__ den, double sign,
-                                                       float* __restrict__ x) {
-  scale_body(n, (float)(sign * num[0] / den[0]), x);
+// ---------------------------------------------------------------- two-loop recursion
+// d = -H g over a history of `count` pairs in 2 count + 1 launches: each one finishes the inner
+// product of the launch before (every workgroup sums its at most DOT_BLOCKS partials, in the
+// same tree), updates d with it, and takes the partial sums of the next inner product on
+// the values it has just written. An inner product and an update as launches of their own (two
+// and one) spent 4-5 us each on as little work: 63 launches, 285 us at 128^3 modes with 10
+// pairs; 21 launches and 190 us now. The partial sums alternate between two arrays of DOT_BLOCKS.
+// Every element and sum is the same operation in the same order as in separate launches.
+constexpr int LOOP_U = 4;
+enum LoopKind { LOOP_FIRST = 0, LOOP_DOWN = 1, LOOP_UP = 2 };
+
+struct LoopArgs {
+  size_t n;
+  int kind, j;          // history entry j, newest first
+  const float* S;       // [slots][n]
+  const float* Y;
+  const double* sy;     // per slot
+  const double* yy;
+  const float* g;
+  float* d;
+  double* partial;      // [2][DOT_BLOCKS]
+  double* alpha;        // per slot
+  const float* last;    // nullable: the last launch also takes the partials of last . d
+};
+
+// slot(k): the slot of history entry k.
+template <class Slot>
+__device__ __forceinline__ void loop_body(const LoopArgs& a, int count, Slot slot) {
+  const size_t n = a.n;
+  const int np = (int)gridDim.x;
+  // which of the two arrays the launch reads: launches of one recursion take turns
+  const int turn = a.kind == LOOP_FIRST ? 1 : a.kind == LOOP_DOWN ? a.j : 2 * count - 1 - a.j;
+  const double* in = a.partial + (size_t)(turn & 1) * DOT_BLOCKS;
+  double* out = a.partial + (size_t)((turn + 1) & 1) * DOT_BLOCKS;
+  const bool down_end = a.kind == LOOP_DOWN && a.j + 1 == count;
+  const bool end = a.kind == LOOP_UP ? a.j == 0 : a.kind == LOOP_FIRST && count == 0;
+  const float* x = a.g;
+  if (a.kind == LOOP_DOWN) x = a.Y + slot(a.j) * n;
+  if (a.kind == LOOP_UP) x = a.S + slot(a.j) * n;
+  const float* v = nullptr;  // the other factor of the next inner product
+  if (end)
+    v = a.last;
+  else if (a.kind == LOOP_FIRST)
+    v = a.S + slot(0) * n;
+  else if (a.kind == LOOP_DOWN)
+    v = down_end ? a.Y + slot(a.j) * n : a.S + slot(a.j + 1) * n;
+  else
+    v = a.Y + slot(a.j - 1) * n;
+  // LOOP_U elements per thread in flight; the first ones are asked for before the inner product
+  // is finished, which does not need them
+  const size_t stride = (size_t)gridDim.x * TB;
+  size_t k0 = (size_t)blockIdx.x * TB + threadIdx.x;
+  float xr[LOOP_U], dr[LOOP_U], vr[LOOP_U];
+  auto load = [&](size_t k) {
+#pragma unroll
+    for (int u = 0; u < LOOP_U; ++u) {
+      const size_t e = k + u * stride;
+      const bool in = e < n;
+      xr[u] = in ? x[e] : 0.f;
+      dr[u] = in && a.kind != LOOP_FIRST ? a.d[e] : 0.f;
+      vr[u] = in && v ? v[e] : 0.f;
+    }
+  };
+  load(k0);
+  float c = 0.f, gamma = 1.f;
+  if (a.kind != LOOP_FIRST) {
+    const size_t i = slot(a.j);
+    const double q = dot_total(in, np) / a.sy[i];
+    if (a.kind == LOOP_DOWN) {  // alpha_i = s_i.q / s_i.y_i; q -= alpha_i y_i
+      if (blockIdx.x == 0 && threadIdx.x == 0) a.alpha[i] = q;
+      c = (float)(-1.0 * (q - 0.0));
+    } else {  // beta = y_i.r / s_i.y_i; r += (alpha_i - beta) s_i
+      c = (float)(1.0 * (a.alpha[i] - q));
+    }
+  }
+  if (down_end) {  // r = gamma q, gamma = s.y / y.y of the newest pair
+    const size_t i = slot(0);
+    gamma = (float)(1.0 * a.sy[i] / a.yy[i]);
+  }
+  double acc = 0.0;
+  while (k0 < n) {
+    float xc[LOOP_U], dc[LOOP_U], vc[LOOP_U];
+#pragma unroll
+    for (int u = 0; u < LOOP_U; ++u) {
+      xc[u] = xr[u];
+      dc[u] = dr[u];
+      vc[u] = vr[u];
+    }
+    const size_t at = k0;
+    k0 += LOOP_U * stride;
+    if (k0 < n) load(k0);
+#pragma unroll
+    for (int u = 0; u < LOOP_U; ++u) {
+      const size_t e = at + u * stride;
+      if (e < n) {
+        float r = a.kind == LOOP_FIRST ? __fmaf_rn(0.f, xc[u], __fmul_rn(1.f, xc[u]))
+                                       : __fmaf_rn(c, xc[u], dc[u]);
+        if (down_end) r *= gamma;
+        if (end) r = __fmaf_rn(0.f, r, __fmul_rn(-1.f, r));
+        a.d[e] = r;
+        if (v) acc += (double)vc[u] * (double)r;
+      }
+    }
+  }
+  if (v) {
+    __shared__ double sh[TB];
+    const double s = block_sum(acc, sh);
+    if (threadIdx.x == 0) out[blockIdx.x] = s;
+  }
+}
+
+struct LoopOrder {
+  unsigned char slot[64];
+};
+
+__global__ __launch_bounds__(TB) void loop_kernel(LoopArgs a, int count, LoopOrder o) {
+  loop_body(a, count, [&](int k) { return (size_t)o.slot[k]; });
 }
 
 // out = alpha a + beta b (host scalars; out may alias a or b).
@@ -120,67 +227,178 @@ unsigned stream_grid(size_t n) {
 }
 
 // ---------------------------------------------------------------- binned spectra
-constexpr int PS_THREADS = 2048;  // accumulating threads (each owns a contiguous mode range)
+constexpr int PS_SLOTS = 2048;   // partial sums per shell the work buffer has room for
+constexpr int PS_BLOCKS = 1024;   // of them used: workgroups at most
+constexpr int PS_ROWS = 8;       // rows (ix, iy) that share their shells: (+-i, +-j), (+-j, +-i)
 
-// Thread t accumulates modes [t chunk, (t + 1) chunk) of the half spectrum into its own
-// slice work[q][bin][t] (q = count, |a|^2, |b|^2, Re a conj b; Hermitian weight applied),
-// flushing its running sums whenever the shell changes (consecutive kz rarely change it).
-__global__ __launch_bounds__(TB) void power_partial_kernel(int n, const float2* __restrict__ a,
-                                                           const float2* __restrict__ b,
-                                                           int nbins, size_t chunk,
-                                                           double* __restrict__ work) {
-  const int t = blockIdx.x * TB + threadIdx.x;
-  if (t >= PS_THREADS) return;
-  const int h = n / 2 + 1;
-  const size_t total = (size_t)n * n * h;
-  for (int q = 0; q < 4; ++q)
-    for (int k = 0; k < nbins; ++k) work[((size_t)q * nbins + k) * PS_THREADS + t] = 0.0;
-  const size_t lo = (size_t)t * chunk;
-  const size_t hi = lo + chunk < total ? lo + chunk : total;
-  int cur = -1;
-  double acc[4] = {0.0, 0.0, 0.0, 0.0};
-  auto flush = [&]() {
-    if (cur >= 0)
-      for (int q = 0; q < 4; ++q) work[((size_t)q * nbins + cur) * PS_THREADS + t] += acc[q];
-    acc[0] = acc[1] = acc[2] = acc[3] = 0.0;
-  };
-  for (size_t e = lo; e < hi; ++e) {
-    const int iz = (int)(e % h);
-    const size_t r = e / h;
-    const int iy = (int)(r % n), ix = (int)(r / n);
-    const long mx = ix <= n / 2 ? ix : ix - n, my = iy <= n / 2 ? iy : iy - n, mz = iz;
-    const long m2 = mx * mx + my * my + mz * mz;
-    if (m2 == 0) continue;
-    int bin = (int)sqrt((double)m2);  // floor(sqrt(m2)), corrected to the exact integer
-    while ((long)(bin + 1) * (bin + 1) <= m2) ++bin;
-    while ((long)bin * bin > m2) --bin;
-    if (bin >= nbins) continue;
-    if (bin != cur) {
-      flush();
-      cur = bin;
-    }
-    const double w = (iz == 0 || 2 * iz == n) ? 1.0 : 2.0;
-    const float2 av = a[e], bv = b[e];
-    acc[0] += w;
-    acc[1] += w * ((double)av.x * av.x + (double)av.y * av.y);
-    acc[2] += w * ((double)bv.x * bv.x + (double)bv.y * bv.y);
-    acc[3] += w * ((double)av.x * bv.x + (double)av.y * bv.y);
-  }
-  flush();
+// Highest shell that holds a mode: floor(sqrt(3) n / 2).
+int top_shell(int n) {
+  const long m2 = 3L * (n / 2) * (n / 2);
+  long k = 0;
+  while ((k + 1) * (k + 1) <= m2) ++k;
+  return (int)k;
 }
 
-// out[q][bin] = sum over threads of work[q][bin][t] (fixed tree); spectra normalised by the
-// mode count and L^3 / n^6 once the count is known (q = 0 block of each bin does it).
+// A wavefront sums the modes of one set of rows at a time: the up to eight rows (+-i, +-j) and
+// (+-j, +-i), 0 <= j <= i <= n / 2, have the same shells along kz, so each lane first adds its
+// kz of all of them (16 coalesced loads in flight), and one segmented scan over the lanes,
+// whose shells ascend with kz, then leaves every shell's sum in the last lane of its run. That
+// lane adds it to the wavefront's own LDS slice: one lane per word and instruction, in
+// program order, so the sums are bitwise reproducible. The workgroup's slices are added in
+// order and go out as partial sums.
+// Bound by reading the two spectra once (135 MB at n = 256). One thread per contiguous range
+// of modes, each with its slice of a global table, in 8 workgroups of uncoalesced 8-byte
+// reads, took 5200 us there, this 34.
+template <int CTRL, int RMASK>
+__device__ __forceinline__ uint32_t lane_move(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, RMASK, 0xF, RMASK == 0xF);
+}
+template <int CTRL, int RMASK>
+__device__ __forceinline__ double lane_move(double v) {
+  const uint64_t u = (uint64_t)__double_as_longlong(v);
+  const uint32_t lo = lane_move<CTRL, RMASK>((uint32_t)u);
+  const uint32_t hi = lane_move<CTRL, RMASK>((uint32_t)(u >> 32));
+  return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
+struct ShellSums {
+  double v[3];  // |a|^2, |b|^2, Re a conj b
+  uint32_t c;   // modes
+};
+
+// One step of the segmented scan: keys ascend over the lanes and are never 0 in a lane that a
+// move could leave without a source (such a lane reads key 0).
+template <int CTRL, int RMASK>
+__device__ __forceinline__ void shell_step(ShellSums& s, uint32_t key) {
+  const uint32_t k = lane_move<CTRL, RMASK>(key);
+  ShellSums o;
+#pragma unroll
+  for (int q = 0; q < 3; ++q) o.v[q] = lane_move<CTRL, RMASK>(s.v[q]);
+  o.c = lane_move<CTRL, RMASK>(s.c);
+  if (k == key) {
+#pragma unroll
+    for (int q = 0; q < 3; ++q) s.v[q] += o.v[q];
+    s.c += o.c;
+  }
+}
+
+__global__ __launch_bounds__(TB) void power_partial_kernel(int n, const float2* __restrict__ a,
+                                                           const float2* __restrict__ b,
+                                                           int shells, int items, int nbins,
+                                                           double* __restrict__ work) {
+  extern __shared__ double ps_lds[];  // per wavefront: sums [3][shells], then counts [shells]
+  const int lane = threadIdx.x & 63, waves = blockDim.x >> 6;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int h = n / 2 + 1;
+  double* sum = ps_lds + (size_t)w * 3 * shells;
+  uint32_t* cnt = reinterpret_cast<uint32_t*>(ps_lds + (size_t)waves * 3 * shells) + w * shells;
+  for (int k = lane; k < 3 * shells; k += 64) sum[k] = 0.0;
+  for (int k = lane; k < shells; k += 64) cnt[k] = 0u;
+  // one chunk of 64 kz of one set of rows at a time, the next one's loads in flight
+  struct Chunk {
+    float2 a[PS_ROWS], b[PS_ROWS];
+    int ij2, z0;
+    uint32_t use;
+  };
+  const int step = gridDim.x * waves;
+  int t = blockIdx.x * waves + w, z0 = 0;
+  auto load = [&](Chunk& c) {
+    // t = i (i + 1) / 2 + j
+    int i = (int)((sqrtf(8.f * (float)t + 1.f) - 1.f) * 0.5f);
+    while ((i + 1) * (i + 2) / 2 <= t) ++i;
+    while (i * (i + 1) / 2 > t) --i;
+    const int j = t - i * (i + 1) / 2;
+    // distinct indices of +-i and of +-j, and whether (j, i) differs from (i, j)
+    const bool mi = i > 0 && 2 * i < n, mj = j > 0 && 2 * j < n, sw = i != j;
+    c.ij2 = i * i + j * j;
+    c.z0 = z0;
+    c.use = 0u;
+    const bool in = z0 + lane < h;
+#pragma unroll
+    for (int r = 0; r < PS_ROWS; ++r) {
+      const bool ni = (r & 1) != 0, nj = (r & 2) != 0, flip = (r & 4) != 0;
+      const bool use = (!ni || mi) && (!nj || mj) && (!flip || sw);
+      c.use |= (use ? 1u : 0u) << r;
+      c.a[r] = c.b[r] = make_float2(0.f, 0.f);
+      if (use && in) {
+        const int ii = ni ? n - i : i, jj = nj ? n - j : j;
+        const size_t e = ((size_t)(flip ? jj : ii) * n + (flip ? ii : jj)) * h + z0 + lane;
+        c.a[r] = a[e];
+        c.b[r] = b[e];
+      }
+    }
+  };
+  Chunk next;
+  if (t < items) load(next);
+  while (t < items) {
+    const Chunk c = next;
+    z0 += 64;
+    if (z0 >= h) {
+      z0 = 0;
+      t += step;
+    }
+    if (t < items) load(next);
+    const int iz = c.z0 + lane;
+    const bool in = iz < h;
+    const int m2 = c.ij2 + iz * iz;
+    int shell = (int)sqrtf((float)m2);  // floor(sqrt(m2)), corrected to the exact integer
+    shell += (shell + 1) * (shell + 1) <= m2 ? 1 : 0;
+    shell -= shell * shell > m2 ? 1 : 0;
+    const double wz = (iz == 0 || 2 * iz == n) ? 1.0 : 2.0;
+    ShellSums s{{0.0, 0.0, 0.0}, 0u};
+    if (in && m2 > 0) {
+#pragma unroll
+      for (int r = 0; r < PS_ROWS; ++r)
+        if ((c.use >> r) & 1u) {
+          const float2 av = c.a[r], bv = c.b[r];
+          s.v[0] += wz * ((double)av.x * av.x + (double)av.y * av.y);
+          s.v[1] += wz * ((double)bv.x * bv.x + (double)bv.y * bv.y);
+          s.v[2] += wz * ((double)av.x * bv.x + (double)av.y * bv.y);
+          s.c += (uint32_t)wz;
+        }
+    }
+    // shell 0 holds the excluded mode only; lanes past the row get keys of their own
+    const uint32_t key = in ? (uint32_t)shell + 1u : 0x40000000u + (uint32_t)lane;
+    shell_step<0x111, 0xF>(s, key);  // row_shr 1, 2, 4, 8
+    shell_step<0x112, 0xF>(s, key);
+    shell_step<0x114, 0xF>(s, key);
+    shell_step<0x118, 0xF>(s, key);
+    shell_step<0x142, 0xA>(s, key);  // row_bcast 15, 31
+    shell_step<0x143, 0xC>(s, key);
+    const uint32_t up = (uint32_t)__shfl_down((int)key, 1, 64);
+    if (in && (lane == 63 || up != key) && shell > 0 && shell < shells) {
+#pragma unroll
+      for (int q = 0; q < 3; ++q) sum[q * shells + shell] += s.v[q];
+      cnt[shell] += s.c;
+    }
+  }
+  __syncthreads();
+  const uint32_t* c0 = reinterpret_cast<const uint32_t*>(ps_lds + (size_t)waves * 3 * shells);
+  for (int k = threadIdx.x; k < shells; k += blockDim.x) {
+    double v[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int u = 0; u < waves; ++u) {
+      v[0] += (double)c0[u * shells + k];
+#pragma unroll
+      for (int q = 0; q < 3; ++q) v[q + 1] += ps_lds[((size_t)u * 3 + q) * shells + k];
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) work[((size_t)q * nbins + k) * PS_SLOTS + blockIdx.x] = v[q];
+  }
+}
+
+// out[q][bin] = sum over the workgroups of work[q][bin][block] (fixed tree); spectra normalised
+// by the mode count and L^3 / n^6. Shells past the last that holds a mode are zero.
 __global__ __launch_bounds__(TB) void power_reduce_kernel(const double* __restrict__ work,
-                                                          int nbins, double norm,
-                                                          double* __restrict__ out) {
+                                                          int nbins, int shells, int blocks,
+                                                          double norm, double* __restrict__ out) {
   __shared__ double sh[TB];
   const int bin = blockIdx.x;
   double s[4];
   for (int q = 0; q < 4; ++q) {
     double acc = 0.0;
-    const double* src = work + ((size_t)q * nbins + bin) * PS_THREADS;
-    for (int t = threadIdx.x; t < PS_THREADS; t += TB) acc += src[t];
+    const double* src = work + ((size_t)q * nbins + bin) * PS_SLOTS;
+    if (bin < shells)
+      for (int t = threadIdx.x; t < blocks; t += TB) acc += src[t];
     s[q] = block_sum(acc, sh);
   }
   if (threadIdx.x == 0) {
@@ -192,7 +410,8 @@ __global__ __launch_bounds__(TB) void power_reduce_kernel(const double* __restri
 
 }  // namespace
 
-size_t vec_work_doubles(size_t n) { return (size_t)dot_blocks(n) + 64; }
+// Partial sums of the three inner products of a candidate pair (the recursion uses two arrays).
+size_t vec_work_doubles(size_t) { return (size_t)3 * DOT_BLOCKS + 64; }
 
 void launch_vec_dot(size_t n, const float* a, const float* b, const double* den, double* out,
                     double* work, hipStream_t s) {
@@ -207,26 +426,19 @@ void launch_vec_axpby(size_t n, float alpha, const float* a, float beta, const f
 }
 
 // d = -H g by the two-loop recursion. order[0..count): history slots, newest first. sy, yy:
-// s.y and y.y per slot (device). scal: 2 m + 2 device doubles (alpha per slot, beta).
-void launch_lbfgs_direction(size_t n, int m, int count, const int* order, const float* S,
+// s.y and y.y per slot (device). scal: device doubles, alpha per slot.
+void launch_lbfgs_direction(size_t n, int count, const int* order, const float* S,
                             const float* Y, const double* sy, const double* yy, const float* g,
                             float* d, double* work, double* scal, hipStream_t s) {
-  const unsigned gs = stream_grid(n);
-  axpby_kernel<<<gs, TB, 0, s>>>(n, 1.f, g, 0.f, g, d);  // q = g
-  double* alpha = scal;
-  double* beta = scal + m;
-  for (int j = 0; j < count; ++j) {  // newest to oldest
-    const int i = order[j];
-    launch_vec_dot(n, S + (size_t)i * n, d, sy + i, alpha + i, work, s);  // alpha_i = s.q / s.y
-    axpy_dev_kernel<<<gs, TB, 0, s>>>(n, alpha + i, nullptr, -1.0, Y + (size_t)i * n, d);
-  }
-  if (count > 0) scale_dev_kernel<<<gs, TB, 0, s>>>(n, sy + order[0], yy + order[0], 1.0, d);
-  for (int j = count - 1; j >= 0; --j) {  // oldest to newest
-    const int i = order[j];
-    launch_vec_dot(n, Y + (size_t)i * n, d, sy + i, beta, work, s);  // beta = y.r / s.y
-    axpy_dev_kernel<<<gs, TB, 0, s>>>(n, alpha + i, beta, 1.0, S + (size_t)i * n, d);
-  }
-  axpby_kernel<<<gs, TB, 0, s>>>(n, -1.f, d, 0.f, d, d);
+  const int nb = dot_blocks(n);
+  LoopArgs a{n, LOOP_FIRST, 0, S, Y, sy, yy, g, d, work, scal, nullptr};
+  LoopOrder o{};
+  for (int j = 0; j < count; ++j) o.slot[j] = (unsigned char)order[j];
+  loop_kernel<<<nb, TB, 0, s>>>(a, count, o);
+  a.kind = LOOP_DOWN;
+  for (a.j = 0; a.j < count; ++a.j) loop_kernel<<<nb, TB, 0, s>>>(a, count, o);  // newest first
+  a.kind = LOOP_UP;
+  for (a.j = count - 1; a.j >= 0; --a.j) loop_kernel<<<nb, TB, 0, s>>>(a, count, o);
 }
 
 // ---------------------------------------------------------------- device-driven L-BFGS
@@ -241,10 +453,7 @@ enum Gate {
   G_DIR = 2,   // accepted and still running (the next direction)
   G_RESET = 3  // ... and that direction was not a descent direction
 };
-constexpr int NO_SLOT = -1;   // the vector as given
-constexpr int NEW_SLOT = -2;  // slot of the candidate pair (state.slot)
-// j >= 0: history entry j, slot state.order[j]; a kernel with jc >= 0 runs only while
-// jc < state.count.
+// A kernel with jc >= 0 (history entry jc) runs only while jc < state.count.
 
 __device__ __forceinline__ bool gate_open(const pmr_lbfgs_state* st, int gate, int jc) {
   bool on;
@@ -259,10 +468,6 @@ __device__ __forceinline__ bool gate_open(const pmr_lbfgs_state* st, int gate, i
   return on && (jc < 0 || jc < st->count);
 }
 
-__device__ __forceinline__ size_t slot_of(const pmr_lbfgs_state* st, int j) {
-  return j == NO_SLOT ? 0 : (size_t)(j == NEW_SLOT ? st->slot : st->order[j]);
-}
-
 __device__ __forceinline__ double* f_hist(pmr_lbfgs_state* st) {
   return reinterpret_cast<double*>(st + 1);
 }
@@ -271,48 +476,70 @@ __device__ __forceinline__ long long* clock_hist(pmr_lbfgs_state* st) {
 }
 
 __global__ __launch_bounds__(TB) void lb_dot_partial_kernel(const pmr_lbfgs_state* st, int gate,
-                                                            int jc, const float* A, int ja,
-                                                            const float* B, int jb, size_t n,
-                                                            double* partial) {
-  if (!gate_open(st, gate, jc)) return;
-  dot_partial_body(A + slot_of(st, ja) * n, B + slot_of(st, jb) * n, n, partial);
+                                                            const float* A, const float* B,
+                                                            size_t n, double* partial) {
+  if (!gate_open(st, gate, -1)) return;
+  dot_partial_body(A, B, n, partial);
 }
 
-__global__ __launch_bounds__(TB) void lb_dot_final_kernel(const pmr_lbfgs_state* st, int gate,
-                                                          int jc, const double* partial, int np,
-                                                          const double* den, int jden,
-                                                          double* out, int jout) {
-  if (!gate_open(st, gate, jc)) return;
-  dot_final_body(partial, np, den ? den + slot_of(st, jden) : nullptr, out + slot_of(st, jout));
+// One launch of the recursion over the device-held history (entry j >= count: nothing).
+__global__ __launch_bounds__(TB) void lb_loop_kernel(const pmr_lbfgs_state* st, LoopArgs a) {
+  if (!gate_open(st, G_DIR, a.kind == LOOP_FIRST ? -1 : a.j)) return;
+  loop_body(a, st->count, [&](int k) { return (size_t)st->order[k]; });
 }
 
-// y += sign * (A[slot] - B) * X[slot]
-__global__ __launch_bounds__(TB) void lb_axpy_kernel(const pmr_lbfgs_state* st, int gate, int jc,
-                                                     size_t n, const double* A, int ja,
-                                                     const double* B, double sign,
-                                                     const float* X, int jx, float* y) {
-  if (!gate_open(st, gate, jc)) return;
-  axpy_body(n, (float)(sign * (A[slot_of(st, ja)] - (B ? B[0] : 0.0))), X + slot_of(st, jx) * n,
-            y);
+// The candidate pair of an accepted trial, s = xt - x and y = gt - g, into its slot, with the
+// partial sums of s.y, y.y and s.s.
+__global__ __launch_bounds__(TB) void lb_pair_kernel(const pmr_lbfgs_state* st, size_t n,
+                                                     const float* xt, const float* x,
+                                                     const float* gt, const float* g, float* S,
+                                                     float* Y, double* partial) {
+  if (!gate_open(st, G_ACC, -1)) return;
+  __shared__ double sh[TB];
+  float* sv = S + (size_t)st->slot * n;
+  float* yv = Y + (size_t)st->slot * n;
+  double acc[3] = {0.0, 0.0, 0.0};
+  const size_t stride = (size_t)gridDim.x * TB;
+  for (size_t i = (size_t)blockIdx.x * TB + threadIdx.x; i < n; i += stride) {
+    const float sx = __fmaf_rn(-1.f, x[i], __fmul_rn(1.f, xt[i]));
+    const float yx = __fmaf_rn(-1.f, g[i], __fmul_rn(1.f, gt[i]));
+    sv[i] = sx;
+    yv[i] = yx;
+    acc[0] += (double)sx * (double)yx;
+    acc[1] += (double)yx * (double)yx;
+    acc[2] += (double)sx * (double)sx;
+  }
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    const double t = block_sum(acc[q], sh);
+    if (threadIdx.x == 0) partial[(size_t)q * DOT_BLOCKS + blockIdx.x] = t;
+  }
 }
 
-// x *= sign * num[slot] / den[slot]
-__global__ __launch_bounds__(TB) void lb_scale_kernel(const pmr_lbfgs_state* st, int gate, int jc,
-                                                      size_t n, const double* num,
-                                                      const double* den, int j, double sign,
-                                                      float* x) {
-  if (!gate_open(st, gate, jc)) return;
-  const size_t i = slot_of(st, j);
-  scale_body(n, (float)(sign * num[i] / den[i]), x);
+// The move to the accepted trial, x = xt and g = gt, with the partial sums of g.g.
+__global__ __launch_bounds__(TB) void lb_move_kernel(const pmr_lbfgs_state* st, size_t n,
+                                                     const float* xt, float* x, const float* gt,
+                                                     float* g, double* partial) {
+  if (!gate_open(st, G_ACC, -1)) return;
+  __shared__ double sh[TB];
+  double acc = 0.0;
+  const size_t stride = (size_t)gridDim.x * TB;
+  for (size_t i = (size_t)blockIdx.x * TB + threadIdx.x; i < n; i += stride) {
+    x[i] = __fmaf_rn(0.f, xt[i], __fmul_rn(1.f, xt[i]));
+    const float v = __fmaf_rn(0.f, gt[i], __fmul_rn(1.f, gt[i]));
+    g[i] = v;
+    acc += (double)v * (double)v;
+  }
+  const double t = block_sum(acc, sh);
+  if (threadIdx.x == 0) partial[blockIdx.x] = t;
 }
 
-// out[slot] = alpha a + beta b
-__global__ __launch_bounds__(TB) void lb_axpby_kernel(const pmr_lbfgs_state* st, int gate, int jc,
+// out = alpha a + beta b
+__global__ __launch_bounds__(TB) void lb_axpby_kernel(const pmr_lbfgs_state* st, int gate,
                                                       size_t n, float alpha, const float* a,
-                                                      float beta, const float* b, float* out,
-                                                      int jout) {
-  if (!gate_open(st, gate, jc)) return;
-  axpby_body(n, alpha, a, beta, b, out + slot_of(st, jout) * n);
+                                                      float beta, const float* b, float* out) {
+  if (!gate_open(st, gate, -1)) return;
+  axpby_body(n, alpha, a, beta, b, out);
 }
 
 // xt = x + t d
@@ -343,27 +570,31 @@ __global__ void lb_init_kernel(pmr_lbfgs_state* st, pmr_lbfgs_params p, const do
   clock_hist(st)[0] = wall_clock64();
 }
 
-// a zero gradient ends the stage
-__global__ void lb_gg_kernel(pmr_lbfgs_state* st) {
+// g.g from its partials; a zero gradient ends the stage
+__global__ __launch_bounds__(TB) void lb_gg_kernel(pmr_lbfgs_state* st, const double* partial,
+                                                   int np) {
   if (!gate_open(st, G_DIR, -1)) return;
-  if (st->gg == 0.0) st->status = PMR_LBFGS_STATIONARY;
+  const double gg = dot_total(partial, np);
+  if (threadIdx.x != 0) return;
+  st->gg = gg;
+  if (gg == 0.0) st->status = PMR_LBFGS_STATIONARY;
 }
 
-// not a descent direction: clear the history, d = -g follows
-__global__ void lb_gd_kernel(pmr_lbfgs_state* st) {
+// g.d from its partials; not a descent direction: clear the history, d = -g follows. Then the
+// first trial step of the search.
+__global__ __launch_bounds__(TB) void lb_gd_kernel(pmr_lbfgs_state* st, const double* partial,
+                                                   int np) {
   if (!gate_open(st, G_DIR, -1)) return;
-  if (st->gd >= 0.0) {
+  const double gd = dot_total(partial, np);
+  if (threadIdx.x != 0) return;
+  if (gd >= 0.0) {
     st->count = 0;
     st->reset = 1;
     st->gd = -st->gg;
   } else {
     st->reset = 0;
+    st->gd = gd;
   }
-}
-
-// first trial step of the search
-__global__ void lb_step_kernel(pmr_lbfgs_state* st) {
-  if (!gate_open(st, G_DIR, -1)) return;
   st->probe = st->count == 0;
   st->t = st->probe ? __ddiv_rn(1.0, __dsqrt_rn(st->gg)) : 1.0;
   st->halvings = 0;
@@ -394,10 +625,18 @@ __global__ void lb_test_kernel(pmr_lbfgs_state* st, const double* loss) {
   }
 }
 
-// curvature test, history update, the move to x_t and the stopping rules
-__global__ void lb_accept_kernel(pmr_lbfgs_state* st, const double* sy, const double* yy) {
+// inner products of the candidate pair, curvature test, history update and the stopping rules
+__global__ __launch_bounds__(TB) void lb_accept_kernel(pmr_lbfgs_state* st,
+                                                       const double* partial, int np, double* sy,
+                                                       double* yy) {
   if (!gate_open(st, G_ACC, -1)) return;
+  const double p[3] = {dot_total(partial, np), dot_total(partial + DOT_BLOCKS, np),
+                       dot_total(partial + 2 * DOT_BLOCKS, np)};
+  if (threadIdx.x != 0) return;
   const int i = st->slot;
+  sy[i] = p[0];
+  yy[i] = p[1];
+  st->ss = p[2];
   if (sy[i] > __dmul_rn(st->p.curvature_eps, __dsqrt_rn(__dmul_rn(yy[i], st->ss)))) {
     const int keep = st->count < st->p.m ? st->count : st->p.m - 1;
     for (int k = keep; k > 0; --k) st->order[k] = st->order[k - 1];
@@ -419,38 +658,23 @@ __global__ void lb_accept_kernel(pmr_lbfgs_state* st, const double* sy, const do
 
 }  // namespace
 
-// FP64 inner product out[jout] = A[ja] . B[jb] (/ den[jden]) under a gate.
-void lb_dot(const pmr_lbfgs_state* st, int gate, int jc, size_t n, const float* A, int ja,
-            const float* B, int jb, const double* den, int jden, double* out, int jout,
-            double* work, hipStream_t s) {
-  const int nb = dot_blocks(n);
-  lb_dot_partial_kernel<<<nb, TB, 0, s>>>(st, gate, jc, A, ja, B, jb, n, work);
-  lb_dot_final_kernel<<<1, TB, 0, s>>>(st, gate, jc, work, nb, den, jden, out, jout);
-}
-
-// The next direction at x (g): the zero-gradient test, the two-loop recursion over the
-// device-held history, the descent test with its fallback d = -g, and the first step.
+// The next direction at x (g), whose g.g partials are at the start of `work`: the
+// zero-gradient test, the two-loop recursion over the device-held history, the descent test
+// with its fallback d = -g, and the first step.
 void lb_direction(pmr_lbfgs_state* st, size_t n, int m, const float* g, float* d, const float* S,
                   const float* Y, const double* sy, const double* yy, double* work,
                   hipStream_t s) {
-  const unsigned gs = stream_grid(n);
-  lb_dot(st, G_DIR, -1, n, g, NO_SLOT, g, NO_SLOT, nullptr, NO_SLOT, &st->gg, NO_SLOT, work, s);
-  lb_gg_kernel<<<1, 1, 0, s>>>(st);
-  lb_axpby_kernel<<<gs, TB, 0, s>>>(st, G_DIR, -1, n, 1.f, g, 0.f, g, d, NO_SLOT);  // q = g
-  for (int j = 0; j < m; ++j) {  // newest to oldest: alpha_i = s_i.q / s_i.y_i; q -= alpha_i y_i
-    lb_dot(st, G_DIR, j, n, S, j, d, NO_SLOT, sy, j, st->alpha, j, work, s);
-    lb_axpy_kernel<<<gs, TB, 0, s>>>(st, G_DIR, j, n, st->alpha, j, nullptr, -1.0, Y, j, d);
-  }
-  lb_scale_kernel<<<gs, TB, 0, s>>>(st, G_DIR, 0, n, sy, yy, 0, 1.0, d);  // r = gamma q
-  for (int j = m - 1; j >= 0; --j) {  // oldest to newest: beta = y_i.r / s_i.y_i
-    lb_dot(st, G_DIR, j, n, Y, j, d, NO_SLOT, sy, j, &st->beta, NO_SLOT, work, s);
-    lb_axpy_kernel<<<gs, TB, 0, s>>>(st, G_DIR, j, n, st->alpha, j, &st->beta, 1.0, S, j, d);
-  }
-  lb_axpby_kernel<<<gs, TB, 0, s>>>(st, G_DIR, -1, n, -1.f, d, 0.f, d, d, NO_SLOT);
-  lb_dot(st, G_DIR, -1, n, g, NO_SLOT, d, NO_SLOT, nullptr, NO_SLOT, &st->gd, NO_SLOT, work, s);
-  lb_gd_kernel<<<1, 1, 0, s>>>(st);
-  lb_axpby_kernel<<<gs, TB, 0, s>>>(st, G_RESET, -1, n, -1.f, g, 0.f, g, d, NO_SLOT);
-  lb_step_kernel<<<1, 1, 0, s>>>(st);
+  const int nb = dot_blocks(n);
+  lb_gg_kernel<<<1, TB, 0, s>>>(st, work, nb);
+  LoopArgs a{n, LOOP_FIRST, 0, S, Y, sy, yy, g, d, work, st->alpha, g};
+  lb_loop_kernel<<<nb, TB, 0, s>>>(st, a);
+  a.kind = LOOP_DOWN;
+  for (a.j = 0; a.j < m; ++a.j) lb_loop_kernel<<<nb, TB, 0, s>>>(st, a);  // newest to oldest
+  a.kind = LOOP_UP;
+  for (a.j = m - 1; a.j >= 0; --a.j) lb_loop_kernel<<<nb, TB, 0, s>>>(st, a);  // oldest to newest
+  // (the 2 count + 1 launches that ran leave the partials of g.d in the first array)
+  lb_gd_kernel<<<1, TB, 0, s>>>(st, work, nb);
+  lb_axpby_kernel<<<stream_grid(n), TB, 0, s>>>(st, G_RESET, n, -1.f, g, 0.f, g, d);
 }
 
 void launch_lbfgs_init(size_t n, const pmr_lbfgs_params& p, pmr_lbfgs_state* st,
@@ -458,6 +682,7 @@ void launch_lbfgs_init(size_t n, const pmr_lbfgs_params& p, pmr_lbfgs_state* st,
                        const float* Y, const double* sy, const double* yy, double* work,
                        long long clock_khz, hipStream_t s) {
   lb_init_kernel<<<1, 1, 0, s>>>(st, p, loss, clock_khz);
+  lb_dot_partial_kernel<<<dot_blocks(n), TB, 0, s>>>(st, G_DIR, g, g, n, work);
   lb_direction(st, n, p.m, g, d, S, Y, sy, yy, work, s);
 }
 
@@ -469,39 +694,37 @@ void launch_lbfgs_trial(size_t n, const pmr_lbfgs_state* st, const float* x, con
 void launch_lbfgs_update(size_t n, int m, pmr_lbfgs_state* st, const double* loss, float* x,
                          float* g, const float* xt, const float* gt, float* d, float* S,
                          float* Y, double* sy, double* yy, double* work, hipStream_t s) {
-  const unsigned gs = stream_grid(n);
+  const int nb = dot_blocks(n);
   lb_test_kernel<<<1, 1, 0, s>>>(st, loss);
-  lb_axpby_kernel<<<gs, TB, 0, s>>>(st, G_ACC, -1, n, 1.f, xt, -1.f, x, S, NEW_SLOT);
-  lb_axpby_kernel<<<gs, TB, 0, s>>>(st, G_ACC, -1, n, 1.f, gt, -1.f, g, Y, NEW_SLOT);
-  lb_dot(st, G_ACC, -1, n, S, NEW_SLOT, Y, NEW_SLOT, nullptr, NO_SLOT, sy, NEW_SLOT, work, s);
-  lb_dot(st, G_ACC, -1, n, Y, NEW_SLOT, Y, NEW_SLOT, nullptr, NO_SLOT, yy, NEW_SLOT, work, s);
-  lb_dot(st, G_ACC, -1, n, S, NEW_SLOT, S, NEW_SLOT, nullptr, NO_SLOT, &st->ss, NO_SLOT, work, s);
-  lb_accept_kernel<<<1, 1, 0, s>>>(st, sy, yy);
-  lb_axpby_kernel<<<gs, TB, 0, s>>>(st, G_ACC, -1, n, 1.f, xt, 0.f, xt, x, NO_SLOT);
-  lb_axpby_kernel<<<gs, TB, 0, s>>>(st, G_ACC, -1, n, 1.f, gt, 0.f, gt, g, NO_SLOT);
+  lb_pair_kernel<<<nb, TB, 0, s>>>(st, n, xt, x, gt, g, S, Y, work);
+  lb_accept_kernel<<<1, TB, 0, s>>>(st, work, nb, sy, yy);
+  lb_move_kernel<<<nb, TB, 0, s>>>(st, n, xt, x, gt, g, work);
   lb_direction(st, n, m, g, d, S, Y, sy, yy, work, s);
 }
 
-size_t power_work_doubles(int nbins) { return (size_t)4 * nbins * PS_THREADS; }
+size_t power_work_doubles(int nbins) { return (size_t)4 * nbins * PS_SLOTS; }
 
 void launch_power_bins(int n, double box, const float2* a, const float2* b, int nbins,
                        double* out, double* work, hipStream_t s) {
-  const size_t total = (size_t)n * n * (n / 2 + 1);
-  const size_t chunk = (total + PS_THREADS - 1) / PS_THREADS;
-  power_partial_kernel<<<PS_THREADS / TB, TB, 0, s>>>(n, a, b, nbins, chunk, work);
+  const int top = top_shell(n) + 1, shells = nbins < top ? nbins : top;
+  const int items = (n / 2 + 1) * (n / 2 + 2) / 2;
+  // 28 bytes of LDS per shell and wavefront, at most 64 KB (two wavefronts at n = 1024)
+  const int waves = shells * 28 * 4 <= 64 * 1024 ? 4 : 2;
+  const int need = (items + waves - 1) / waves, blocks = need < PS_BLOCKS ? need : PS_BLOCKS;
+  power_partial_kernel<<<blocks, 64 * waves, (size_t)waves * shells * 28, s>>>(
+      n, a, b, shells, items, nbins, work);
   const double norm = box * box * box / ((double)n * n * n * (double)n * n * n);
-  power_reduce_kernel<<<nbins, TB, 0, s>>>(work, nbins, norm, out);
+  power_reduce_kernel<<<nbins, TB, 0, s>>>(work, nbins, shells, blocks, norm, out);
 }
 
 }  // namespace pmr
 
 // ---------------------------------------------------------------- fixed scratch
-// The scratch of pmr_lbfgs_direction_noalloc: the partial sums of one inner product
-// (vec_work_doubles(n) <= DOT_BLOCKS + 64) followed by the two-loop scalars (alpha per slot,
-// beta: at most 2 * 64 + 8). One copy per GPU, held until the process ends; every call on a
+// The scratch of pmr_lbfgs_direction_noalloc: the two arrays of partial sums followed by the
+// two-loop scalars (alpha per slot: at most 64). One copy per GPU, held until the process ends; every call on a
 // GPU shares it, so calls that overlap on one GPU (several streams or threads) race.
 constexpr int NOALLOC_MAX_M = 64;
-constexpr size_t NOALLOC_DOUBLES = (size_t)pmr::DOT_BLOCKS + 64 + 2 * NOALLOC_MAX_M + 8;
+constexpr size_t NOALLOC_DOUBLES = (size_t)2 * pmr::DOT_BLOCKS + NOALLOC_MAX_M;
 static __device__ __align__(256) double scratch[NOALLOC_DOUBLES];
 
 namespace {
@@ -569,7 +792,7 @@ int pmr_lbfgs_direction(size_t n, int m, int count, const int* order, const floa
     }
   }
   double* w = (double*)work;
-  launch_lbfgs_direction(n, m, count, order, S, Y, sy, yy, g, d, w, w + vec_work_doubles(n),
+  launch_lbfgs_direction(n, count, order, S, Y, sy, yy, g, d, w, w + vec_work_doubles(n),
                          (hipStream_t)stream);
   return hipGetLastError() == hipSuccess ? PMR_OK : PMR_E_HIP;
 }
@@ -578,7 +801,7 @@ int pmr_lbfgs_direction_noalloc(size_t n, int m, int count, const int* order, co
                                 const float* Y, const double* sy, const double* yy,
                                 const float* g, float* d, void* stream) {
   if (!g || !d || n == 0 || g == d || m < 1 || count < 0 || count > m) return PMR_E_INVALID;
-  if (m > NOALLOC_MAX_M) return PMR_E_SHAPE;  // the fixed scratch holds 2 m + 2 scalars
+  if (m > NOALLOC_MAX_M) return PMR_E_SHAPE;  // the fixed scratch holds 64 scalars
   if (count > 0) {
     if (!order || !S || !Y || !sy || !yy) return PMR_E_INVALID;
     unsigned long long seen = 0;
@@ -591,9 +814,7 @@ int pmr_lbfgs_direction_noalloc(size_t n, int m, int count, const int* order, co
   double* w = nullptr;
   const int st = scratch_of(s, &w);
   if (st != PMR_OK) return st;
-  const size_t part = vec_work_doubles(n);
-  if (part + 2 * (size_t)m + 2 > NOALLOC_DOUBLES) return PMR_E_SHAPE;
-  launch_lbfgs_direction(n, m, count, order, S, Y, sy, yy, g, d, w, w + part, s);
+  launch_lbfgs_direction(n, count, order, S, Y, sy, yy, g, d, w, w + 2 * DOT_BLOCKS, s);
   return hipGetLastError() == hipSuccess ? PMR_OK : PMR_E_HIP;
 }
 
