@@ -267,6 +267,12 @@ int pmr_fft_r2c(int n, int batch, const float* in, void* out, void* stream);
  * (kz = 0, n/2 columns after the inner transforms) are ignored, as irfftn does. */
 int pmr_fft_c2r(int n, int batch, void* inout, float* out, void* stream);
 
+/* The same from an input that is kept: `work` (16-byte aligned device memory of
+ * pmr_fft_c2r_work_bytes(n, batch)) takes the intermediate spectra, so the caller need not
+ * copy the input first. PMR_E_INVALID for a null or misaligned pointer. */
+size_t pmr_fft_c2r_work_bytes(int n, int batch);
+int pmr_fft_c2r_work(int n, int batch, const void* in, void* work, float* out, void* stream);
+
 /* Tile shape of one strided FFT pass for size n (process-wide; the autotuner sets it).
  * `pass` PMR_FFT_YPASS (the middle axis), PMR_FFT_XPASS (the outermost axis with a
  * single-input k-space operator: forward or inverse only, force, smoothing, Zel'dovich; also

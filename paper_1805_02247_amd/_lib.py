@@ -96,6 +96,8 @@ SIGNATURES = {
     "pmr_debug_copy": (ctypes.c_longlong, [vp, ci, ci, vp]),
     "pmr_fft_r2c": (ci, [ci, ci, vp, vp, vp]),
     "pmr_fft_c2r": (ci, [ci, ci, vp, vp, vp]),
+    "pmr_fft_c2r_work_bytes": (sz, [ci, ci]),
+    "pmr_fft_c2r_work": (ci, [ci, ci, vp, vp, vp, vp]),
     "pmr_sort_scratch_bytes": (sz, [ci, ci, ci]),
     "pmr_cic_sort": (ci, [ci, ci, ci, cd, vp, vp, vp, vp, vp, sz, vp]),
     "pmr_cic_paint": (ci, [ci, ci, ci, cd, vp, vp, vp, vp, cf, cf, vp, vp, sz, vp]),

@@ -63,6 +63,31 @@ void fft_paint_r2c_512(int, const PaintArgs&, int, float2*, FieldMap, hipStream_
 void fft_ypass_512(int, float2*, FieldMap, bool, hipStream_t, KzWin);
 void fft_xpass_512(int, const XPassArgs&, hipStream_t);
 
+void fft_zy_r2c_16(int, const float*, FieldMap, const float*, float, float, const double*, float2*,
+                 FieldMap, hipStream_t);
+void fft_yz_c2r_16(int, const float2*, FieldMap, float*, FieldMap, const float*, hipStream_t);
+void fft_yz_c2r3_16(int, const float2*, FieldMap, Vec3*, size_t, double, hipStream_t);
+void fft_zy_r2c_32(int, const float*, FieldMap, const float*, float, float, const double*, float2*,
+                 FieldMap, hipStream_t);
+void fft_yz_c2r_32(int, const float2*, FieldMap, float*, FieldMap, const float*, hipStream_t);
+void fft_yz_c2r3_32(int, const float2*, FieldMap, Vec3*, size_t, double, hipStream_t);
+void fft_zy_r2c_64(int, const float*, FieldMap, const float*, float, float, const double*, float2*,
+                 FieldMap, hipStream_t);
+void fft_yz_c2r_64(int, const float2*, FieldMap, float*, FieldMap, const float*, hipStream_t);
+void fft_yz_c2r3_64(int, const float2*, FieldMap, Vec3*, size_t, double, hipStream_t);
+void fft_zy_r2c_128(int, const float*, FieldMap, const float*, float, float, const double*, float2*,
+                 FieldMap, hipStream_t);
+void fft_yz_c2r_128(int, const float2*, FieldMap, float*, FieldMap, const float*, hipStream_t);
+void fft_yz_c2r3_128(int, const float2*, FieldMap, Vec3*, size_t, double, hipStream_t);
+void fft_zy_r2c_256(int, const float*, FieldMap, const float*, float, float, const double*, float2*,
+                 FieldMap, hipStream_t);
+void fft_yz_c2r_256(int, const float2*, FieldMap, float*, FieldMap, const float*, hipStream_t);
+void fft_yz_c2r3_256(int, const float2*, FieldMap, Vec3*, size_t, double, hipStream_t);
+void fft_zy_r2c_512(int, const float*, FieldMap, const float*, float, float, const double*, float2*,
+                 FieldMap, hipStream_t);
+void fft_yz_c2r_512(int, const float2*, FieldMap, float*, FieldMap, const float*, hipStream_t);
+void fft_yz_c2r3_512(int, const float2*, FieldMap, Vec3*, size_t, double, hipStream_t);
+
 #define PMR_FOR_N(MACRO) \
   MACRO(16) MACRO(32) MACRO(64) MACRO(128) MACRO(256) MACRO(512)
 
@@ -93,6 +118,49 @@ void launch_zpass_c2r3(int n, int items, const float2* in, FieldMap im, Vec3* ou
   switch (n) {
 #define CASE(NN) \
   case NN: fft_zc2r3_##NN(items, in, im, out, out_item_stride, s); break;
+    PMR_FOR_N(CASE)
+#undef CASE
+    default: break;
+  }
+}
+
+void launch_zy_r2c(int n, int fields, const float* in, FieldMap im, const float* in2, float a1,
+                   float a2, const double* scale_dev, float2* out, FieldMap om, hipStream_t s) {
+  if (!plane_passes(n)) {
+    launch_zpass_r2c(n, fields, in, im, in2, a1, a2, scale_dev, out, om, s);
+    launch_ypass(n, fields, out, om, false, s);
+    return;
+  }
+  switch (n) {
+#define CASE(NN) \
+  case NN: fft_zy_r2c_##NN(fields, in, im, in2, a1, a2, scale_dev, out, om, s); break;
+    PMR_FOR_N(CASE)
+#undef CASE
+    default: break;
+  }
+}
+
+void launch_yz_c2r(int n, int fields, float2* in, FieldMap im, float* out, FieldMap om,
+                   const float* add, hipStream_t s) {
+  if (!plane_passes(n)) {
+    launch_ypass(n, fields, in, im, true, s);
+    launch_zpass_c2r(n, fields, in, im, out, om, add, s);
+    return;
+  }
+  switch (n) {
+#define CASE(NN) \
+  case NN: fft_yz_c2r_##NN(fields, in, im, out, om, add, s); break;
+    PMR_FOR_N(CASE)
+#undef CASE
+    default: break;
+  }
+}
+
+void launch_yz_c2r3(int n, int items, const float2* in, FieldMap im, Vec3* out,
+                    size_t out_item_stride, double box, hipStream_t s) {
+  switch (n) {
+#define CASE(NN) \
+  case NN: fft_yz_c2r3_##NN(items, in, im, out, out_item_stride, box, s); break;
     PMR_FOR_N(CASE)
 #undef CASE
     default: break;

@@ -560,6 +560,276 @@ __global__ __launch_bounds__(NT) void zpass_c2r3_kernel(const float2* __restrict
   }
 }
 
+// ---------------------------------------------------------------- plane passes
+// Up to 128^3 one x plane of a half spectrum fits in LDS (128 rows of 65 values: 69 KB), so a
+// workgroup takes a plane through the y and the z transform at once: the spectrum does not go
+// to memory and back between them, and two or three launches become one. The plane is kept
+// in the z pass's padded rows; the y stages run over its columns with consecutive threads on
+// consecutive columns. Every line goes through the same stages and operators as in the
+// separate passes (radix-4 y stages at 64 and 128, as those are tuned), so the results are
+// the same bit for bit.
+template <int N>
+struct Plane {
+  static constexpr int H = N / 2, NH = H + 1;
+  static constexpr int P = ZTile<N>::PITCH;  // row pitch in LDS (complex); slot of column l: zk(l)
+  static constexpr int NTH = N >= 128 ? 1024 : N >= 64 ? 512 : 256;
+  static constexpr int YR = N >= 64 ? 4 : 8;  // radix of the plain y stages
+  static constexpr int PAIRS = (NH + 1) / 2;  // column pairs of a row
+};
+constexpr int PLANE_MAX = 128;
+
+// One Stockham stage (see stockham_stage) along y over the NH columns of the plane.
+template <int N, int R, int PREV, int DIR>
+__device__ __forceinline__ void column_stage(float2* lds, const float2* tw) {
+  using T = Plane<N>;
+  constexpr int NTH = T::NTH, NB = (N / R) * T::NH, PER = (NB + NTH - 1) / NTH;
+  float2 u[PER][R];
+#pragma unroll
+  for (int m = 0; m < PER; ++m) {
+    const int b = threadIdx.x + m * NTH;
+    if (b < NB) {
+      const int i = b / T::NH, l = zk(b % T::NH);
+#pragma unroll
+      for (int r = 0; r < R; ++r) u[m][r] = lds[(i + r * (N / R)) * T::P + l];
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int m = 0; m < PER; ++m) {
+    const int b = threadIdx.x + m * NTH;
+    if (b < NB) {
+      const int i = b / T::NH, l = zk(b % T::NH);
+      const int k = i & (PREV - 1);
+      if constexpr (PREV > 1) {
+#pragma unroll
+        for (int r = 1; r < R; ++r) {
+          float2 w = tw[r * k * (N / (PREV * R))];
+          if (DIR > 0) w.y = -w.y;
+          u[m][r] = cmul(u[m][r], w);
+        }
+      }
+      bfly<R, DIR>(u[m]);
+      const int j0 = (i - k) * R + k;
+#pragma unroll
+      for (int r = 0; r < R; ++r) lds[(j0 + r * PREV) * T::P + l] = u[m][r];
+    }
+  }
+  __syncthreads();
+}
+
+// The whole y transform; radices as in fft_lds.
+template <int N, int DIR, int RMAX, int PREV = 1>
+__device__ __forceinline__ void column_fft(float2* lds, const float2* tw) {
+  constexpr int REM = N / PREV;
+  if constexpr (REM > 1) {
+    constexpr int R = REM >= RMAX ? RMAX : REM;
+    column_stage<N, R, PREV, DIR>(lds, tw);
+    column_fft<N, DIR, RMAX, PREV * R>(lds, tw);
+  }
+}
+
+// Spectrum rows <-> LDS, as 16-byte column pairs where the pitch is even (the partner of an odd
+// last column is row padding).
+template <int N>
+__device__ __forceinline__ void plane_load(float2* lds, const float2* __restrict__ src,
+                                           size_t pitch) {
+  using T = Plane<N>;
+  if ((pitch & 1) == 0) {
+#pragma unroll 4
+    for (int e = threadIdx.x; e < N * T::PAIRS; e += T::NTH) {
+      const int n = e / T::PAIRS, l = 2 * (e % T::PAIRS);
+      const float4 v = *reinterpret_cast<const float4*>(src + (size_t)n * pitch + l);
+      float2* d = lds + n * T::P + zk(l);
+      d[0] = make_float2(v.x, v.y);
+      if (l + 1 < T::NH) d[1] = make_float2(v.z, v.w);
+    }
+  } else {
+#pragma unroll 4
+    for (int e = threadIdx.x; e < N * T::NH; e += T::NTH) {
+      const int n = e / T::NH, l = e % T::NH;
+      lds[n * T::P + zk(l)] = src[(size_t)n * pitch + l];
+    }
+  }
+}
+
+template <int N>
+__device__ __forceinline__ void plane_store(const float2* lds, float2* __restrict__ dst,
+                                            size_t pitch) {
+  using T = Plane<N>;
+  if ((pitch & 1) == 0) {
+    for (int e = threadIdx.x; e < N * T::PAIRS; e += T::NTH) {
+      const int n = e / T::PAIRS, l = 2 * (e % T::PAIRS);
+      const float2* z = lds + n * T::P + zk(l);
+      const float2 a = z[0], b = l + 1 < T::NH ? z[1] : make_float2(0.f, 0.f);
+      *reinterpret_cast<float4*>(dst + (size_t)n * pitch + l) = make_float4(a.x, a.y, b.x, b.y);
+    }
+  } else {
+    for (int e = threadIdx.x; e < N * T::NH; e += T::NTH) {
+      const int n = e / T::NH, l = e % T::NH;
+      dst[(size_t)n * pitch + l] = lds[n * T::P + zk(l)];
+    }
+  }
+}
+
+// The inverse z transform of the plane's rows, in place (complex point k of a row at zk(k) holds
+// real points 2 k and 2 k + 1 afterwards).
+template <int N>
+__device__ __forceinline__ void plane_z_inverse(float2* lds, const float2* tw) {
+  using T = Plane<N>;
+  constexpr int Q = T::H / 2 + 1;
+  for (int e = threadIdx.x; e < N * Q; e += T::NTH) {
+    float2* z = lds + (e / Q) * T::P;
+    const int k = e % Q;
+    const float2 xk = z[zk(k)], xm = z[zk(T::H - k)];
+    inv_split<T::H>(z, k, xk, xm, tw);
+  }
+  __syncthreads();
+  fft_lds<T::H, N, 1, T::P, 2, +1, T::NTH, true>(lds, tw);
+}
+
+// Inverse y, then c2r along z, of one plane per workgroup (zpass_c2r_kernel after the inverse
+// y pass). Blocks: fields * N, mapped so that neighbouring planes share an L2.
+template <int N>
+__global__ __launch_bounds__(Plane<N>::NTH) void zpass_plane_c2r_kernel(
+    const float2* __restrict__ in, FieldMap im, float* __restrict__ out, FieldMap om,
+    const float* __restrict__ add) {
+  using T = Plane<N>;
+  __shared__ float2 lds[N * T::P];
+  __shared__ float2 tw[N];
+  make_twiddles<N, T::NTH>(tw);
+  const int b = xcd_block(blockIdx.x, gridDim.x), field = b / N, ix = b % N;
+  plane_load<N>(lds, in + im.off(field) + (size_t)ix * N * im.pitch, im.pitch);
+  __syncthreads();
+  column_fft<N, +1, T::YR>(lds, tw);
+  plane_z_inverse<N>(lds, tw);
+  const size_t o = om.off(field) + (size_t)ix * N * N;
+  float2* dst = reinterpret_cast<float2*>(out + o);
+  const float2* ad = add ? reinterpret_cast<const float2*>(add + o) : nullptr;
+  for (int e = threadIdx.x; e < N * T::H; e += T::NTH) {
+    float2 v = lds[(e / T::H) * T::P + zk(e % T::H)];
+    if (ad) {
+      const float2 w = ad[e];
+      v.x += w.x;
+      v.y += w.y;
+    }
+    dst[e] = v;
+  }
+}
+
+// The force mesh of one plane per workgroup: component 0 inverse along y, components 1 and 2
+// from the potential in component 1 (i k_y and i k_z of it, XOP_YGRAD), each c2r along z, into
+// interleaved cells (zpass_c2r3_kernel). A component's real plane waits in registers.
+template <int N>
+__global__ __launch_bounds__(Plane<N>::NTH) void zpass_plane_c2r3_kernel(
+    const float2* __restrict__ in, FieldMap im, Vec3* __restrict__ out, size_t out_item_stride,
+    double box) {
+  using T = Plane<N>;
+  constexpr int PER = N * N / T::NTH;
+  static_assert(N * N % T::NTH == 0, "whole cells per thread sweep");
+  __shared__ float2 lds[N * T::P];
+  __shared__ float2 tw[N];
+  make_twiddles<N, T::NTH>(tw);
+  const float kf = (float)(2.0 * M_PI / box);
+  const int b = xcd_block(blockIdx.x, gridDim.x), item = b / N, ix = b % N;
+  float real[3][PER];
+#pragma unroll
+  for (int f = 0; f < 3; ++f) {
+    plane_load<N>(lds, in + im.off(item * 3 + (f ? 1 : 0)) + (size_t)ix * N * im.pitch, im.pitch);
+    __syncthreads();
+    if (f == 0) {
+      column_fft<N, +1, T::YR>(lds, tw);
+    } else {
+      for (int e = threadIdx.x; e < N * T::NH; e += T::NTH) {
+        const int n = e / T::NH, l = e % T::NH;
+        float2* p = lds + n * T::P + zk(l);
+        const float2 v = *p;
+        const float c = f == 1 ? axis_coef<N>(n, kf) : axis_coef<N>(l, kf);
+        *p = cmul_i<1>(make_float2(c * v.x, c * v.y));
+      }
+      __syncthreads();
+      column_fft<N, +1, 8>(lds, tw);
+    }
+    plane_z_inverse<N>(lds, tw);
+    const float* l = reinterpret_cast<const float*>(lds);
+#pragma unroll
+    for (int m = 0; m < PER; ++m) {
+      const int e = threadIdx.x + m * T::NTH;
+      const int r = e / N, zz = e % N;
+      real[f][m] = l[2 * (r * T::P + zk(zz >> 1)) + (zz & 1)];
+    }
+    __syncthreads();
+  }
+  Vec3* dst = out + item * out_item_stride + (size_t)ix * N * N;
+#pragma unroll
+  for (int m = 0; m < PER; ++m) {
+    const int e = threadIdx.x + m * T::NTH;
+    __builtin_nontemporal_store(real[0][m], &dst[e].x);
+    __builtin_nontemporal_store(real[1][m], &dst[e].y);
+    __builtin_nontemporal_store(real[2][m], &dst[e].z);
+  }
+}
+
+// r2c along z, then forward y, of one plane per workgroup (zpass_r2c_kernel, then the forward y
+// pass).
+template <int N>
+__global__ __launch_bounds__(Plane<N>::NTH) void zpass_plane_r2c_kernel(
+    const float* __restrict__ in, FieldMap im, const float* __restrict__ in2, float a1, float a2,
+    const double* __restrict__ scale_dev, float2* __restrict__ out, FieldMap om) {
+  using T = Plane<N>;
+  constexpr int H = T::H, Q = H / 2 + 1;
+  __shared__ float2 lds[N * T::P];
+  __shared__ float2 tw[N];
+  make_twiddles<N, T::NTH>(tw);
+  const int b = xcd_block(blockIdx.x, gridDim.x), field = b / N, ix = b % N;
+  const size_t o = im.off(field) + (size_t)ix * N * N;
+  const float2* src = reinterpret_cast<const float2*>(in + o);
+  const float2* src2 = in2 ? reinterpret_cast<const float2*>(in2 + o) : nullptr;
+  float sc = 1.0f;
+  if (scale_dev) sc = (float)scale_dev[field / im.fpi];
+  const float b1 = a1 * sc, b2 = a2 * sc;
+#pragma unroll 4
+  for (int e = threadIdx.x; e < N * H; e += T::NTH) {
+    float2 v = src[e];
+    v.x *= b1;
+    v.y *= b1;
+    if (src2) {
+      float2 w = src2[e];
+      v.x += b2 * w.x;
+      v.y += b2 * w.y;
+    }
+    lds[(e / H) * T::P + zk(e % H)] = v;
+  }
+  __syncthreads();
+  fft_lds<H, N, 1, T::P, 2, -1, T::NTH, true>(lds, tw);
+  // split (see zpass_r2c_kernel), in place: the pair (k, H - k) owns its two slots
+  for (int e = threadIdx.x; e < N * Q; e += T::NTH) {
+    const int k = e % Q;
+    float2* z = lds + (e / Q) * T::P;
+    if (k == 0) {
+      const float2 z0 = z[0];
+      z[0] = make_float2(z0.x + z0.y, 0.f);
+      z[zk(H)] = make_float2(z0.x - z0.y, 0.f);
+    } else {
+      const float2 zv = z[zk(k)], zm = z[zk(H - k)];
+      {
+        float2 s = make_float2(0.5f * (zv.x + zm.x), 0.5f * (zv.y - zm.y));
+        float2 df = make_float2(0.5f * (zv.x - zm.x), 0.5f * (zv.y + zm.y));
+        float2 t = cmul(tw[k], df);
+        z[zk(k)] = make_float2(s.x + t.y, s.y - t.x);
+      }
+      if (k != H - k) {
+        float2 s = make_float2(0.5f * (zm.x + zv.x), 0.5f * (zm.y - zv.y));
+        float2 df = make_float2(0.5f * (zm.x - zv.x), 0.5f * (zm.y + zv.y));
+        float2 t = cmul(tw[H - k], df);
+        z[zk(H - k)] = make_float2(s.x + t.y, s.y - t.x);
+      }
+    }
+  }
+  __syncthreads();
+  column_fft<N, -1, T::YR>(lds, tw);
+  plane_store<N>(lds, out + om.off(field) + (size_t)ix * N * om.pitch, om.pitch);
+}
+
 // ---------------------------------------------------------------- strided passes
 // Tile: PC consecutive kz columns (from kz0) of the N points of one line family.
 // Element (n, l) of a tile sits at base + n * stride + l; in LDS at n * PC + l.
@@ -1005,6 +1275,30 @@ void zc2r(int fields, const float2* in, FieldMap im, float* out, FieldMap om, co
   const int res = resident_grid<zpass_c2r_kernel<N>, NT>();
   zpass_c2r_kernel<N><<<ntiles < res ? ntiles : res, NT, 0, s>>>(
       in, im, out, om, add, per, ntiles);
+}
+
+// Both transforms of the y and z axes: plane by plane where a plane fits in LDS.
+template <int N>
+void zy_r2c(int fields, const float* in, FieldMap im, const float* in2, float a1, float a2,
+            const double* sc, float2* out, FieldMap om, hipStream_t s) {
+  if constexpr (N <= PLANE_MAX)
+    zpass_plane_r2c_kernel<N><<<fields * N, Plane<N>::NTH, 0, s>>>(in, im, in2, a1, a2, sc, out,
+                                                                   om);
+}
+
+template <int N>
+void yz_c2r(int fields, const float2* in, FieldMap im, float* out, FieldMap om, const float* add,
+            hipStream_t s) {
+  if constexpr (N <= PLANE_MAX)
+    zpass_plane_c2r_kernel<N><<<fields * N, Plane<N>::NTH, 0, s>>>(in, im, out, om, add);
+}
+
+template <int N>
+void yz_c2r3(int items, const float2* in, FieldMap im, Vec3* out, size_t out_item_stride,
+             double box, hipStream_t s) {
+  if constexpr (N <= PLANE_MAX)
+    zpass_plane_c2r3_kernel<N><<<items * N, Plane<N>::NTH, 0, s>>>(in, im, out, out_item_stride,
+                                                                   box);
 }
 
 int log2i(int n) {

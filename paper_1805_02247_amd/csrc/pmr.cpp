@@ -410,16 +410,20 @@ void r2c_zy(pmr_ctx* c, int n, int ncomp, const float* in, size_t in_item_stride
             float2* out, size_t out_item_stride, size_t out_comp_stride) {
   const int fields = c->B * ncomp;
   const double n3 = (double)n * n * n, cn = (double)n * n * (n / 2 + 1);
+  const FieldMap im = fmap(ncomp, in_item_stride, in_comp_stride);
+  const FieldMap om = fmap(ncomp, out_item_stride, out_comp_stride, spec_pitch(n));
+  if (plane_passes(n)) {
+    ProfScope ps(c, PMR_PROF_ZPASS, fields * ((in2 ? 8.0 : 4.0) * n3 + 8.0 * cn));
+    launch_zy_r2c(n, fields, in, im, in2, a1, a2, scale, out, om, c->stream);
+    return;
+  }
   {
     ProfScope ps(c, PMR_PROF_ZPASS, fields * ((in2 ? 8.0 : 4.0) * n3 + 8.0 * cn));
-    launch_zpass_r2c(n, fields, in, fmap(ncomp, in_item_stride, in_comp_stride), in2, a1, a2,
-                     scale, out, fmap(ncomp, out_item_stride, out_comp_stride, spec_pitch(n)),
-                     c->stream);
+    launch_zpass_r2c(n, fields, in, im, in2, a1, a2, scale, out, om, c->stream);
   }
   {
     ProfScope ps(c, PMR_PROF_YPASS, fields * 16.0 * cn);
-    launch_ypass(n, fields, out, fmap(ncomp, out_item_stride, out_comp_stride, spec_pitch(n)), false,
-                 c->stream);
+    launch_ypass(n, fields, out, om, false, c->stream);
   }
 }
 
@@ -428,15 +432,20 @@ void c2r_yz(pmr_ctx* c, int n, int ncomp, float2* in, size_t in_item_stride, siz
             float* out, size_t out_item_stride, size_t out_comp_stride, const float* add) {
   const int fields = c->B * ncomp;
   const double n3 = (double)n * n * n, cn = (double)n * n * (n / 2 + 1);
+  const FieldMap im = fmap(ncomp, in_item_stride, in_comp_stride, spec_pitch(n));
+  const FieldMap om = fmap(ncomp, out_item_stride, out_comp_stride);
+  if (plane_passes(n)) {
+    ProfScope ps(c, PMR_PROF_ZPASS, fields * (8.0 * cn + (add ? 8.0 : 4.0) * n3));
+    launch_yz_c2r(n, fields, in, im, out, om, add, c->stream);
+    return;
+  }
   {
     ProfScope ps(c, PMR_PROF_YPASS, fields * 16.0 * cn);
-    launch_ypass(n, fields, in, fmap(ncomp, in_item_stride, in_comp_stride, spec_pitch(n)), true,
-                 c->stream);
+    launch_ypass(n, fields, in, im, true, c->stream);
   }
   {
     ProfScope ps(c, PMR_PROF_ZPASS, fields * (8.0 * cn + (add ? 8.0 : 4.0) * n3));
-    launch_zpass_c2r(n, fields, in, fmap(ncomp, in_item_stride, in_comp_stride, spec_pitch(n)), out,
-                     fmap(ncomp, out_item_stride, out_comp_stride), add, c->stream);
+    launch_zpass_c2r(n, fields, in, im, out, om, add, c->stream);
   }
 }
 
@@ -608,6 +617,8 @@ void pm_step(pmr_ctx* c, int i, bool advance = true, const uint32_t* order = nul
   // that each window's spectra stay in the memory-side cache between the passes.
   const FieldMap fm3 = fmap(3, 3 * cm, cm, spec_pitch(c->nm));
   const FieldMap fc0 = fmap(1, 3 * cm, 0, spec_pitch(c->nm));  // component 0 of each item
+  // plane by plane instead, y and z together, where a plane fits in LDS (no windows then)
+  const bool planes = plane_force(c->nm, B) && fft_slab_columns(c->nm) == 0;
   for (const KzWin& win : kz_windows(c->nm)) {
     const double part = window_share(c->nm, win);
     {
@@ -628,6 +639,7 @@ void pm_step(pmr_ctx* c, int i, bool advance = true, const uint32_t* order = nul
       ProfScope ps(c, PMR_PROF_XPASS_FORCE, part * 24.0 * B * c->cm);
       launch_xpass(XOP_FORCE_X, a, c->stream);
     }
+    if (planes) continue;
     {
       ProfScope ps(c, PMR_PROF_YPASS, part * 16.0 * B * c->cm);
       launch_ypass(c->nm, B, c->cB, fc0, true, c->stream, win);
@@ -647,7 +659,10 @@ void pm_step(pmr_ctx* c, int i, bool advance = true, const uint32_t* order = nul
     }
   }
   Vec3* F = fslot(c, fsl);
-  {
+  if (planes) {
+    ProfScope ps(c, PMR_PROF_ZPASS, 2 * 8.0 * B * c->cm + B * 12.0 * c->nm3);
+    launch_yz_c2r3(c->nm, c->B, c->cB, fm3, F, c->nm3, c->cfg.box, c->stream);
+  } else {
     ProfScope ps(c, PMR_PROF_ZPASS, 3 * 8.0 * B * c->cm + B * 12.0 * c->nm3);
     launch_zpass_c2r3(c->nm, c->B, c->cB, fm3, F, c->nm3, c->stream);
   }
@@ -684,6 +699,28 @@ void refresh_xd(pmr_ctx* c) {
     launch_noise_fields(c->ob, (size_t)c->B * c->no3, c->noise_tab, c->noise_k, c->noise_mu,
                         c->noise_w, c->stream);
   c->xd_dirty = 0;
+}
+
+// Inverse transform of spectra in the standard layout: the x pass writes `mid` (rows of
+// `pitch` values; `in` itself at the standard pitch), y and z finish from there.
+int c2r_from(int n, int batch, const float2* in, float2* mid, size_t pitch, float* out,
+             hipStream_t s) {
+  const size_t n3 = (size_t)n * n * n, cn = cplx(n), cm = (size_t)n * n * pitch;
+  XPassArgs a;
+  std::memset(&a, 0, sizeof(a));
+  a.n = n;
+  a.batch = batch;
+  a.n_in = a.n_out = 1;
+  a.in[0] = in;
+  a.out[0] = mid;
+  a.in_item_stride = cn;
+  a.out_item_stride = cm;
+  a.in_pitch = (size_t)(n / 2 + 1);
+  a.out_pitch = pitch;
+  a.box = 1.0;
+  launch_xpass(XOP_INV, a, s);
+  launch_yz_c2r(n, batch, mid, fmap(1, cm, 0, pitch), out, fmap(1, n3, 0), nullptr, s);
+  return hipGetLastError() == hipSuccess ? PMR_OK : PMR_E_HIP;
 }
 
 }  // namespace
@@ -990,11 +1027,18 @@ int pmr_adjoint(pmr_ctx* c, const double* loss_bar, const float* mass_bar, void*
     // g0 -> o0, g12 -> o1, g2 -> dbar_f (temporarily); feature adjoint:
     // dbar_f = g0 + irfft(G1 rfft(g12) - G2 rfft(g2))
     const size_t po = spec_pitch(c->no);
-    launch_zpass_r2c(c->no, B, o1, fmap(1, no3, 0), nullptr, 1.f, 0.f, nullptr, c->cB,
-                     fmap(1, 3 * co, 0, po), s);
-    launch_zpass_r2c(c->no, B, dbar_f, fmap(1, no3, 0), nullptr, 1.f, 0.f, nullptr, c->cB + co,
-                     fmap(1, 3 * co, 0, po), s);
-    launch_ypass(c->no, 2 * B, c->cB, fmap(2, 3 * co, co, po), false, s);
+    if (plane_passes(c->no)) {
+      launch_zy_r2c(c->no, B, o1, fmap(1, no3, 0), nullptr, 1.f, 0.f, nullptr, c->cB,
+                    fmap(1, 3 * co, 0, po), s);
+      launch_zy_r2c(c->no, B, dbar_f, fmap(1, no3, 0), nullptr, 1.f, 0.f, nullptr, c->cB + co,
+                    fmap(1, 3 * co, 0, po), s);
+    } else {
+      launch_zpass_r2c(c->no, B, o1, fmap(1, no3, 0), nullptr, 1.f, 0.f, nullptr, c->cB,
+                       fmap(1, 3 * co, 0, po), s);
+      launch_zpass_r2c(c->no, B, dbar_f, fmap(1, no3, 0), nullptr, 1.f, 0.f, nullptr, c->cB + co,
+                       fmap(1, 3 * co, 0, po), s);
+      launch_ypass(c->no, 2 * B, c->cB, fmap(2, 3 * co, co, po), false, s);
+    }
     XPassArgs a = xargs(c, c->no);
     a.n_in = 2;
     a.n_out = 1;
@@ -1050,6 +1094,7 @@ int pmr_adjoint(pmr_ctx* c, const double* loss_bar, const float* mass_bar, void*
                        B, c->cB, fm3, s);
     }
     const FieldMap dm1 = fmap(1, cm, 0, spec_pitch(c->nm));
+    const bool planes = plane_passes(c->nm) && fft_slab_columns(c->nm) == 0;
     for (const KzWin& win : kz_windows(c->nm)) {
       const double part = window_share(c->nm, win);
       {
@@ -1085,6 +1130,7 @@ int pmr_adjoint(pmr_ctx* c, const double* loss_bar, const float* mass_bar, void*
         ProfScope ps(c, PMR_PROF_XPASS_FORCE_ADJ, part * 24.0 * B * c->cm);
         launch_xpass(XOP_FORCE_X_ADJ, a, s);
       }
+      if (planes) continue;
       {
         ProfScope ps(c, PMR_PROF_YPASS, part * 16.0 * B * c->cm);
         launch_ypass(c->nm, B, c->cA, dm1, true, s, win);
@@ -1092,7 +1138,10 @@ int pmr_adjoint(pmr_ctx* c, const double* loss_bar, const float* mass_bar, void*
     }
     {
       ProfScope ps(c, PMR_PROF_ZPASS, B * (8.0 * c->cm + 4.0 * c->nm3));
-      launch_zpass_c2r(c->nm, B, c->cA, dm1, c->dbar, fmap(1, c->nm3, 0), nullptr, s);
+      if (planes)
+        launch_yz_c2r(c->nm, B, c->cA, dm1, c->dbar, fmap(1, c->nm3, 0), nullptr, s);
+      else
+        launch_zpass_c2r(c->nm, B, c->cA, dm1, c->dbar, fmap(1, c->nm3, 0), nullptr, s);
     }
     {
       // compulsory: position (FP64), Fbar in and g out per particle; F and dbar per cell
@@ -1242,9 +1291,8 @@ int pmr_fft_r2c(int n, int batch, const float* in, void* out, void* stream) {
   const size_t n3 = (size_t)n * n * n, cn = cplx(n);
   const size_t nh = (size_t)(n / 2 + 1);  // the caller's array has the standard pitch
   float2* o = (float2*)out;
-  launch_zpass_r2c(n, batch, in, fmap(1, n3, 0), nullptr, 1.f, 0.f, nullptr, o, fmap(1, cn, 0, nh),
-                   s);
-  launch_ypass(n, batch, o, fmap(1, cn, 0, nh), false, s);
+  launch_zy_r2c(n, batch, in, fmap(1, n3, 0), nullptr, 1.f, 0.f, nullptr, o, fmap(1, cn, 0, nh),
+                s);
   XPassArgs a;
   std::memset(&a, 0, sizeof(a));
   a.n = n;
@@ -1262,24 +1310,21 @@ int pmr_fft_r2c(int n, int batch, const float* in, void* out, void* stream) {
 int pmr_fft_c2r(int n, int batch, void* inout, float* out, void* stream) {
   if (!inout || !out || batch < 1) return PMR_E_INVALID;
   if (!pow2_in(n, 16, 512)) return PMR_E_SHAPE;
-  hipStream_t s = (hipStream_t)stream;
-  const size_t n3 = (size_t)n * n * n, cn = cplx(n);
-  const size_t nh = (size_t)(n / 2 + 1);
-  float2* d = (float2*)inout;
-  XPassArgs a;
-  std::memset(&a, 0, sizeof(a));
-  a.n = n;
-  a.batch = batch;
-  a.n_in = a.n_out = 1;
-  a.in[0] = d;
-  a.out[0] = d;
-  a.in_item_stride = a.out_item_stride = cn;
-  a.in_pitch = a.out_pitch = nh;
-  a.box = 1.0;
-  launch_xpass(XOP_INV, a, s);
-  launch_ypass(n, batch, d, fmap(1, cn, 0, nh), true, s);
-  launch_zpass_c2r(n, batch, d, fmap(1, cn, 0, nh), out, fmap(1, n3, 0), nullptr, s);
-  return hipGetLastError() == hipSuccess ? PMR_OK : PMR_E_HIP;
+  return c2r_from(n, batch, (const float2*)inout, (float2*)inout, (size_t)(n / 2 + 1), out,
+                  (hipStream_t)stream);
+}
+
+size_t pmr_fft_c2r_work_bytes(int n, int batch) {
+  if (!pow2_in(n, 16, 512) || batch < 1) return 0;
+  return (size_t)batch * n * n * spec_pitch(n) * sizeof(float2);
+}
+
+int pmr_fft_c2r_work(int n, int batch, const void* in, void* work, float* out, void* stream) {
+  if (!in || !out || batch < 1) return PMR_E_INVALID;
+  if (!pow2_in(n, 16, 512)) return PMR_E_SHAPE;
+  if (!work || ((uintptr_t)work & 15)) return PMR_E_INVALID;
+  return c2r_from(n, batch, (const float2*)in, (float2*)work, spec_pitch(n), out,
+                  (hipStream_t)stream);
 }
 
 int pmr_fft_set_tile(int n, int pass, int columns, int threads, int staging) {

@@ -210,6 +210,26 @@ void launch_paint_r2c(int n, int channels, const PaintArgs& a, int batch, float2
                       hipStream_t s);
 void launch_zpass_c2r3(int n, int items, const float2* in, FieldMap im, Vec3* out,
                        size_t out_item_stride, hipStream_t s);
+// The y and z transforms together: plane by plane in one launch up to 128^3 (plane_passes),
+// else the separate passes (the c2r then runs the inverse y pass in place on `in`).
+inline bool plane_passes(int n) { return n <= 128; }
+// The force mesh plane by plane: three transforms in turn in each workgroup, so it wants a plane
+// for every CU (256), except below 128^3, where the launches it saves are worth more. 128^3, one
+// item (128 planes): 35 us against 32 in three launches; four items 83 against 91; 64^3 x 32: 74
+// against 98. (The passes over one field at 128^3, one item: 14-16 us either way, in one launch
+// instead of two.)
+inline bool plane_force(int n, int items) {
+  return plane_passes(n) && (n < 128 || (size_t)items * n >= 256);
+}
+void launch_zy_r2c(int n, int fields, const float* in, FieldMap im, const float* in2, float a1,
+                   float a2, const double* scale_dev, float2* out, FieldMap om, hipStream_t s);
+void launch_yz_c2r(int n, int fields, float2* in, FieldMap im, float* out, FieldMap om,
+                   const float* add, hipStream_t s);
+// (plane_passes(n) only) the force mesh from the x component (field 0 of each item) and the
+// potential (field 1), both spectral along y: inverse y with the potential's y and z
+// derivatives, then c2r, into interleaved cells.
+void launch_yz_c2r3(int n, int items, const float2* in, FieldMap im, Vec3* out,
+                    size_t out_item_stride, double box, hipStream_t s);
 // A window [lo, hi) of kz columns of the half spectrum (hi = 0: all of them).
 struct KzWin {
   int lo = 0, hi = 0;
