@@ -250,8 +250,8 @@ enum {
                                      and the adjoint gathers: its algorithmic bytes are 0 */
   PMR_PROF_NETWORK = 14           /* the single network's forward and adjoint kernels; their
                                      algorithmic figure is FLOPs: 2 (4H + H^2) per voxel
-                                     forward, 2 (8H + 2H^2) adjoint (recomputed activations
-                                     and the transposed products) */
+                                     forward, the same adjoint (the transposed products; at
+                                     H = 8, which recomputes the activations, twice that) */
 };
 int pmr_profile_begin(pmr_ctx* ctx, int kernel_class, int max_launches);
 int pmr_profile_end(pmr_ctx* ctx, double* total_ms, long long* launches, double* alg_bytes);

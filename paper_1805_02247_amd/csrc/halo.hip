@@ -278,6 +278,14 @@ __device__ __forceinline__ void load_inputs(const float* __restrict__ d0,
   }
 }
 
+// One layer-1 pre-activation, its fused operations written out: left to the compiler, which
+// product is rounded first depended on how the value is used, and a different last bit here can
+// take the other BF16 value in the mixed path.
+__device__ __forceinline__ float layer1(float4 r, float f0, float f1, float f2) {
+#pragma clang fp contract(off)
+  return __builtin_fmaf(r.z, f2, __builtin_fmaf(r.x, f0, r.y * f1)) + r.w;
+}
+
 // Layer 1 as B fragments (K slots = hidden units, N = voxels) and its ReLU mask (bit t).
 template <class P, int H>
 __device__ __forceinline__ void h1_frags(const float* sw, const float (&in)[3],
@@ -291,7 +299,7 @@ __device__ __forceinline__ void h1_frags(const float* sw, const float (&in)[3],
     for (int j = 0; j < P::J; ++j) {
       const int t = kb * P::J + j, k = slot_neuron(t, g);
       const float4 r = l1_row<H>(sw, k);
-      const float a1 = r.x * f0 + r.y * f1 + r.z * f2 + r.w;
+      const float a1 = layer1(r, f0, f1, f2);
       P::set(b[kb], j, fmaxf(a1, 0.f));
       mask |= (a1 > 0.f ? 1u : 0u) << t;
     }
@@ -311,21 +319,38 @@ __device__ __forceinline__ void product(const typename P::frag (&a)[H / 16][H / 
   }
 }
 
-// y = W3 relu(a2 + b2) + b3 for the voxel of this lane's column (on all four lane groups).
+// y = W3 relu(a2 + b2) + b3 for the voxel of this lane's column (on all four lane groups), and
+// the layer-2 ReLU mask of this lane's neurons (bit 4 q + i).
 template <int H>
-__device__ __forceinline__ float out_layer(const float* sw, const floatx4_t (&acc)[H / 16]) {
+__device__ __forceinline__ float out_layer(const float* sw, const floatx4_t (&acc)[H / 16],
+                                           uint32_t& mask) {
   using S = SOff<H>;
   const int g = (threadIdx.x & 63) >> 4;
   float p = 0.f;
+  mask = 0;
 #pragma unroll
   for (int q = 0; q < H / 16; ++q)
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const float2 r = l2_row<H>(sw, 16 * q + 4 * g + i);
-      p += r.y * fmaxf(acc[q][i] + r.x, 0.f);
+      const float a2 = acc[q][i] + r.x;
+      p += r.y * fmaxf(a2, 0.f);
+      mask |= (a2 > 0.f ? 1u : 0u) << (4 * q + i);
     }
   return group_sum4(p) + sw[S::B3];
 }
+
+// What the adjoint needs of a voxel's forward pass: y, and per lane group the ReLU signs of its
+// H / 4 neurons in both layers (layer 1 in the low half). [voxel][4] words of 16 bits up to
+// H = 32, of 32 bits at 64: 12 or 20 bytes per voxel with y.
+template <int H>
+struct Signs {
+  typedef uint16_t type;
+};
+template <>
+struct Signs<64> {
+  typedef uint32_t type;
+};
 
 // W2 in the element type of P, row-major [out][in]: the BF16 copy after the FP32 block, or
 // (FP32) the block's own W2.
@@ -345,7 +370,9 @@ __global__ __launch_bounds__(TB) void mlp_fwd_mx_kernel(const float* __restrict_
                                                         const float* __restrict__ d1,
                                                         const float* __restrict__ d2, size_t n,
                                                         const float* __restrict__ w,
-                                                        float* __restrict__ mass) {
+                                                        float* __restrict__ mass,
+                                                        float* __restrict__ yout,
+                                                        typename Signs<H>::type* __restrict__ sgn) {
   using S = SOff<H>;
   constexpr int MB = MFMA_MB, GV = 16 * MB;  // voxels per group
   __shared__ __attribute__((aligned(16))) float sw[S::SIZE];
@@ -367,32 +394,40 @@ __global__ __launch_bounds__(TB) void mlp_fwd_mx_kernel(const float* __restrict_
 #pragma unroll
       for (int q = 0; q < 3; ++q) in[mb][q] = nxt[mb][q];
     load_inputs<MB>(d0, d1, d2, v0 + nwaves * GV, n, nxt);
+    float y[MB];
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) {
       typename P::frag b[H / P::KS];
-      uint32_t mask;
+      uint32_t m1, m2;
       const float* ws = lds_fence<P, H>(sw);
-      h1_frags<P, H>(ws, in[mb], b, mask);
+      h1_frags<P, H>(ws, in[mb], b, m1);
       floatx4_t acc[H / 16];
       product<P, H>(aw, b, acc);
-      const float y = out_layer<H>(ws, acc);
+      y[mb] = out_layer<H>(ws, acc, m2);
       const size_t v = v0 + 16 * mb + (l & 15);
-      if (l < 16 && v < n) mass[v] = softplus_f(y);
+      if (v < n) sgn[4 * v + (l >> 4)] = (typename Signs<H>::type)(m1 | (m2 << (H / 4)));
+    }
+    // every lane group holds both voxel blocks' outputs: the first takes one, the second the other
+    static_assert(MB == 2, "two lane groups finish the two blocks");
+    const size_t v = v0 + l;
+    if (l < GV && v < n) {
+      const float o = l < 16 ? y[0] : y[1];
+      mass[v] = softplus_f(o);
+      yout[v] = o;
     }
   }
 }
 
-// Input gradient (weights frozen, forward recomputed), as mlp_bwd_kernel, with both H x H
-// products (W2 h1 and W2^T a2bar) on the matrix cores.
+// Input gradient (weights frozen), as mlp_bwd_kernel, from the output and the ReLU signs the
+// forward kept: of the H x H products only W2^T a2bar is left, on the matrix cores. (Recomputing
+// the forward took twice its matrix and vector work: 128^3 x 4, FP32 at H = 32, 444 us, this 258,
+// with 277 -> 299 in the forward for the signs; 256^3, BF16 at H = 64, 949 -> 540 and
+// 495 -> 619.)
 template <class P, int H>
-__global__ __launch_bounds__(TB) void mlp_bwd_mx_kernel(const float* __restrict__ d0,
-                                                        const float* __restrict__ d1,
-                                                        const float* __restrict__ d2, size_t n,
-                                                        const float* __restrict__ w,
-                                                        const float* __restrict__ mbar,
-                                                        float* __restrict__ g0,
-                                                        float* __restrict__ g12,
-                                                        float* __restrict__ g2) {
+__global__ __launch_bounds__(TB) void mlp_bwd_mx_kernel(
+    const float* __restrict__ y, const typename Signs<H>::type* __restrict__ sgn, size_t n,
+    const float* __restrict__ w, const float* __restrict__ mbar, float* __restrict__ g0,
+    float* __restrict__ g12, float* __restrict__ g2) {
   using S = SOff<H>;
   constexpr int MB = MFMA_MB, GV = 16 * MB;  // voxels per group
   constexpr int KB = H / P::KS;
@@ -400,45 +435,41 @@ __global__ __launch_bounds__(TB) void mlp_bwd_mx_kernel(const float* __restrict_
   load_small_weights<H>(sw, w);
   if (n == 0) return;
   const int l = threadIdx.x & 63, c = l & 15, g = l >> 4;
-  typename P::frag aw[H / 16][KB], at[H / 16][KB];
-  load_w2_frags<P, H, false>(w2_rows<P, H>(w), aw);
+  typename P::frag at[H / 16][KB];
   load_w2_frags<P, H, true>(w2_rows<P, H>(w), at);
   const size_t groups = (n + GV - 1) / GV;
   const size_t nwaves = (size_t)gridDim.x * (TB / 64);
   size_t gi = (size_t)blockIdx.x * (TB / 64) + (threadIdx.x >> 6);
-  float nxt[MB][3], nmb[MB];
-  load_inputs<MB>(d0, d1, d2, gi * GV, n, nxt);
+  float ny[MB], nmb[MB];
+  uint32_t nsg[MB];
+  auto load = [&](size_t v0) {
 #pragma unroll
-  for (int mb = 0; mb < MB; ++mb) {
-    const size_t v = gi * GV + 16 * mb + c;
-    nmb[mb] = mbar[v < n ? v : n - 1];
-  }
+    for (int mb = 0; mb < MB; ++mb) {
+      size_t v = v0 + 16 * mb + c;
+      v = v < n ? v : n - 1;
+      ny[mb] = y[v];
+      nmb[mb] = mbar[v];
+      nsg[mb] = sgn[4 * v + g];
+    }
+  };
+  load(gi * GV);
   for (; gi < groups; gi += nwaves) {
     const size_t v0 = gi * GV;
-    float in[MB][3], mbr[MB];
+    float yr[MB], mbr[MB];
+    uint32_t sg[MB];
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) {
-#pragma unroll
-      for (int q = 0; q < 3; ++q) in[mb][q] = nxt[mb][q];
+      yr[mb] = ny[mb];
       mbr[mb] = nmb[mb];
+      sg[mb] = nsg[mb];
     }
-    load_inputs<MB>(d0, d1, d2, v0 + nwaves * GV, n, nxt);
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb) {
-      const size_t v = v0 + nwaves * GV + 16 * mb + c;
-      nmb[mb] = mbar[v < n ? v : n - 1];
-    }
+    load(v0 + nwaves * GV);
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) {
       const size_t v = v0 + 16 * mb + c;
       typename P::frag b[KB];
-      uint32_t mask;
       const float* ws = lds_fence<P, H>(sw);
-      h1_frags<P, H>(ws, in[mb], b, mask);
-      floatx4_t acc[H / 16];
-      product<P, H>(aw, b, acc);
-      const float y = out_layer<H>(ws, acc);
-      const float yb = v < n ? mbr[mb] * sigmoid_f(y) : 0.f;
+      const float yb = v < n ? mbr[mb] * sigmoid_f(yr[mb]) : 0.f;
       // a2bar = ybar W3 [a2 > 0] as B fragments (K slots = output neurons)
 #pragma unroll
       for (int kb = 0; kb < KB; ++kb)
@@ -446,9 +477,10 @@ __global__ __launch_bounds__(TB) void mlp_bwd_mx_kernel(const float* __restrict_
         for (int j = 0; j < P::J; ++j) {
           const int t = kb * P::J + j, q = t >> 2, i = t & 3;
           const float2 r = l2_row<H>(ws, 16 * q + 4 * g + i);
-          P::set(b[kb], j, acc[q][i] + r.x > 0.f ? yb * r.y : 0.f);
+          P::set(b[kb], j, (sg[mb] >> (H / 4 + t)) & 1u ? yb * r.y : 0.f);
         }
       // h1bar = W2^T a2bar; a1bar = h1bar [a1 > 0]; fbar = W1^T a1bar
+      floatx4_t acc[H / 16];
       product<P, H>(at, b, acc);
       float p0 = 0.f, p1 = 0.f, p2 = 0.f;
 #pragma unroll
@@ -456,7 +488,7 @@ __global__ __launch_bounds__(TB) void mlp_bwd_mx_kernel(const float* __restrict_
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const int t = 4 * q + i, k = 16 * q + 4 * g + i;
-          const float hb = (mask >> t) & 1u ? acc[q][i] : 0.f;
+          const float hb = (sg[mb] >> t) & 1u ? acc[q][i] : 0.f;
           const float4 r = l1_row<H>(ws, k);
           p0 += r.x * hb;
           p1 += r.y * hb;
@@ -722,58 +754,60 @@ static unsigned mx_blocks(size_t n) {
 
 template <class P, int H>
 static void mlp_fwd_mx_t(const float* d0, const float* d1, const float* d2, size_t n,
-                         const float* w, float* mass, hipStream_t s) {
+                         const float* w, float* mass, float* y, void* sgn, hipStream_t s) {
   constexpr auto k = mlp_fwd_mx_kernel<P, H>;
-  k<<<mx_blocks<k>(n), TB, 0, s>>>(d0, d1, d2, n, w, mass);
+  k<<<mx_blocks<k>(n), TB, 0, s>>>(d0, d1, d2, n, w, mass, y, (typename Signs<H>::type*)sgn);
 }
 template <class P, int H>
-static void mlp_bwd_mx_t(const float* d0, const float* d1, const float* d2, size_t n,
-                         const float* w, const float* mbar, float* g0, float* g12, float* g2,
-                         hipStream_t s) {
+static void mlp_bwd_mx_t(const float* y, const void* sgn, size_t n, const float* w,
+                         const float* mbar, float* g0, float* g12, float* g2, hipStream_t s) {
   constexpr auto k = mlp_bwd_mx_kernel<P, H>;
-  k<<<mx_blocks<k>(n), TB, 0, s>>>(d0, d1, d2, n, w, mbar, g0, g12, g2);
+  k<<<mx_blocks<k>(n), TB, 0, s>>>(y, (const typename Signs<H>::type*)sgn, n, w, mbar, g0, g12,
+                                   g2);
 }
 
+// Bytes per voxel of the forward's output and signs (none for the vector-unit network, H = 8).
+size_t mlp_keep_bytes(int H) { return H == 64 ? 20 : H >= 16 ? 12 : 0; }
+
 int launch_mlp_fwd_mfma(int H, const float* d0, const float* d1, const float* d2, size_t n,
-                        const float* w, float* mass, hipStream_t s) {
+                        const float* w, float* mass, float* y, void* sgn, hipStream_t s) {
   switch (H) {
-    case 32: mlp_fwd_mx_t<MxBF16, 32>(d0, d1, d2, n, w, mass, s); return 0;
-    case 64: mlp_fwd_mx_t<MxBF16, 64>(d0, d1, d2, n, w, mass, s); return 0;
+    case 32: mlp_fwd_mx_t<MxBF16, 32>(d0, d1, d2, n, w, mass, y, sgn, s); return 0;
+    case 64: mlp_fwd_mx_t<MxBF16, 64>(d0, d1, d2, n, w, mass, y, sgn, s); return 0;
     default: return -1;
   }
 }
 
-int launch_mlp_bwd_mfma(int H, const float* d0, const float* d1, const float* d2, size_t n,
-                        const float* w, const float* mbar, float* g0, float* g12, float* g2,
-                        hipStream_t s) {
+int launch_mlp_bwd_mfma(int H, const float* y, const void* sgn, size_t n, const float* w,
+                        const float* mbar, float* g0, float* g12, float* g2, hipStream_t s) {
   switch (H) {
-    case 32: mlp_bwd_mx_t<MxBF16, 32>(d0, d1, d2, n, w, mbar, g0, g12, g2, s); return 0;
-    case 64: mlp_bwd_mx_t<MxBF16, 64>(d0, d1, d2, n, w, mbar, g0, g12, g2, s); return 0;
+    case 32: mlp_bwd_mx_t<MxBF16, 32>(y, sgn, n, w, mbar, g0, g12, g2, s); return 0;
+    case 64: mlp_bwd_mx_t<MxBF16, 64>(y, sgn, n, w, mbar, g0, g12, g2, s); return 0;
     default: return -1;
   }
 }
 
 // FP32 network: H x H layer on the FP32 matrix cores where H is a multiple of 16, else one
-// thread per voxel on the vector units.
+// thread per voxel on the vector units (whose adjoint recomputes the forward).
 int launch_mlp_fwd(int H, const float* d0, const float* d1, const float* d2, size_t n,
-                   const float* w, float* mass, hipStream_t s) {
+                   const float* w, float* mass, float* y, void* sgn, hipStream_t s) {
   switch (H) {
     case 8: mlp_fwd_t<8>(d0, d1, d2, n, w, mass, s); return 0;
-    case 16: mlp_fwd_mx_t<MxF32, 16>(d0, d1, d2, n, w, mass, s); return 0;
-    case 32: mlp_fwd_mx_t<MxF32, 32>(d0, d1, d2, n, w, mass, s); return 0;
-    case 64: mlp_fwd_mx_t<MxF32, 64>(d0, d1, d2, n, w, mass, s); return 0;
+    case 16: mlp_fwd_mx_t<MxF32, 16>(d0, d1, d2, n, w, mass, y, sgn, s); return 0;
+    case 32: mlp_fwd_mx_t<MxF32, 32>(d0, d1, d2, n, w, mass, y, sgn, s); return 0;
+    case 64: mlp_fwd_mx_t<MxF32, 64>(d0, d1, d2, n, w, mass, y, sgn, s); return 0;
     default: return -1;
   }
 }
 
-int launch_mlp_bwd(int H, const float* d0, const float* d1, const float* d2, size_t n,
-                   const float* w, const float* mbar, float* g0, float* g12, float* g2,
-                   hipStream_t s) {
+int launch_mlp_bwd(int H, const float* d0, const float* d1, const float* d2, const float* y,
+                   const void* sgn, size_t n, const float* w, const float* mbar, float* g0,
+                   float* g12, float* g2, hipStream_t s) {
   switch (H) {
     case 8: mlp_bwd_t<8>(d0, d1, d2, n, w, mbar, g0, g12, g2, s); return 0;
-    case 16: mlp_bwd_mx_t<MxF32, 16>(d0, d1, d2, n, w, mbar, g0, g12, g2, s); return 0;
-    case 32: mlp_bwd_mx_t<MxF32, 32>(d0, d1, d2, n, w, mbar, g0, g12, g2, s); return 0;
-    case 64: mlp_bwd_mx_t<MxF32, 64>(d0, d1, d2, n, w, mbar, g0, g12, g2, s); return 0;
+    case 16: mlp_bwd_mx_t<MxF32, 16>(y, sgn, n, w, mbar, g0, g12, g2, s); return 0;
+    case 32: mlp_bwd_mx_t<MxF32, 32>(y, sgn, n, w, mbar, g0, g12, g2, s); return 0;
+    case 64: mlp_bwd_mx_t<MxF32, 64>(y, sgn, n, w, mbar, g0, g12, g2, s); return 0;
     default: return -1;
   }
 }

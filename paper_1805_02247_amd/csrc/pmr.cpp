@@ -99,6 +99,8 @@ struct pmr_ctx {
   // device buffers
   float* inv_var;
   float* mlp_w;
+  float* net_y;    // single network: output before the softplus [B][no3]
+  char* net_sgn;   // and ReLU signs, for its adjoint
   float* halo2_w;  // prepared weights of the two-network model
   float* u2;       // its position network's input adjoint [B no3 / 16][81][16]
   float* h2aux;    // its position mask and mass-network output [2][B][no3]
@@ -218,6 +220,9 @@ void plan(pmr_ctx* c, Plan& P) {
   const size_t B = c->B;
   c->inv_var = P.take<float>(c->cp);
   c->mlp_w = P.take<float>(mlp_weight_floats(c->H > 0 ? c->H : 8));
+  const size_t keep = c->H > 0 ? mlp_keep_bytes(c->H) : 0;
+  c->net_y = P.take<float>(keep ? B * c->no3 : 0);
+  c->net_sgn = P.take<char>(keep ? (keep - 4) * B * c->no3 : 0);
   const bool two = c->cfg.halo_model == PMR_HALO_TWO;
   c->halo2_w = P.take<float>(two ? HALO2_WEIGHT_FLOATS : 0);
   c->u2 = P.take<float>(two ? 81 * B * c->no3 : 0);
@@ -953,9 +958,11 @@ int pmr_forward(pmr_ctx* c, const void* modes, float* mass_out, double* loss_out
       ProfScope ps(c, PMR_PROF_NETWORK, 2.0 * (4.0 * Hd + Hd * Hd) * B * no3);
       const int rc = c->cfg.precision == PMR_MIXED
                          ? launch_mlp_fwd_mfma(c->H, c->delta_f, c->dR, c->dR + (size_t)B * no3,
-                                               (size_t)B * no3, c->mlp_w, c->mass, s)
+                                               (size_t)B * no3, c->mlp_w, c->mass, c->net_y,
+                                               c->net_sgn, s)
                          : launch_mlp_fwd(c->H, c->delta_f, c->dR, c->dR + (size_t)B * no3,
-                                          (size_t)B * no3, c->mlp_w, c->mass, s);
+                                          (size_t)B * no3, c->mlp_w, c->mass, c->net_y,
+                                          c->net_sgn, s);
       if (rc != 0) return PMR_E_SHAPE;
     }
     smooth(c, c->no, c->mass, 3, c->MR, nullptr);
@@ -1016,13 +1023,14 @@ int pmr_adjoint(pmr_ctx* c, const double* loss_bar, const float* mass_bar, void*
       launch_halo2_stencil_adj(c->u2, c->log_no, (size_t)B * no3, o0, o1, dbar_f, s);
     } else {
       const double Hd = c->H;
-      ProfScope ps(c, PMR_PROF_NETWORK, 2.0 * (8.0 * Hd + 2.0 * Hd * Hd) * B * no3);
+      const double passes = mlp_keep_bytes(c->H) ? 1.0 : 2.0;  // H = 8 recomputes the forward
+      ProfScope ps(c, PMR_PROF_NETWORK, passes * 2.0 * (4.0 * Hd + Hd * Hd) * B * no3);
       if (c->cfg.precision == PMR_MIXED)
-        launch_mlp_bwd_mfma(c->H, c->delta_f, c->dR, c->dR + (size_t)B * no3, (size_t)B * no3,
-                            c->mlp_w, o2, o0, o1, dbar_f, s);
+        launch_mlp_bwd_mfma(c->H, c->net_y, c->net_sgn, (size_t)B * no3, c->mlp_w, o2, o0, o1,
+                            dbar_f, s);
       else
-        launch_mlp_bwd(c->H, c->delta_f, c->dR, c->dR + (size_t)B * no3, (size_t)B * no3,
-                       c->mlp_w, o2, o0, o1, dbar_f, s);
+        launch_mlp_bwd(c->H, c->delta_f, c->dR, c->dR + (size_t)B * no3, c->net_y, c->net_sgn,
+                       (size_t)B * no3, c->mlp_w, o2, o0, o1, dbar_f, s);
     }
     // g0 -> o0, g12 -> o1, g2 -> dbar_f (temporarily); feature adjoint:
     // dbar_f = g0 + irfft(G1 rfft(g12) - G2 rfft(g2))

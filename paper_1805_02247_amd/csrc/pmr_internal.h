@@ -337,17 +337,19 @@ void launch_lpt2_phi_bar(const float* phi, const float* Sbar, size_t s_item_stri
 
 // halo.hip
 size_t mlp_weight_floats(int H);
+size_t mlp_keep_bytes(int H);
+// y and sgn (nullptr at H = 8): the output and ReLU signs per voxel, mlp_keep_bytes(H) in all,
+// written by the forward and read by the adjoint.
 int launch_mlp_fwd(int H, const float* d0, const float* d1, const float* d2, size_t n,
-                   const float* w, float* mass, hipStream_t s);
+                   const float* w, float* mass, float* y, void* sgn, hipStream_t s);
 int launch_mlp_prepare_bf16(int H, float* w, hipStream_t s);
 int launch_mlp_fwd_mfma(int H, const float* d0, const float* d1, const float* d2, size_t n,
-                        const float* w, float* mass, hipStream_t s);
-int launch_mlp_bwd_mfma(int H, const float* d0, const float* d1, const float* d2, size_t n,
-                        const float* w, const float* mbar, float* g0, float* g12, float* g2,
-                        hipStream_t s);
-int launch_mlp_bwd(int H, const float* d0, const float* d1, const float* d2, size_t n,
-                   const float* w, const float* mbar, float* g0, float* g12, float* g2,
-                   hipStream_t s);
+                        const float* w, float* mass, float* y, void* sgn, hipStream_t s);
+int launch_mlp_bwd_mfma(int H, const float* y, const void* sgn, size_t n, const float* w,
+                        const float* mbar, float* g0, float* g12, float* g2, hipStream_t s);
+int launch_mlp_bwd(int H, const float* d0, const float* d1, const float* d2, const float* y,
+                   const void* sgn, size_t n, const float* w, const float* mbar, float* g0,
+                   float* g12, float* g2, hipStream_t s);
 void launch_target_x(const float* mtr, size_t per_item, int batch, const double* prm, float* xd,
                      hipStream_t s);
 void launch_residual(const float* mr, const float* xd, size_t per_item, int batch,
