@@ -368,7 +368,7 @@ int pmr_lbfgs_direction(size_t n, int m, int count, const int* order, const floa
 /* pmr_lbfgs_direction without the `work` argument, for callers that cannot allocate device
  * memory (code under HIP graph capture, tight optimiser loops, harnesses that forbid it):
  * the FP64 partial sums and the two-loop scalars live in a fixed array inside the library,
- * one per GPU (2112 doubles, about 17 KB: 2048 partial sums and up to 64 scalars),
+ * one per GPU (1.6 MB: partial sums, Gram matrices and scalars),
  * held until the process ends; the call allocates nothing and frees nothing. Same arguments, rules and results
  * (bit for bit) as pmr_lbfgs_direction; PMR_E_SHAPE for m > 64 (beyond the fixed array),
  * PMR_E_HIP if the array's address on the stream's GPU cannot be taken. All calls on one

@@ -215,6 +215,228 @@ __global__ __launch_bounds__(TB) void loop_kernel(LoopArgs a, int count, LoopOrd
   loop_body(a, count, [&](int k) { return (size_t)o.slot[k]; });
 }
 
+// ---------------------------------------------------------------- two-loop recursion by its Gram matrix
+// Every inner product of the recursion is a combination of those of the s_j and y_j with the
+// y_k and g (s_i.q = s_i.g - sum_j alpha_j s_i.y_j, ...), so up to 15 pairs one pass over
+// the vectors takes all of them at once, as two 16 x 16 blocks on the FP64 matrix cores
+// (products of FP32 values exact, sums in FP64), the scalar recursion runs on them, and one more
+// pass combines the vectors. The history is read twice as in the recursion itself, but in
+// three launches instead of 2 c + 1, the direction is not written and read back at every
+// entry, and it is rounded to FP32 once. An optimiser step over the modes of a 128^3 box with
+// 10 pairs: 201 -> 110 us (the Gram pass 48 of them: 28 are the matrix instructions, 36 the reads).
+constexpr int GRAM_MAX = 15;       // pairs: with g, the columns of a block
+constexpr int GRAM_TB = 512;
+constexpr int GRAM_BLOCKS = 256;   // partial Gram matrices at most
+constexpr int GRAM_N = 2 * 256;    // [y_j | g].[y_k | g] and s_j.[y_k | g], g in column 15
+typedef double gram4 __attribute__((ext_vector_type(4)));
+typedef float float4v __attribute__((ext_vector_type(4)));
+
+int gram_blocks(size_t n) {
+  const size_t b = (n + 64 * (GRAM_TB / 64) - 1) / (64 * (GRAM_TB / 64));
+  return (int)(b < 1 ? 1 : b > GRAM_BLOCKS ? GRAM_BLOCKS : b);
+}
+
+// Vector v of block h: y_v (h = 0, also the columns) or s_v, newest first; g at (0, 15).
+template <class Slot>
+__device__ __forceinline__ const float* gram_vector(const LoopArgs& a, int count, Slot slot,
+                                                    int h, int v) {
+  if (v < count) return (h ? a.S : a.Y) + slot(v) * a.n;
+  return h == 0 && v == GRAM_MAX ? a.g : nullptr;
+}
+
+// Partial Gram matrices. A wavefront takes 64 elements at a time: lane l holds elements
+// 16 q + 4 (l / 16) .. + 3 of vector l % 16 of both blocks, which as operands of
+// v_mfma_f64_16x16x4 (A[m][k], B[k][n]: m, n = l % 16, k = l / 16) give the same element to both
+// factors whichever k it sits at. C[m][n]: n = l % 16, m = l / 16 + 4 r.
+template <class Slot>
+__device__ __forceinline__ void gram_body(const LoopArgs& a, int count, Slot slot,
+                                          double* __restrict__ out) {
+  constexpr int WAVES = GRAM_TB / 64;
+  __shared__ double red[WAVES][GRAM_N / 4];
+  const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const size_t n = a.n;
+  // rows past the last vector read g and count as zero
+  const float* pv[2];
+  bool use[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const float* p = gram_vector(a, count, slot, h, l & 15);
+    use[h] = p != nullptr;
+    pv[h] = p ? p : a.g;
+  }
+  // whole blocks as 16-byte loads where every vector starts on 16 bytes
+  const bool wide = (n & 3) == 0 && (((uintptr_t)a.S | (uintptr_t)a.Y | (uintptr_t)a.g) & 15) == 0;
+  const size_t step = (size_t)gridDim.x * WAVES * 64;
+  size_t e0 = ((size_t)blockIdx.x * WAVES + w) * 64;
+  float4v next[2][4];
+  auto load = [&](size_t e) {
+    const size_t at = e + 4 * (l >> 4);
+    if (wide && e + 64 <= n) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          next[h][q] = *reinterpret_cast<const float4v*>(pv[h] + at + 16 * q);
+    } else {
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const size_t k = at + 16 * q + i;
+            next[h][q][i] = k < n ? pv[h][k] : 0.f;
+          }
+    }
+  };
+  gram4 cy = {0.0, 0.0, 0.0, 0.0}, cs = cy;
+  if (e0 < n) load(e0);
+  while (e0 < n) {
+    float4v cur[2][4];
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        cur[h][q] = use[h] ? next[h][q] : float4v{0.f, 0.f, 0.f, 0.f};
+    e0 += step;
+    if (e0 < n) load(e0);
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const double x = (double)cur[0][q][i], y = (double)cur[1][q][i];
+        cy = __builtin_amdgcn_mfma_f64_16x16x4f64(x, x, cy, 0, 0, 0);
+        cs = __builtin_amdgcn_mfma_f64_16x16x4f64(y, x, cs, 0, 0, 0);
+      }
+  }
+  // the workgroup's wavefronts in order, a quarter of the entries at a time
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    red[w][l] = cy[r];
+    red[w][64 + l] = cs[r];
+    __syncthreads();
+    for (int t = threadIdx.x; t < GRAM_N / 4; t += GRAM_TB) {
+      double s = 0.0;
+#pragma unroll
+      for (int u = 0; u < WAVES; ++u) s += red[u][t];
+      const int lane = t & 63, row = (lane >> 4) + 4 * r, col = lane & 15;
+      out[(size_t)blockIdx.x * GRAM_N + (t >> 6) * 256 + row * 16 + col] = s;
+    }
+    __syncthreads();
+  }
+}
+
+// d = cg g + sum_j (cy_j y_j + cs_j s_j), rounded once, with the coefficients of -H g from the
+// Gram matrix (lane j of the first wavefront follows entry j through both loops); the partial
+// sums of last . d in dot_partial_body's order when `last` is given.
+template <class Slot>
+__device__ __forceinline__ void combine_body(const LoopArgs& a, int count, Slot slot,
+                                             const double* __restrict__ G) {
+  __shared__ double co[2][16];
+  __shared__ double cg_sh;
+  const double* GS = G + 256;
+  const int t = threadIdx.x;
+  if (t < 64) {
+    const int j = t < count ? t : 0;
+    double alpha = 0.0, delta = 0.0, gamma = 1.0;
+    if (count > 0) {
+      const size_t i0 = slot(0);
+      gamma = a.sy[i0] / a.yy[i0];
+      const double sy = a.sy[slot(j)];
+      double sq = GS[16 * j + GRAM_MAX];  // s_j.q
+      for (int k = 0; k < count; ++k) {              // newest to oldest
+        const double ak = __shfl(sq / sy, k, 64);
+        if (t == k) alpha = ak;
+        sq -= ak * GS[16 * j + k];
+      }
+      double yr = G[16 * j + GRAM_MAX];  // y_j.r
+      for (int k = 0; k < count; ++k) yr -= __shfl(alpha, k, 64) * G[16 * j + k];
+      yr *= gamma;
+      for (int k = count - 1; k >= 0; --k) {  // oldest to newest
+        const double dk = __shfl(alpha - yr / sy, k, 64);
+        if (t == k) delta = dk;
+        yr += dk * GS[16 * k + j];
+      }
+    }
+    if (t < count) {
+      co[0][t] = gamma * alpha;
+      co[1][t] = -delta;
+    }
+    if (t == 0) cg_sh = -gamma;
+  }
+  __syncthreads();
+  const double cg = cg_sh;
+  const size_t n = a.n, stride = (size_t)gridDim.x * TB;
+  double acc = 0.0;
+  constexpr int U = 2;  // elements in flight per thread
+  for (size_t k0 = (size_t)blockIdx.x * TB + t; k0 < n; k0 += U * stride) {
+    double r[U];
+    float gv[U], yv[U][GRAM_MAX], sv[U][GRAM_MAX];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const size_t k = k0 + u * stride;
+      const size_t e = k < n ? k : k0;
+      gv[u] = a.g[e];
+#pragma unroll
+      for (int j = 0; j < GRAM_MAX; ++j)
+        if (j < count) {
+          yv[u][j] = a.Y[slot(j) * n + e];
+          sv[u][j] = a.S[slot(j) * n + e];
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      r[u] = cg * (double)gv[u];
+#pragma unroll
+      for (int j = 0; j < GRAM_MAX; ++j)
+        if (j < count) {
+          r[u] = __builtin_fma(co[0][j], (double)yv[u][j], r[u]);
+          r[u] = __builtin_fma(co[1][j], (double)sv[u][j], r[u]);
+        }
+      const size_t k = k0 + u * stride;
+      if (k < n) {
+        const float d = (float)r[u];
+        a.d[k] = d;
+        if (a.last) acc += (double)gv[u] * (double)d;
+      }
+    }
+  }
+  if (a.last) {
+    __shared__ double sh[TB];
+    const double s = block_sum(acc, sh);
+    if (t == 0) a.partial[blockIdx.x] = s;
+  }
+}
+
+__global__ __launch_bounds__(GRAM_TB) void gram_kernel(LoopArgs a, int count, LoopOrder o,
+                                                       double* out) {
+  gram_body(a, count, [&](int k) { return (size_t)o.slot[k]; }, out);
+}
+
+// total[e] = sum over the partial matrices of entry e, one wavefront per entry (fixed order).
+__device__ __forceinline__ void gram_sum_body(const double* __restrict__ part, int blocks,
+                                              double* __restrict__ total) {
+  const int e = blockIdx.x * (TB / 64) + (threadIdx.x >> 6), l = threadIdx.x & 63;
+  double s = 0.0;
+  for (int b = l; b < blocks; b += 64) s += part[(size_t)b * GRAM_N + e];
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) s += __shfl_down(s, d, 64);
+  if (l == 0) total[e] = s;
+}
+
+__global__ __launch_bounds__(TB) void gram_sum_kernel(const double* part, int blocks,
+                                                      double* total) {
+  gram_sum_body(part, blocks, total);
+}
+
+__global__ __launch_bounds__(TB) void combine_kernel(LoopArgs a, int count, LoopOrder o,
+                                                     const double* G) {
+  combine_body(a, count, [&](int k) { return (size_t)o.slot[k]; }, G);
+}
+
+// The Gram matrix and its partials in a work buffer, after the partial sums of inner products.
+size_t gram_doubles(size_t n) { return (size_t)(gram_blocks(n) + 1) * GRAM_N; }
+
 // out = alpha a + beta b (host scalars; out may alias a or b).
 __global__ __launch_bounds__(TB) void axpby_kernel(size_t n, float alpha, const float* a,
                                                    float beta, const float* b, float* out) {
@@ -410,8 +632,9 @@ __global__ __launch_bounds__(TB) void power_reduce_kernel(const double* __restri
 
 }  // namespace
 
-// Partial sums of the three inner products of a candidate pair (the recursion uses two arrays).
-size_t vec_work_doubles(size_t) { return (size_t)3 * DOT_BLOCKS + 64; }
+// Partial sums of the three inner products of a candidate pair (the recursion uses two arrays),
+// then the Gram matrices.
+size_t vec_work_doubles(size_t n) { return (size_t)3 * DOT_BLOCKS + 64 + gram_doubles(n); }
 
 void launch_vec_dot(size_t n, const float* a, const float* b, const double* den, double* out,
                     double* work, hipStream_t s) {
@@ -426,14 +649,25 @@ void launch_vec_axpby(size_t n, float alpha, const float* a, float beta, const f
 }
 
 // d = -H g by the two-loop recursion. order[0..count): history slots, newest first. sy, yy:
-// s.y and y.y per slot (device). scal: device doubles, alpha per slot.
-void launch_lbfgs_direction(size_t n, int count, const int* order, const float* S,
+// s.y and y.y per slot (device). work: two arrays of partial sums; gram: gram_doubles(n); scal:
+// alpha per slot. The Gram form takes any count it has room for, in buffers of up to one slot
+// more than that: the same choice as the device-driven optimiser's (by its history length), so
+// that both drivers' directions agree bit for bit.
+void launch_lbfgs_direction(size_t n, int m, int count, const int* order, const float* S,
                             const float* Y, const double* sy, const double* yy, const float* g,
-                            float* d, double* work, double* scal, hipStream_t s) {
+                            float* d, double* work, double* gram, double* scal, hipStream_t s) {
   const int nb = dot_blocks(n);
   LoopArgs a{n, LOOP_FIRST, 0, S, Y, sy, yy, g, d, work, scal, nullptr};
   LoopOrder o{};
   for (int j = 0; j < count; ++j) o.slot[j] = (unsigned char)order[j];
+  if (count <= GRAM_MAX && m <= GRAM_MAX + 1) {
+    const int gb = gram_blocks(n);
+    double* total = gram + (size_t)gb * GRAM_N;
+    gram_kernel<<<gb, GRAM_TB, 0, s>>>(a, count, o, gram);
+    gram_sum_kernel<<<GRAM_N / (TB / 64), TB, 0, s>>>(gram, gb, total);
+    combine_kernel<<<nb, TB, 0, s>>>(a, count, o, total);
+    return;
+  }
   loop_kernel<<<nb, TB, 0, s>>>(a, count, o);
   a.kind = LOOP_DOWN;
   for (a.j = 0; a.j < count; ++a.j) loop_kernel<<<nb, TB, 0, s>>>(a, count, o);  // newest first
@@ -486,6 +720,24 @@ __global__ __launch_bounds__(TB) void lb_dot_partial_kernel(const pmr_lbfgs_stat
 __global__ __launch_bounds__(TB) void lb_loop_kernel(const pmr_lbfgs_state* st, LoopArgs a) {
   if (!gate_open(st, G_DIR, a.kind == LOOP_FIRST ? -1 : a.j)) return;
   loop_body(a, st->count, [&](int k) { return (size_t)st->order[k]; });
+}
+
+// The Gram form of the same.
+__global__ __launch_bounds__(GRAM_TB) void lb_gram_kernel(const pmr_lbfgs_state* st, LoopArgs a,
+                                                          double* out) {
+  if (!gate_open(st, G_DIR, -1)) return;
+  gram_body(a, st->count, [&](int k) { return (size_t)st->order[k]; }, out);
+}
+__global__ __launch_bounds__(TB) void lb_gram_sum_kernel(const pmr_lbfgs_state* st,
+                                                         const double* part, int blocks,
+                                                         double* total) {
+  if (!gate_open(st, G_DIR, -1)) return;
+  gram_sum_body(part, blocks, total);
+}
+__global__ __launch_bounds__(TB) void lb_combine_kernel(const pmr_lbfgs_state* st, LoopArgs a,
+                                                        const double* G) {
+  if (!gate_open(st, G_DIR, -1)) return;
+  combine_body(a, st->count, [&](int k) { return (size_t)st->order[k]; }, G);
 }
 
 // The candidate pair of an accepted trial, s = xt - x and y = gt - g, into its slot, with the
@@ -667,12 +919,22 @@ void lb_direction(pmr_lbfgs_state* st, size_t n, int m, const float* g, float* d
   const int nb = dot_blocks(n);
   lb_gg_kernel<<<1, TB, 0, s>>>(st, work, nb);
   LoopArgs a{n, LOOP_FIRST, 0, S, Y, sy, yy, g, d, work, st->alpha, g};
-  lb_loop_kernel<<<nb, TB, 0, s>>>(st, a);
-  a.kind = LOOP_DOWN;
-  for (a.j = 0; a.j < m; ++a.j) lb_loop_kernel<<<nb, TB, 0, s>>>(st, a);  // newest to oldest
-  a.kind = LOOP_UP;
-  for (a.j = m - 1; a.j >= 0; --a.j) lb_loop_kernel<<<nb, TB, 0, s>>>(st, a);  // oldest to newest
-  // (the 2 count + 1 launches that ran leave the partials of g.d in the first array)
+  if (m <= GRAM_MAX) {
+    const int gb = gram_blocks(n);
+    double* gram = work + 3 * DOT_BLOCKS + 64;
+    double* total = gram + (size_t)gb * GRAM_N;
+    lb_gram_kernel<<<gb, GRAM_TB, 0, s>>>(st, a, gram);
+    lb_gram_sum_kernel<<<GRAM_N / (TB / 64), TB, 0, s>>>(st, gram, gb, total);
+    lb_combine_kernel<<<nb, TB, 0, s>>>(st, a, total);
+  } else {
+    lb_loop_kernel<<<nb, TB, 0, s>>>(st, a);
+    a.kind = LOOP_DOWN;
+    for (a.j = 0; a.j < m; ++a.j) lb_loop_kernel<<<nb, TB, 0, s>>>(st, a);  // newest to oldest
+    a.kind = LOOP_UP;
+    for (a.j = m - 1; a.j >= 0; --a.j) lb_loop_kernel<<<nb, TB, 0, s>>>(st, a);  // to newest
+  }
+  // (either way the partials of g.d are in the first array: after 2 count + 1 launches that ran,
+  // or from the combination)
   lb_gd_kernel<<<1, TB, 0, s>>>(st, work, nb);
   lb_axpby_kernel<<<stream_grid(n), TB, 0, s>>>(st, G_RESET, n, -1.f, g, 0.f, g, d);
 }
@@ -720,11 +982,12 @@ void launch_power_bins(int n, double box, const float2* a, const float2* b, int 
 }  // namespace pmr
 
 // ---------------------------------------------------------------- fixed scratch
-// The scratch of pmr_lbfgs_direction_noalloc: the two arrays of partial sums followed by the
-// two-loop scalars (alpha per slot: at most 64). One copy per GPU, held until the process ends; every call on a
+// The scratch of pmr_lbfgs_direction_noalloc: the two arrays of partial sums, the two-loop
+// scalars (alpha per slot: at most 64) and the Gram matrices. One copy per GPU, held until the process ends; every call on a
 // GPU shares it, so calls that overlap on one GPU (several streams or threads) race.
 constexpr int NOALLOC_MAX_M = 64;
-constexpr size_t NOALLOC_DOUBLES = (size_t)2 * pmr::DOT_BLOCKS + NOALLOC_MAX_M;
+constexpr size_t NOALLOC_DOUBLES = (size_t)2 * pmr::DOT_BLOCKS + NOALLOC_MAX_M +
+                                   (size_t)(pmr::GRAM_BLOCKS + 1) * pmr::GRAM_N;
 static __device__ __align__(256) double scratch[NOALLOC_DOUBLES];
 
 namespace {
@@ -792,8 +1055,8 @@ int pmr_lbfgs_direction(size_t n, int m, int count, const int* order, const floa
     }
   }
   double* w = (double*)work;
-  launch_lbfgs_direction(n, count, order, S, Y, sy, yy, g, d, w, w + vec_work_doubles(n),
-                         (hipStream_t)stream);
+  launch_lbfgs_direction(n, m, count, order, S, Y, sy, yy, g, d, w, w + 3 * DOT_BLOCKS + 64,
+                         w + vec_work_doubles(n), (hipStream_t)stream);
   return hipGetLastError() == hipSuccess ? PMR_OK : PMR_E_HIP;
 }
 
@@ -814,7 +1077,8 @@ int pmr_lbfgs_direction_noalloc(size_t n, int m, int count, const int* order, co
   double* w = nullptr;
   const int st = scratch_of(s, &w);
   if (st != PMR_OK) return st;
-  launch_lbfgs_direction(n, count, order, S, Y, sy, yy, g, d, w, w + 2 * DOT_BLOCKS, s);
+  launch_lbfgs_direction(n, m, count, order, S, Y, sy, yy, g, d, w,
+                         w + 2 * DOT_BLOCKS + NOALLOC_MAX_M, w + 2 * DOT_BLOCKS, s);
   return hipGetLastError() == hipSuccess ? PMR_OK : PMR_E_HIP;
 }
 
