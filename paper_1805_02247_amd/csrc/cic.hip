@@ -28,6 +28,8 @@ namespace {
 
 constexpr int TB = 256;  // threads per block for per-particle kernels
 
+#include "sort_network.h"
+
 // ---------------------------------------------------------------- keys
 // Key and CIC fractions (id order) of one particle on an nm mesh.
 __device__ __forceinline__ uint32_t key_frac(const double* xyz, double scale, int nm, uint32_t item,
@@ -41,25 +43,21 @@ __device__ __forceinline__ uint32_t key_frac(const double* xyz, double scale, in
   return item * cells + ((uint32_t)ix * nm + iy) * nm + iz;
 }
 
-// Clears the counters of the sort that follows (thread g of `total`).
-__device__ __forceinline__ void clear_counters(SortClear c, int g, int total) {
-  for (size_t i = (size_t)g; i < c.n; i += (size_t)total) c.p[i] = 0u;
-}
-
 __global__ void keys_kernel(const double* __restrict__ x, int log_np3, int total, double scale,
                             int nm, uint32_t* __restrict__ keys, Vec3* __restrict__ frac,
-                            SortClear clear) {
+                            SortCount count) {
   const int g = blockIdx.x * TB + threadIdx.x;
-  if (g >= total) return;
-  clear_counters(clear, g, total);
+  if (g >= total) return;  // (whole wavefronts: totals are multiples of 16^3)
   const size_t np3 = (size_t)1 << log_np3;
   const uint32_t item = g >> log_np3;
   const size_t id = g & (np3 - 1);
   const double* xi = x + (size_t)item * 3 * np3 + id;
   double p[3] = {xi[0], xi[np3], xi[2 * np3]};
   Vec3 f;
-  keys[g] = key_frac(p, scale, nm, item, &f);
+  const uint32_t key = key_frac(p, scale, nm, item, &f);
+  keys[g] = key;
   if (frac) frac[g] = f;
+  if (count.cnt) count_segments(count.cnt, key >> count.shift);
 }
 
 // ---------------------------------------------------------------- sorted particle streams
@@ -171,7 +169,7 @@ struct StepArgs {
   double drift;
   int key_nm;         // mesh of the keys emitted for x_{i+1}
   double key_scale;
-  SortClear clear;    // counters of the sort of those keys
+  SortCount count;    // counters of the sort of those keys
 };
 
 // First particle of block L when the lattice rows (item, i, j, :) are visited in patches of
@@ -206,7 +204,6 @@ __global__ __launch_bounds__(TB) void kick_drift_kernel(StepArgs a) {
                     ? patch_block_start(L, log_np, KD_PATCH_LOG) + threadIdx.x
                     : L * TB + threadIdx.x;
   if (g >= a.total) return;
-  clear_counters(a.clear, g, a.total);
   const size_t np3 = (size_t)1 << a.log_np3;
   const int item = g >> a.log_np3;
   const size_t id = g & (np3 - 1);
@@ -246,7 +243,9 @@ __global__ __launch_bounds__(TB) void kick_drift_kernel(StepArgs a) {
   }
   if (a.keys) {
     Vec3 f;
-    __builtin_nontemporal_store(key_frac(xn, a.key_scale, a.key_nm, item, &f), a.keys + g);
+    const uint32_t key = key_frac(xn, a.key_scale, a.key_nm, item, &f);
+    if (a.count.cnt) count_segments(a.count.cnt, key >> a.count.shift);
+    __builtin_nontemporal_store(key, a.keys + g);
     __builtin_nontemporal_store(f.x, &a.frac[g].x);
     __builtin_nontemporal_store(f.y, &a.frac[g].y);
     __builtin_nontemporal_store(f.z, &a.frac[g].z);
@@ -378,10 +377,9 @@ __global__ __launch_bounds__(TB) void za_init_kernel(const float* __restrict__ p
                                                      float* __restrict__ p_ck,
                                                      uint32_t* __restrict__ keys,
                                                      Vec3* __restrict__ frac, int key_nm,
-                                                     double key_scale, SortClear clear) {
+                                                     double key_scale, SortCount count) {
   const int g = blockIdx.x * TB + threadIdx.x;
   if (g >= total) return;
-  clear_counters(clear, g, total);
   const size_t np3 = (size_t)1 << log_np3;
   const int item = g >> log_np3;
   const size_t id = g & (np3 - 1);
@@ -400,17 +398,19 @@ __global__ __launch_bounds__(TB) void za_init_kernel(const float* __restrict__ p
     if (p_ck) p_ck[pi + q * np3] = Gp0 * ps + c2p * ps2;
   }
   Vec3 f;
-  keys[g] = key_frac(xn, key_scale, key_nm, item, &f);
+  const uint32_t key = key_frac(xn, key_scale, key_nm, item, &f);
+  keys[g] = key;
   frac[g] = f;
+  if (count.cnt) count_segments(count.cnt, key >> count.shift);
 }
 
 }  // namespace
 
 // ================================================================ host launchers
 void launch_keys(const double* x, int log_np3, int total, double scale, int nm, uint32_t* keys,
-                 Vec3* frac, SortClear clear, hipStream_t s) {
+                 Vec3* frac, SortCount count, hipStream_t s) {
   keys_kernel<<<(total + TB - 1) / TB, TB, 0, s>>>(x, log_np3, total, scale, nm, keys, frac,
-                                                   clear);
+                                                   count);
 }
 
 // Rows per wave: the tuned value when set and valid, else the default rule (see
@@ -476,9 +476,9 @@ void launch_paint_mass(const uint32_t* keys, const Vec3* frac, const uint32_t* r
 void launch_kick_drift(const double* x, double* x_next, const float* p_in, float* p,
                        float* p_ck, const Vec3* F, uint32_t* keys, Vec3* frac, int batch,
                        int log_np3, int nm, double box, float kick, double drift, int key_nm,
-                       SortClear clear, hipStream_t s) {
+                       SortCount count, hipStream_t s) {
   StepArgs a{};
-  a.clear = clear;
+  a.count = count;
   a.frac = frac;
   a.x = x;
   a.x_next = x_next;
@@ -545,12 +545,12 @@ void launch_adjoint_update(float* xbar, float* pbar, const Vec3* gpos, int batch
 void launch_za_init(const float* psi, const float* psi2, int batch, int np, int log_np3,
                     double box, double half_cell, double D0, float Gp0, double c2x, float c2p,
                     double* x, float* p, float* p_ck, uint32_t* keys, Vec3* frac, int key_nm,
-                    SortClear clear, hipStream_t s) {
+                    SortCount count, hipStream_t s) {
   const int total = batch << log_np3;
   za_init_kernel<<<(total + TB - 1) / TB, TB, 0, s>>>(psi, psi2, np, log_np3, total, box,
                                                        half_cell, D0, Gp0, c2x, c2p, x, p, p_ck,
                                                        keys, frac, key_nm, (double)key_nm / box,
-                                                       clear);
+                                                       count);
 }
 
 }  // namespace pmr

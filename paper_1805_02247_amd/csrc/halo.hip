@@ -614,6 +614,7 @@ __global__ __launch_bounds__(TB) void sumsq_partial_kernel(const float* __restri
   const size_t base = (size_t)b * per_item + (size_t)blockIdx.x * RED_TILE;
   const size_t lim = (size_t)b * per_item + per_item;
   double s = 0.0;
+#pragma unroll
   for (int i = 0; i < RED_ITEMS; ++i) {
     const size_t j = base + (size_t)i * TB + threadIdx.x;
     if (j < lim) {
@@ -625,28 +626,30 @@ __global__ __launch_bounds__(TB) void sumsq_partial_kernel(const float* __restri
   if (threadIdx.x == 0) partial[(size_t)b * nblk + blockIdx.x] = tot;
 }
 
-// out[b] = sum_k partial[b][k] in a fixed order (one block per item)
-__global__ __launch_bounds__(TB) void sum_partials_kernel(const double* __restrict__ partial,
-                                                          int nblk, double* __restrict__ out) {
-  __shared__ double sh[TB];
-  const int b = blockIdx.x;
+// Sum of an item's partials in a fixed order, on every thread of its block.
+__device__ __forceinline__ double sum_partials(const double* __restrict__ partial, int nblk,
+                                               double* sh) {
   double s = 0.0;
-  for (int k = threadIdx.x; k < nblk; k += TB) s += partial[(size_t)b * nblk + k];
-  const double tot = block_sum_fixed(s, sh);
-  if (threadIdx.x == 0) out[b] = tot;
+  for (int k = threadIdx.x; k < nblk; k += TB) s += partial[k];
+  return block_sum_fixed(s, sh);
 }
 
-// loss_out[b] = (prior_weight * prior + data, prior, data)
-__global__ void finalize_loss_kernel(const double* __restrict__ prior, const double* __restrict__ data,
-                                     const double* __restrict__ prm, int batch,
-                                     double* __restrict__ loss_out) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= batch) return;
+// loss_out[b] = (prior_weight * prior + data, prior, data) from their partial sums (one block
+// per item)
+__global__ __launch_bounds__(TB) void finalize_loss_kernel(const double* __restrict__ pp, int np,
+                                                           const double* __restrict__ dp, int nd,
+                                                           const double* __restrict__ prm,
+                                                           double* __restrict__ loss_out) {
+  __shared__ double sh[TB];
+  const int b = blockIdx.x;
+  const double prior = sum_partials(pp + (size_t)b * np, np, sh);
+  const double data = sum_partials(dp + (size_t)b * nd, nd, sh);
+  if (threadIdx.x != 0) return;
   // an item whose parameters failed the device-side check reports a NaN loss
   const double bad = prm[b * NPRM + PRM_VALID] != 0.0 ? 0.0 : __builtin_nan("");
-  loss_out[3 * b + 0] = prm[b * NPRM + 5] * prior[b] + data[b] + bad;
-  loss_out[3 * b + 1] = prior[b] + bad;
-  loss_out[3 * b + 2] = data[b] + bad;
+  loss_out[3 * b + 0] = prm[b * NPRM + 5] * prior + data + bad;
+  loss_out[3 * b + 1] = prior + bad;
+  loss_out[3 * b + 2] = data + bad;
 }
 
 // ---------------------------------------------------------------- loss parameters
@@ -687,29 +690,34 @@ __global__ void noise_table_store_kernel(NoiseTable t, double* __restrict__ tab)
 __global__ __launch_bounds__(TB) void project_prior_kernel(const float2* __restrict__ s, int n,
                                                            const float* __restrict__ inv_var,
                                                            float2* __restrict__ ps, int nblk,
-                                                           double* __restrict__ partial) {
+                                                           double* __restrict__ partial,
+                                                           uint32_t* __restrict__ cnt,
+                                                           size_t n_cnt) {
   __shared__ double sh[TB];
-  const int nh = n / 2 + 1;
-  const size_t per = (size_t)n * n * nh;
+  for (size_t i = ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * TB + threadIdx.x; i < n_cnt;
+       i += (size_t)gridDim.x * gridDim.y * TB)
+    cnt[i] = 0u;
+  const uint32_t nh = n / 2 + 1;
+  const uint32_t per = (uint32_t)n * n * nh;  // n <= 512: fits 32 bits
   const int b = blockIdx.y;
-  const float2* sb = s + b * per;
+  const float2* sb = s + (size_t)b * per;
   double acc = 0.0;
+#pragma unroll 8
   for (int i = 0; i < RED_ITEMS; ++i) {
-    const size_t e = (size_t)blockIdx.x * RED_TILE + (size_t)i * TB + threadIdx.x;
+    const uint32_t e = blockIdx.x * RED_TILE + i * TB + threadIdx.x;
     if (e >= per) continue;
-    const int kz = (int)(e % nh);
-    const int iy = (int)((e / nh) % n);
-    const int ix = (int)(e / ((size_t)nh * n));
+    const uint32_t row = e / nh, kz = e - row * nh;
     float2 v = sb[e];
     double w = 2.0;
-    if (kz == 0 || kz == n / 2) {
-      const int jx = (n - ix) & (n - 1), jy = (n - iy) & (n - 1);
+    if (kz == 0 || kz == (uint32_t)n / 2) {
+      const uint32_t iy = row & (n - 1), ix = row / n;
+      const uint32_t jx = (n - ix) & (n - 1), jy = (n - iy) & (n - 1);
       const float2 q = sb[((size_t)jx * n + jy) * nh + kz];
       v = make_float2(0.5f * (v.x + q.x), 0.5f * (v.y - q.y));
       w = 1.0;
     }
     if (e == 0) v = make_float2(0.f, 0.f);
-    ps[b * per + e] = v;
+    ps[(size_t)b * per + e] = v;
     acc += 0.5 * w * ((double)v.x * v.x + (double)v.y * v.y) * (double)inv_var[e];
   }
   const double tot = block_sum_fixed(acc, sh);
@@ -839,25 +847,24 @@ void launch_l2_adj(const float* d, const float* t, size_t per_item, int batch,
 
 int reduce_blocks(size_t per_item) { return (int)((per_item + RED_TILE - 1) / RED_TILE); }
 
-// out[b] = sum over item b of (a - c)^2, deterministic.
 void launch_sumsq(const float* a, const float* c, size_t per_item, int batch, double* partial,
-                  double* out, hipStream_t s) {
+                  hipStream_t s) {
   const int nblk = reduce_blocks(per_item);
   sumsq_partial_kernel<<<dim3(nblk, batch), TB, 0, s>>>(a, c, per_item, nblk, partial);
-  sum_partials_kernel<<<batch, TB, 0, s>>>(partial, nblk, out);
 }
 
 void launch_project_prior(const float2* modes, int n, int batch, const float* inv_var, float2* ps,
-                          double* partial, double* prior_out, hipStream_t s) {
+                          double* partial, uint32_t* cnt, size_t n_cnt,
+                          hipStream_t s) {
   const size_t per = (size_t)n * n * (n / 2 + 1);
   const int nblk = reduce_blocks(per);
-  project_prior_kernel<<<dim3(nblk, batch), TB, 0, s>>>(modes, n, inv_var, ps, nblk, partial);
-  sum_partials_kernel<<<batch, TB, 0, s>>>(partial, nblk, prior_out);
+  project_prior_kernel<<<dim3(nblk, batch), TB, 0, s>>>(modes, n, inv_var, ps, nblk, partial, cnt,
+                                                        n_cnt);
 }
 
-void launch_finalize_loss(const double* prior, const double* data, const double* prm, int batch,
-                          double* loss_out, hipStream_t s) {
-  finalize_loss_kernel<<<(batch + 63) / 64, 64, 0, s>>>(prior, data, prm, batch, loss_out);
+void launch_finalize_loss(const double* prior, int n_prior, const double* data, int n_data,
+                          const double* prm, int batch, double* loss_out, hipStream_t s) {
+  finalize_loss_kernel<<<batch, TB, 0, s>>>(prior, n_prior, data, n_data, prm, loss_out);
 }
 
 void launch_params_store(const double* host, int batch, double* prm, hipStream_t s) {

@@ -130,6 +130,8 @@ struct pmr_ctx {
   uint32_t* keys_sorted;
   void* sort_scratch;
   size_t sort_scratch_bytes;
+  uint32_t* sort_cnt;  // counters of the sorts, zero between them
+  size_t n_sort_cnt;
   uint32_t* ids_o;
   Vec3* frac_o;
   Vec3* frac_id;  // CIC fractions of the current positions, id order [B*np3]
@@ -153,9 +155,8 @@ struct pmr_ctx {
   float* pbar;
   float* dbar;   // [B][nm3]
   float* ob;     // [4][B][no3]
-  double* partial;
-  double* prior;
-  double* data;
+  double* partial;   // partial sums of the data term [B][reduce_blocks(no^3)]
+  double* ppartial;  // and of the prior [B][reduce_blocks(np^2 (np/2 + 1))]
   // event timing of one kernel class (pmr_profile_begin/end)
   int prof_class;
   std::vector<hipEvent_t> prof_ev;
@@ -253,6 +254,12 @@ void plan(pmr_ctx* c, Plan& P) {
     c->sort_scratch_bytes = sm > so ? sm : so;
   }
   c->sort_scratch = P.take<char>(c->sort_scratch_bytes);
+  {
+    const size_t sm = cell_sort_segments((int)(B * c->np3), B * c->nm * c->nm, c->log_nm);
+    const size_t so = cell_sort_segments((int)(B * c->np3), B * c->no * c->no, c->log_no);
+    c->n_sort_cnt = sm > so ? sm : so;
+  }
+  c->sort_cnt = P.take<uint32_t>(c->n_sort_cnt);
   c->ids_o = P.take<uint32_t>(B * c->np3);
   c->frac_o = P.take<Vec3>(B * c->np3);
   c->frac_id = P.take<Vec3>(B * c->np3);
@@ -277,10 +284,8 @@ void plan(pmr_ctx* c, Plan& P) {
   c->pbar = P.take<float>(B * 3 * c->np3);
   c->dbar = P.take<float>(B * c->nm3);
   c->ob = P.take<float>(4 * B * c->no3);
-  const size_t nred = (size_t)reduce_blocks(c->cmax > c->no3 ? c->cmax : c->no3);
-  c->partial = P.take<double>(B * nred);
-  c->prior = P.take<double>(B);
-  c->data = P.take<double>(B);
+  c->partial = P.take<double>(B * reduce_blocks(c->no3));
+  c->ppartial = P.take<double>(B * reduce_blocks(c->cp));
 }
 
 void init_sizes(pmr_ctx* c, const pmr_config* cfg) {
@@ -582,10 +587,16 @@ uint32_t* invslot(pmr_ctx* c, int s) {
 }
 uint32_t* rowslot(pmr_ctx* c, int s) { return c->rows + (size_t)s * (c->B * c->nm * c->nm + 1); }
 int fs_of(pmr_ctx* c, int i) { return c->k == 0 ? i : i % c->k; }
-// The counters of the sort on the nm^3 mesh, for the kernel that writes its keys to clear.
-SortClear sort_counters(pmr_ctx* c, int nm) {
-  return cell_sort_clear(c->sort_scratch, (int)(c->B * c->np3), (size_t)c->B * nm * nm,
-                         ilog2((size_t)nm));
+// The kernels that write keys on the nm^3 mesh count their segments on the way where the
+// sort's segment numbers are packed (below 2^25). A launch that only counts reads every key
+// again and cost 3-4 us for few particles, 29 us at 128^3 x 4 and 92 at 256^3 on 512^3; the
+// counting adds 0.4, 12 and 60 us to the kick.
+bool count_with_keys(pmr_ctx* c, int nm) {
+  return cell_sort_packed((int)(c->B * c->np3), (size_t)c->B * nm * nm, ilog2((size_t)nm));
+}
+SortCount key_count(pmr_ctx* c, int nm) {
+  if (!count_with_keys(c, nm)) return SortCount{nullptr, 0};
+  return sort_count(c->sort_cnt, (int)(c->B * c->np3), (size_t)c->B * nm * nm, ilog2((size_t)nm));
 }
 
 // One forward PM step i: sort x_i, paint, force, kick + drift (keys of x_{i+1} emitted on
@@ -604,8 +615,9 @@ void pm_step(pmr_ctx* c, int i, bool advance = true, const uint32_t* order = nul
   {
     ProfScope ps(c, PMR_PROF_SORT, 0.0);
     launch_cell_sort(c->keys, order, total, c->log_nm, (size_t)B * c->nm * c->nm, keyslot(c, fsl),
-                     idslot(c, fsl), rowslot(c, fsl), c->sort_scratch, c->frac_id,
-                     fracslot(c, fsl), invslot(c, fsl), c->stream);
+                     idslot(c, fsl), rowslot(c, fsl), c->sort_cnt, count_with_keys(c, c->nm),
+                     c->n_sort_cnt, c->sort_scratch, c->frac_id, fracslot(c, fsl),
+                     invslot(c, fsl), c->stream);
   }
   const size_t cm = c->sm;
   const FieldMap dm = fmap(1, cm, 0, spec_pitch(c->nm));
@@ -681,7 +693,7 @@ void pm_step(pmr_ctx* c, int i, bool advance = true, const uint32_t* order = nul
     float* pck = (c->k > 0 && (i + 1) % c->k == 0 && i + 1 < c->n) ? ckpt_p(c, (i + 1) / c->k)
                                                                       : nullptr;
     launch_kick_drift(x, xn, p_in, c->p, pck, F, c->keys, c->frac_id, B, c->log_np3, c->nm,
-                      c->cfg.box, (float)c->kick[i], c->drift[i], key_nm, sort_counters(c, key_nm),
+                      c->cfg.box, (float)c->kick[i], c->drift[i], key_nm, key_count(c, key_nm),
                       c->stream);
   }
 }
@@ -894,7 +906,8 @@ int pmr_forward(pmr_ctx* c, const void* modes, float* mass_out, double* loss_out
   const int B = c->B;
   hipStream_t s = c->stream;
   // H0: projection and prior
-  launch_project_prior((const float2*)modes, c->np, B, c->inv_var, c->ps, c->partial, c->prior, s);
+  launch_project_prior((const float2*)modes, c->np, B, c->inv_var, c->ps, c->ppartial,
+                       c->sort_cnt, c->n_sort_cnt, s);
   // data term of the target (log-normal): x_data = log(G_Rmass * M_t + M0)
   if (c->xd_dirty) refresh_xd(c);
   // H1: Zel'dovich displacement on the particle lattice
@@ -918,7 +931,7 @@ int pmr_forward(pmr_ctx* c, const void* modes, float* mass_out, double* loss_out
                    second ? kLpt2 * c->D0 * c->D0 : 0.0,
                    second ? (float)(2.0 * kLpt2 * c->D0 * c->Gp0) : 0.f, xpos(c, 0), c->p,
                    c->k > 0 ? ckpt_p(c, 0) : nullptr, c->keys, c->frac_id, key_nm,
-                   sort_counters(c, key_nm), s);
+                   key_count(c, key_nm), s);
   }
   // H2-H7: the PM steps
   pm_run(c, 0, c->n);
@@ -928,12 +941,13 @@ int pmr_forward(pmr_ctx* c, const void* modes, float* mass_out, double* loss_out
     ProfScope ps(c, PMR_PROF_SORT, 0.0);
     launch_cell_sort(c->keys, idslot(c, fs_of(c, c->n - 1)), total, c->log_no,
                      (size_t)B * c->no * c->no, c->keys_sorted,
-                     c->ids_o, c->rows_o, c->sort_scratch, c->frac_id, c->frac_o, nullptr, s);
+                     c->ids_o, c->rows_o, c->sort_cnt, count_with_keys(c, c->no), c->n_sort_cnt,
+                     c->sort_scratch, c->frac_id, c->frac_o, nullptr, s);
   }
   launch_paint_mass(c->keys_sorted, c->frac_o, c->rows_o, B, c->no, c->mass_o, 1.f, c->delta_f, s);
   // H9-H11: halo model and likelihood
   if (c->cfg.loss_kind == PMR_LOSS_DENSITY_L2) {
-    launch_sumsq(c->delta_f, c->target, c->no3, B, c->partial, c->data, s);
+    launch_sumsq(c->delta_f, c->target, c->no3, B, c->partial, s);
     if (mass_out)
       HIPC(c, hipMemcpyAsync(mass_out, c->delta_f, B * c->no3 * sizeof(float), hipMemcpyDeviceToDevice, s));
   } else {
@@ -969,10 +983,11 @@ int pmr_forward(pmr_ctx* c, const void* modes, float* mass_out, double* loss_out
     launch_residual(c->MR, c->xd, no3, B, c->params, c->noise_k ? c->noise_mu : nullptr,
                     c->noise_k ? c->noise_w : nullptr, c->r, s);
     smooth(c, c->no, c->r, 4, c->rs, nullptr);
-    launch_sumsq(c->rs, nullptr, no3, B, c->partial, c->data, s);
+    launch_sumsq(c->rs, nullptr, no3, B, c->partial, s);
     if (mass_out) HIPC(c, hipMemcpyAsync(mass_out, c->mass, B * no3 * sizeof(float), hipMemcpyDeviceToDevice, s));
   }
-  launch_finalize_loss(c->prior, c->data, c->params, B, loss_out, s);
+  launch_finalize_loss(c->ppartial, reduce_blocks(c->cp), c->partial, reduce_blocks(c->no3),
+                       c->params, B, loss_out, s);
   c->fwd_done = 1;
   ++c->n_forward;
   const int st = check(c);
@@ -1078,7 +1093,7 @@ int pmr_adjoint(pmr_ctx* c, const double* loss_bar, const float* mass_bar, void*
       // the segment starts from its checkpoint, read in place (x) and as the first kick's
       // input (p)
       launch_keys(xpos(c, j), c->log_np3, (int)(B * c->np3), scale_m, c->nm, c->keys,
-                  c->frac_id, sort_counters(c, c->nm), s);
+                  c->frac_id, key_count(c, c->nm), s);
       const int end = j + c->k < c->n ? j + c->k : c->n;
       // the adjoint of steps j .. end-1 needs x, the sort and F of each step, not the
       // positions the last kick and drift would produce (the next checkpoint)
@@ -1389,10 +1404,15 @@ int pmr_cic_sort(int n_part, int n_mesh, int batch, double box, const double* x,
   void* rest = (char*)scratch + align256((size_t)total * sizeof(uint32_t));
   const size_t rows = (size_t)batch * n_mesh * n_mesh;
   const int log_nm = ilog2((size_t)n_mesh);
+  // counted as the keys are written where the segment numbers allow it
+  const size_t segs = cell_sort_segments(total, rows, log_nm);
+  const bool packed = cell_sort_packed(total, rows, log_nm);
+  uint32_t* cnt = (uint32_t*)rest;
+  launch_sort_clear(cnt, segs, s);
   launch_keys(x, ilog2(np3), total, (double)n_mesh / box, n_mesh, keys, nullptr,
-              cell_sort_clear(rest, total, rows, log_nm), s);
-  launch_cell_sort(keys, nullptr, total, log_nm, rows,
-                   keys_sorted, ids_sorted, row_start, rest, nullptr, nullptr, nullptr, s);
+              packed ? sort_count(cnt, total, rows, log_nm) : SortCount{nullptr, 0}, s);
+  launch_cell_sort(keys, nullptr, total, log_nm, rows, keys_sorted, ids_sorted, row_start, cnt,
+                   packed, 0, cnt + segs, nullptr, nullptr, nullptr, s);
   return hipGetLastError() == hipSuccess ? PMR_OK : PMR_E_HIP;
 }
 

@@ -262,23 +262,28 @@ int fft_slab_columns(int n);
 // row index row_start [rows + 1] (rows = key >> shift), pay_out[pos] = pay_in[id] and
 // inv[id] = pos when given. `order` (nullable) is the order in which the particles are
 // visited (a permutation of the ids, e.g. the previous step's sorted ids; it changes only
-// the speed). Scratch of cell_sort_scratch_bytes(n, rows) bytes. The
-// sort's counters in it must be zero: the kernel that writes the keys clears them on the way
-// (a SortClear of the same scratch, n, rows and shift), which spares the sort a launch.
-struct SortClear {
-  uint32_t* p;
-  size_t n;
+// the speed). Scratch of cell_sort_scratch_bytes(n, rows) bytes. cnt: the sort's counters, one
+// per segment (cell_sort_segments), which hold zeros, or, with `counted`, the counts that the
+// kernel that wrote the keys took (a SortCount of the same counters, n, rows and shift; packed
+// sorts only). The first n_clear counters are zero again afterwards.
+struct SortCount {
+  uint32_t* cnt;  // nullptr: the keys are not counted as they are written
+  int shift;      // key >> shift = segment
 };
-SortClear cell_sort_clear(void* scratch, int n, size_t rows, int shift);
+size_t cell_sort_segments(int n, size_t rows, int shift);
+bool cell_sort_packed(int n, size_t rows, int shift);
+SortCount sort_count(uint32_t* cnt, int n, size_t rows, int shift);
+void launch_sort_clear(uint32_t* cnt, size_t n, hipStream_t s);
 size_t cell_sort_scratch_bytes(int n, size_t rows, int shift);
 void launch_cell_sort(const uint32_t* keys, const uint32_t* order, int n, int shift,
                       size_t rows, uint32_t* keys_sorted, uint32_t* ids_sorted,
-                      uint32_t* row_start, void* scratch, const Vec3* pay_in, Vec3* pay_out,
-                      uint32_t* inv, hipStream_t s);
+                      uint32_t* row_start, uint32_t* cnt, bool counted, size_t n_clear,
+                      void* scratch, const Vec3* pay_in, Vec3* pay_out, uint32_t* inv,
+                      hipStream_t s);
 // cic.hip
-// (the kernels that write keys also clear the counters of the sort that follows)
+// (the kernels that write keys count their segments for the sort that follows when asked to)
 void launch_keys(const double* x, int log_np3, int total, double scale, int nm, uint32_t* keys,
-                 Vec3* frac, SortClear clear, hipStream_t s);
+                 Vec3* frac, SortCount count, hipStream_t s);
 void launch_stream_frac(const uint32_t* ids, const double* x, int total, int log_np3, int nm,
                         double box, Vec3* frac, hipStream_t s);
 void launch_stream_gather(const uint32_t* ids, const Vec3* src, int total, Vec3* dst,
@@ -290,7 +295,7 @@ void launch_paint_mass(const uint32_t* keys, const Vec3* frac, const uint32_t* r
 void launch_kick_drift(const double* x, double* x_next, const float* p_in, float* p,
                        float* p_ck, const Vec3* F, uint32_t* keys, Vec3* frac, int batch,
                        int log_np3, int nm, double box, float kick, double drift, int key_nm,
-                       SortClear clear, hipStream_t s);
+                       SortCount count, hipStream_t s);
 // Position gradient of a step adjoint (or of the final paint: fbar = F = nullptr), computed in
 // sort order and written to g_out in id order:
 //   g = sum_corners dW/dx * (Fbar . F(corner) + mass * dbar(corner)).
@@ -308,7 +313,7 @@ void launch_adjoint_update(float* xbar, float* pbar, const Vec3* gpos, int batch
 void launch_za_init(const float* psi, const float* psi2, int batch, int np, int log_np3,
                     double box, double half_cell, double D0, float Gp0, double c2x, float c2p,
                     double* x, float* p, float* p_ck, uint32_t* keys, Vec3* frac, int key_nm,
-                    SortClear clear, hipStream_t s);
+                    SortCount count, hipStream_t s);
 // Two-network halo model (halo2.hip). Prepared weight block of HALO2_WEIGHT_FLOATS floats.
 constexpr int HALO2_WEIGHT_FLOATS = 448 + (4 * 21 + 2 * 16 + 4 * 8 + 6 * 16) * 64;
 void launch_halo2_prepare(const float* nnp, const float* nnm, float* w, hipStream_t s);
@@ -373,11 +378,14 @@ void launch_noise_fields(const float* mrd, size_t total, const double* tab, int 
 void launch_l2_adj(const float* d, const float* t, size_t per_item, int batch,
                    const double* loss_bar, const float* extra, float* out, hipStream_t s);
 int reduce_blocks(size_t per_item);
+// Partial sums [batch][reduce_blocks(per_item)] of (a - c)^2, finished by launch_finalize_loss.
 void launch_sumsq(const float* a, const float* c, size_t per_item, int batch, double* partial,
-                  double* out, hipStream_t s);
+                  hipStream_t s);
+// Also clears the counters cnt[n_cnt] of the sorts to come.
 void launch_project_prior(const float2* modes, int n, int batch, const float* inv_var, float2* ps,
-                          double* partial, double* prior_out, hipStream_t s);
-void launch_finalize_loss(const double* prior, const double* data, const double* prm, int batch,
-                          double* loss_out, hipStream_t s);
+                          double* partial, uint32_t* cnt, size_t n_cnt,
+                          hipStream_t s);
+void launch_finalize_loss(const double* prior, int n_prior, const double* data, int n_data,
+                          const double* prm, int batch, double* loss_out, hipStream_t s);
 
 }  // namespace pmr

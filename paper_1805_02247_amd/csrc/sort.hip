@@ -1,10 +1,10 @@
 // The cell sort of the particles: the unique (cell key, id) order, the row index of the
 // sorted stream and the payloads that travel with it, in four steps.
 //
-//   1. row_count:  particles per row segment (item, ix, iy and the top bits of iz: a row or
+//   1. counts:     particles per row segment (item, ix, iy and the top bits of iz: a row or
 //                  a part of it, cell_sort_split) = key >> (log2(nm) - split), with one
-//                  atomic per distinct segment per wavefront. The counters are cleared by the
-//                  kernel that writes the keys (SortClear).
+//                  atomic per distinct segment per wavefront, taken by the kernel that writes the
+//                  keys (sort_count) on counters that each row sort leaves at zero.
 //   2. scan:       exclusive scan of the counts -> row_start (the row index the paints and
 //                  gathers use) and a cursor per segment.
 //   3. bucket:     every particle into its segment's range, at a slot taken from the segment's
@@ -18,7 +18,7 @@
 //                  radix sort in global memory. Every sorted entry is written with its
 //                  payload (gathered by id) and its inverse permutation entry.
 //
-// Compulsory traffic: the id-order keys read twice (count, bucket), one word written and read
+// Compulsory traffic: the id-order keys read once (bucket), one word written and read
 // per particle in the buckets, the sorted keys, ids and payload written; no pass over
 // 8-bit digits of the whole key array.
 #include "pmr_internal.h"
@@ -35,166 +35,19 @@ constexpr int SCAN_TILE = TB * SCAN_ITEMS;  // counts per scan block
 constexpr int SCAN1_TB = 1024;              // threads of the one-launch scan
 constexpr int SCAN1_MAX_BLOCKS = 64;        // scan blocks up to which it is used
 
-__device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
+#include "sort_network.h"
 
 __device__ __forceinline__ uint64_t lanes_below() {
   const int l = lane_id();
   return l == 0 ? 0ull : (~0ull >> (64 - l));
 }
 
-// ---------------------------------------------------------------- wavefront sorting network
-// Ascending bitonic sort of 64 K values, element e * 64 + lane in v[e], by lane moves on the
-// vector units. The kernels that use it are bound by its instructions, so each compare and
-// exchange is written to need as few as possible (two at most distances):
-//   * the element a lane keeps, the smaller or the larger of its own and its partner's, is
-//     the median of the two and a bound (0 or ~0) that is constant per lane and distance;
-//   * the first stage of a level up to 16 compares with the mirrored lane (i ^ (k - 1)), which
-//     leaves both halves ascending, so no stage needs a direction;
-//   * larger levels take their descending halves as complemented values sorted ascending;
-//   * lane ^ 1, ^ 2, ^ 3 are quad permutations, ^ 7 and ^ 15 the mirrors of half rows and rows,
-//     ^ 8 the rotation of a row by 8, ^ 4 two moves (^ 7, ^ 3); for ^ 16 and ^ 32 the gfx950 row
-//     swap of two copies of the value leaves own and partner's value in the pair, in either
-//     order, which is all the median needs.
-__device__ __forceinline__ uint32_t med3(uint32_t x, uint32_t y, uint32_t z) {
-  const uint32_t lo = x < y ? x : y, hi = x < y ? y : x;
-  const uint32_t m = hi < z ? hi : z;
-  return lo < m ? m : lo;
-}
-
-template <int CTRL>
-__device__ __forceinline__ uint32_t dpp_mov(uint32_t v) {
-  return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xF, 0xF, true);
-}
-
-// Bound of the compare and exchange whose upper elements are the lanes with bit J set.
-template <int J>
-__device__ __forceinline__ uint32_t bound() {
-  return (lane_id() & J) ? ~0u : 0u;
-}
-
-// Compare and exchange with lane ^ X; the lanes with bit UP set keep the larger value.
-template <int X, int UP>
-__device__ __forceinline__ uint32_t exchange(uint32_t v) {
-  if constexpr (X == 16) {
-    const auto p = __builtin_amdgcn_permlane16_swap(v, v, false, false);
-    return med3(p[0], p[1], bound<UP>());
-  } else if constexpr (X == 32) {
-    const auto p = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-    return med3(p[0], p[1], bound<UP>());
-  } else {
-    uint32_t o;
-    if constexpr (X == 1) o = dpp_mov<0xB1>(v);
-    if constexpr (X == 2) o = dpp_mov<0x4E>(v);
-    if constexpr (X == 3) o = dpp_mov<0x1B>(v);
-    if constexpr (X == 4) o = dpp_mov<0x1B>(dpp_mov<0x141>(v));
-    if constexpr (X == 7) o = dpp_mov<0x141>(v);
-    if constexpr (X == 8) o = dpp_mov<0x128>(v);
-    if constexpr (X == 15) o = dpp_mov<0x140>(v);
-    return med3(v, o, bound<UP>());
-  }
-}
-
-template <int X, int UP, int K>
-__device__ __forceinline__ void exchange_all(uint32_t (&v)[K]) {
-#pragma unroll
-  for (int e = 0; e < K; ++e) v[e] = exchange<X, UP>(v[e]);
-}
-
-// Half-cleaners of distances J, J / 2, ..., 1 across the lanes.
-template <int J, int K>
-__device__ __forceinline__ void clean(uint32_t (&v)[K]) {
-  exchange_all<J, J>(v);
-  if constexpr (J > 1) clean<J / 2>(v);
-}
-
-// Each of K independent registers ascending across its 64 lanes (together, so that one's lane
-// moves fill the wait states of the other's).
-template <int K>
-__device__ __forceinline__ void wave_sort_each(uint32_t (&v)[K]) {
-  const uint32_t b16 = bound<16>(), b32 = bound<32>();
-  // descending runs as complements: of 16 (bit 4) and of 32 (bit 5)
-#pragma unroll
-  for (int e = 0; e < K; ++e) v[e] ^= b16 ^ b32;
-  exchange_all<1, 1>(v);
-  exchange_all<3, 2>(v);
-  clean<1>(v);
-  exchange_all<7, 4>(v);
-  clean<2>(v);
-  exchange_all<15, 8>(v);
-  clean<4>(v);
-#pragma unroll
-  for (int e = 0; e < K; ++e) v[e] ^= b16;
-  clean<16>(v);
-#pragma unroll
-  for (int e = 0; e < K; ++e) v[e] ^= b32;
-  clean<32>(v);
-}
-
-// The 64 K values of K registers ascending, element e * 64 + lane in v[e].
-template <int K>
-__device__ __forceinline__ void wave_sort(uint32_t (&v)[K]) {
-  static_assert(K == 1 || K == 2 || K == 4, "64, 128 or 256 values");
-  // descending runs as complements: of 64 (odd e) and of 128 (e & 2); e = 3 is both
-  if constexpr (K >= 2) v[1] = ~v[1];
-  if constexpr (K == 4) v[2] = ~v[2];
-  wave_sort_each<K>(v);
-  if constexpr (K >= 2) {
-#pragma unroll
-    for (int e = 1; e < K; e += 2) v[e] = ~v[e];
-#pragma unroll
-    for (int e = 0; e < K; e += 2) {
-      const uint32_t x = v[e], y = v[e + 1];
-      v[e] = x < y ? x : y;
-      v[e + 1] = x < y ? y : x;
-    }
-    clean<32>(v);
-  }
-  if constexpr (K == 4) {
-#pragma unroll
-    for (int e = 2; e < 4; ++e) v[e] = ~v[e];
-#pragma unroll
-    for (int d = 2; d >= 1; --d)
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if ((e & d) == 0) {
-          const uint32_t x = v[e], y = v[e + d];
-          v[e] = x < y ? x : y;
-          v[e + d] = x < y ? y : x;
-        }
-    clean<32>(v);
-  }
+__global__ void fill_u32_kernel(uint32_t* __restrict__ p, size_t n, uint32_t v) {
+  for (size_t i = (size_t)blockIdx.x * TB + threadIdx.x; i < n; i += (size_t)gridDim.x * TB)
+    p[i] = v;
 }
 
 // ---------------------------------------------------------------- 1. counts
-// The 64 (row, lane) pairs of a wavefront sorted by a bitonic network across lanes, so that
-// equal rows form runs: the first lane of each run then issues one atomic for the whole run,
-// all runs at once (instead of one round trip per distinct row). Rows must be <= 2^25 (the
-// caller checks), so that no entry equals the end marker ~0 that lanes past the end carry.
-// Runs of equal rows among the sorted (row << 6 | lane) values: for each lane the row, the
-// first lane of its run and the run's length (valid only for real entries).
-struct WaveRuns {
-  uint32_t row;
-  int head, len;
-  bool ok;
-};
-
-__device__ __forceinline__ WaveRuns wave_runs(uint32_t sorted) {
-  const int lane = lane_id();
-  WaveRuns w;
-  w.ok = sorted != ~0u;
-  w.row = sorted >> 6;
-  const uint32_t prev = __shfl_up(w.row, 1, 64);
-  const bool head = w.ok && (lane == 0 || prev != w.row);
-  const uint64_t heads = __ballot(head);
-  const uint64_t valid = __ballot(w.ok);
-  const uint64_t upto = lane == 63 ? ~0ull : ((2ull << lane) - 1ull);  // lanes 0..lane
-  w.head = 63 - __clzll((long long)(heads & upto));
-  const uint64_t after = heads & ~upto;  // heads above this lane
-  const int end = after ? __ffsll((unsigned long long)after) - 1 : __popcll(valid);
-  w.len = end - w.head;
-  return w;
-}
-
 // Particles are visited in `order` (a permutation of the ids, nullable: id order). The
 // previous step's sorted order groups particles by their old cell, and a particle moves
 // about a cell per step, so a wavefront of it falls in one or two new rows.
@@ -211,30 +64,8 @@ __device__ __forceinline__ int group_base(int q) {
   return ((blockIdx.x * (TB / 64) + (threadIdx.x >> 6)) * GROUPS + q) * 64;
 }
 
-__global__ __launch_bounds__(TB) void row_count_kernel(const uint32_t* __restrict__ keys,
-                                                       const uint32_t* __restrict__ order, int n,
-                                                       int shift, uint32_t* __restrict__ cnt) {
-  const int lane = lane_id();
-  uint32_t id[GROUPS], v[GROUPS];
-#pragma unroll
-  for (int q = 0; q < GROUPS; ++q) {
-    const int g = group_base(q) + lane;
-    id[q] = g < n ? visit(order, g) : 0u;
-  }
-#pragma unroll
-  for (int q = 0; q < GROUPS; ++q) {
-    const int g = group_base(q) + lane;
-    v[q] = g < n ? ((keys[id[q]] >> shift) << 6) | (uint32_t)lane : ~0u;
-  }
-  wave_sort_each<GROUPS>(v);
-#pragma unroll
-  for (int q = 0; q < GROUPS; ++q) {
-    const WaveRuns w = wave_runs(v[q]);
-    if (w.ok && w.head == lane) atomicAdd(&cnt[w.row], (uint32_t)w.len);
-  }
-}
-
-// The same with one round trip per distinct row (any number of rows).
+// Counts with one round trip per distinct row (any number of rows); packed row numbers are
+// counted by the kernels that write the keys.
 __global__ __launch_bounds__(TB) void row_count_loop_kernel(const uint32_t* __restrict__ keys,
                                                             const uint32_t* __restrict__ order,
                                                             int n, int shift,
@@ -487,6 +318,8 @@ struct RowSortArgs {
   size_t rows;
   int long_blocks;     // workgroups at the start of the grid that take the long rows
   int block_rows;      // rows such a workgroup tests per step (<= TB)
+  uint32_t* clear;     // counters to clear for the next sort (nullable)
+  size_t n_clear;
 };
 
 // Writes one sorted entry at sorted position pos of row `row`, with its payload
@@ -752,6 +585,10 @@ __global__ __launch_bounds__(TB) void row_sort_kernel(RowSortArgs a) {
   __shared__ uint32_t s[BLOCK_ROW_MAX];
   __shared__ uint32_t found[TB];
   __shared__ int nfound;
+  if (a.clear)
+    for (size_t i = (size_t)blockIdx.x * TB + threadIdx.x; i < a.n_clear;
+         i += (size_t)gridDim.x * TB)
+      a.clear[i] = 0u;
   if ((int)blockIdx.x < a.long_blocks) {
     sort_long_rows(a, s, found, &nfound);
     return;
@@ -782,24 +619,38 @@ int cell_sort_split(int n, size_t rows, int shift) {
 size_t cell_sort_scratch_bytes(int n, size_t rows, int shift) {
   const size_t segs = rows << cell_sort_split(n, rows, shift);
   const size_t nb = (segs + SCAN_TILE - 1) / SCAN_TILE;
-  // counts, cursors, segment starts, scan partials, buckets, radix scratch (hi, lo)
+  // counts (of callers without counters of their own), cursors, segment starts, scan
+  // partials, buckets, radix scratch (hi, lo)
   return (3 * segs + 1 + nb + 64 + 3 * (size_t)n) * sizeof(uint32_t) + 4 * 256;
 }
 
-SortClear cell_sort_clear(void* scratch, int n, size_t rows, int shift) {
-  return SortClear{(uint32_t*)scratch, rows << cell_sort_split(n, rows, shift)};
+size_t cell_sort_segments(int n, size_t rows, int shift) {
+  return rows << cell_sort_split(n, rows, shift);
+}
+
+bool cell_sort_packed(int n, size_t rows, int shift) {
+  return cell_sort_segments(n, rows, shift) <= ((size_t)1 << 25);
+}
+
+SortCount sort_count(uint32_t* cnt, int n, size_t rows, int shift) {
+  return SortCount{cnt, shift - cell_sort_split(n, rows, shift)};
+}
+
+void launch_sort_clear(uint32_t* cnt, size_t n, hipStream_t s) {
+  const size_t b = (n + TB * 8 - 1) / (TB * 8);
+  fill_u32_kernel<<<(int)(b < 1 ? 1 : b > 1024 ? 1024 : b), TB, 0, s>>>(cnt, n, 0u);
 }
 
 void launch_cell_sort(const uint32_t* keys, const uint32_t* order, int n, int shift,
                       size_t rows, uint32_t* keys_sorted, uint32_t* ids_sorted,
-                      uint32_t* row_start, void* scratch, const Vec3* pay_in, Vec3* pay_out,
-                      uint32_t* inv, hipStream_t s) {
+                      uint32_t* row_start, uint32_t* cnt, bool counted, size_t n_clear,
+                      void* scratch, const Vec3* pay_in, Vec3* pay_out, uint32_t* inv,
+                      hipStream_t s) {
   const int split = cell_sort_split(n, rows, shift);
   const int sshift = shift - split;  // key >> sshift = segment
   const size_t segs = rows << split;
   const size_t nb = (segs + SCAN_TILE - 1) / SCAN_TILE;
-  uint32_t* cnt = (uint32_t*)scratch;  // zero: cleared by the kernel that wrote the keys
-  uint32_t* cursor = cnt + segs;
+  uint32_t* cursor = (uint32_t*)scratch;
   uint32_t* seg_start = cursor + segs;
   uint32_t* partial = seg_start + segs + 4;
   uint32_t* bucket = partial + nb + 64;
@@ -809,16 +660,14 @@ void launch_cell_sort(const uint32_t* keys, const uint32_t* order, int n, int sh
   while (((size_t)1 << idbits) < (size_t)n) ++idbits;  // at most 31: n is an int
   // (segment << 6 | lane) fits 32 bits below the end marker ~0 for the wavefront sort of
   // the segment numbers
-  const bool packed = segs <= ((size_t)1 << 25);
-  if (packed)
-    row_count_kernel<<<grid_for(n, TB * GROUPS), TB, 0, s>>>(keys, order, n, sshift, cnt);
-  else
+  const bool packed = cell_sort_packed(n, rows, shift);
+  if (!counted)
     row_count_loop_kernel<<<grid_for(n, TB), TB, 0, s>>>(keys, order, n, sshift, cnt);
   // The one-launch scan reads every count before a tile, so its last workgroup's share grows
   // with the tiles, while three launches cost ~18-20 us up to there: 5.3 us at 8 tiles (128^3
   // particles), 9.2 at 32 (4 items of them), 14 at 64 (512^2 segments). It needs the counts on
   // 16 bytes.
-  if (nb <= SCAN1_MAX_BLOCKS && ((uintptr_t)scratch & 15) == 0) {
+  if (nb <= SCAN1_MAX_BLOCKS && (((uintptr_t)scratch | (uintptr_t)cnt) & 15) == 0) {
     scan_one_kernel<<<(int)nb, SCAN1_TB, 0, s>>>(cnt, segs, (uint32_t)n, row_start, cursor,
                                                  seg_start, split);
   } else {
@@ -846,6 +695,8 @@ void launch_cell_sort(const uint32_t* keys, const uint32_t* order, int n, int sh
   a.shift = sshift;
   a.idbits = idbits;
   a.rows = segs;
+  a.clear = n_clear ? cnt : nullptr;
+  a.n_clear = n_clear;
   // rows tested per workgroup step of the long tier: TB, halved (down to 32) while that leaves
   // workgroups of it without rows, so that the long rows spread over the chip
   a.block_rows = TB;
