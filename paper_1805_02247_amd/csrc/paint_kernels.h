@@ -41,24 +41,103 @@ __device__ __forceinline__ void seg_step(float (&v)[NV], uint32_t key) {
   }
 }
 
-// Only the steps the chunk needs run (wave-uniform): with eq = lanes whose key equals the
-// previous lane's, the longest run of set bits bounds the within-row shifts, and the
-// row-crossing steps run only when a segment crosses lane 16/48 or 32.
+// The same step for finite values in one instruction per value: v = t * m + v with m = 1 where
+// the source lane is in my segment and 0 elsewhere, the lane move being the operand's. With
+// m = 1 the product is exact, so the sum rounds as the plain addition does; with m = 0 a finite
+// v is unchanged (a -0 may become +0, which no sum that starts at +0 can tell apart). The
+// paints are bound by their vector instructions, half of which these steps were: with them, the
+// branch-free loads and the lane masks in scalar registers a chunk of 3 channels went from
+// about 250 to 165, and a launch (us, before -> now) from 54.9 to 43.4 (3 channels) and 35.8 to
+// 28.1 (1) at 128^3, 156 to 145 and 82 to 69 at 64^3 x 32, 836 to 803 and 308 to 291 for 256^3 on
+// 512^3; unfused, 57 to 33 at 128^3, 113 to 77 at 64^3 x 32 and 318 to 167 at 256^3.
+// The compiler does not see into the block, so the wait states between a vector write and a
+// lane move's read of it stand in it. Rows out of RMASK keep v.
+template <int CTRL>
+__device__ __forceinline__ void fma_move4(float& a, float& b, float& c, float& d, float m) {
+#define PMR_FMA_MOVE4(MOVE)                               \
+  asm volatile("s_nop 1\n\t"                              \
+               "v_fmac_f32_dpp %0, %0, %4 " MOVE "\n\t"   \
+               "v_fmac_f32_dpp %1, %1, %4 " MOVE "\n\t"   \
+               "v_fmac_f32_dpp %2, %2, %4 " MOVE "\n\t"   \
+               "v_fmac_f32_dpp %3, %3, %4 " MOVE          \
+               : "+v"(a), "+v"(b), "+v"(c), "+v"(d)       \
+               : "v"(m))
+  if constexpr (CTRL == 0x111) PMR_FMA_MOVE4("row_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:0");
+  if constexpr (CTRL == 0x112) PMR_FMA_MOVE4("row_shr:2 row_mask:0xf bank_mask:0xf bound_ctrl:0");
+  if constexpr (CTRL == 0x114) PMR_FMA_MOVE4("row_shr:4 row_mask:0xf bank_mask:0xf bound_ctrl:0");
+  if constexpr (CTRL == 0x118) PMR_FMA_MOVE4("row_shr:8 row_mask:0xf bank_mask:0xf bound_ctrl:0");
+  if constexpr (CTRL == 0x142) PMR_FMA_MOVE4("row_bcast:15 row_mask:0xa bank_mask:0xf");
+  if constexpr (CTRL == 0x143) PMR_FMA_MOVE4("row_bcast:31 row_mask:0xc bank_mask:0xf");
+#undef PMR_FMA_MOVE4
+}
+
+// (A lane without a source reads key 0 and value 0, which it may add; a row out of the move's
+// mask may compare anything.)
+template <int NV, int CTRL>
+__device__ __forceinline__ void seg_step_fma(float (&v)[NV], uint32_t key) {
+  const uint32_t ks = (uint32_t)__builtin_amdgcn_mov_dpp((int)key, CTRL, 0xF, 0xF, true);
+  const float m = ks == key ? 1.f : 0.f;
+  static_assert(NV % 2 == 0, "");
+#pragma unroll
+  for (int q = 0; q + 4 <= NV; q += 4) fma_move4<CTRL>(v[q], v[q + 1], v[q + 2], v[q + 3], m);
+  if constexpr (NV % 4 == 2) {
+    float p0 = 0.f, p1 = 0.f;
+    fma_move4<CTRL>(v[NV - 2], v[NV - 1], p0, p1, m);
+  }
+}
+
+// Only the steps the chunk needs run (wave-uniform): bit i of eq says that lane i has the key
+// of lane i - 1. A shift by k inside the rows adds something only where k such bits follow one
+// another within a row; the row-crossing steps only where a segment crosses lane 16/48 or 32.
+template <int NV, bool FMA>
+__device__ __forceinline__ void seg_scan_steps(float (&v)[NV], uint32_t key, uint64_t eq) {
+#define PMR_SEG_STEP(CTRL, RMASK)              \
+  do {                                         \
+    if constexpr (FMA)                         \
+      seg_step_fma<NV, CTRL>(v, key);          \
+    else                                       \
+      seg_step<NV, CTRL, RMASK>(v, key);       \
+  } while (0)
+  const uint64_t r1 = eq & 0xFFFEFFFEFFFEFFFEull;
+  if (r1) {
+    PMR_SEG_STEP(0x111, 0xF);  // row_shr:1
+    const uint64_t r2 = r1 & (r1 >> 1);
+    if (r2) {
+      PMR_SEG_STEP(0x112, 0xF);  // row_shr:2
+      const uint64_t r4 = r2 & (r2 >> 2);
+      if (r4) {
+        PMR_SEG_STEP(0x114, 0xF);                      // row_shr:4
+        if (r4 & (r4 >> 4)) PMR_SEG_STEP(0x118, 0xF);  // row_shr:8
+      }
+    }
+  }
+  if (eq & ((1ull << 16) | (1ull << 48))) PMR_SEG_STEP(0x142, 0xA);  // row_bcast:15
+  if (eq & (1ull << 32)) PMR_SEG_STEP(0x143, 0xC);                   // row_bcast:31
+#undef PMR_SEG_STEP
+}
+
+// Scans v over the runs of equal keys and returns the lanes, of those in `ok`, that end a run
+// (two valid lanes only ever share a key with valid lanes between them). `tame`: this lane's
+// values and all sums of up to 64 like them are finite.
 template <int NV>
-__device__ __forceinline__ void seg_scan(float (&v)[NV], uint32_t key) {
+__device__ __forceinline__ uint64_t seg_scan(float (&v)[NV], uint32_t key, uint64_t ok,
+                                             bool tame) {
   // wave_shr:1
   const uint32_t kp = (uint32_t)__builtin_amdgcn_mov_dpp((int)key, 0x138, 0xF, 0xF, true);
-  const int lane = threadIdx.x & 63;
-  const uint64_t eq = __ballot(lane > 0 && kp == key);
-  if (eq == 0) return;
-  int run = 0;  // longest run of ones in eq
-  for (uint64_t m = eq; m; m &= (m >> 1)) ++run;
-  seg_step<NV, 0x111, 0xF>(v, key);                       // row_shr:1
-  if (run >= 2) seg_step<NV, 0x112, 0xF>(v, key);         // row_shr:2
-  if (run >= 4) seg_step<NV, 0x114, 0xF>(v, key);         // row_shr:4
-  if (run >= 8) seg_step<NV, 0x118, 0xF>(v, key);         // row_shr:8
-  if (eq & ((1ull << 16) | (1ull << 48))) seg_step<NV, 0x142, 0xA>(v, key);  // row_bcast:15
-  if (eq & (1ull << 32)) seg_step<NV, 0x143, 0xC>(v, key);  // row_bcast:31
+  const uint64_t eq = __ballot(kp == key) & ~1ull;
+  if (eq != 0) {
+    uint64_t wild = __ballot(!tame);
+    if (wild == 0) seg_scan_steps<NV, true>(v, key, eq);
+    asm volatile("" : "+s"(wild));  // two branches, not two arms: both scan v in place
+    if (wild != 0) {
+      if (!__builtin_amdgcn_inverse_ballot_w64(ok)) {
+#pragma unroll
+        for (int q = 0; q < NV; ++q) v[q] = 0.f;  // (0 times a neighbour's NaN)
+      }
+      seg_scan_steps<NV, false>(v, key, eq);
+    }
+  }
+  return ok & ~(eq >> 1);
 }
 
 // The streams of one 64-particle chunk as they come from memory (one lane's particle).
@@ -67,25 +146,45 @@ struct RawChunk {
   uint32_t key;
   Vec3 f;
   Vec3 u;  // C = 3
-  bool ok;
+  uint64_t ok;  // lanes with a particle of the run (uniform)
 };
 
-// Particles c0 .. c0 + 63 of the sorted stream, those in [beg, end) only.
+// Particles c0 .. c0 + 63 of the sorted stream, those in [beg, end) only (at least one). The
+// other lanes read the run's first or last particle of the chunk, so that the loads need no
+// branch and, from a uniform base, no 64-bit address per lane; the weights drop them.
 template <int C>
 __device__ __forceinline__ RawChunk<C> load_raw(const PaintArgs& a, uint32_t c0, uint32_t beg,
                                                 uint32_t end) {
-  const uint32_t j = c0 + (threadIdx.x & 63);
+  const uint32_t lane = threadIdx.x & 63;
+  const uint32_t lo = beg > c0 ? beg - c0 : 0u;
+  const uint32_t hi = (end - c0 < 64u ? end - c0 : 64u) - 1u;
+  const uint32_t l = lane < lo ? lo : lane > hi ? hi : lane;
   RawChunk<C> r;
-  r.ok = j >= beg && j < end;
-  r.key = 0u;
-  r.f = Vec3{0.f, 0.f, 0.f};
+  r.ok = (~0ull << lo) & (~0ull >> (63u - hi));
+  r.key = (a.keys + c0)[l];
+  r.f = (a.frac + c0)[l];
   r.u = Vec3{0.f, 0.f, 0.f};
-  if (r.ok) {
-    r.key = a.keys[j];
-    r.f = a.frac[j];
-    if constexpr (C == 3) r.u = a.val[j];
-  }
+  if constexpr (C == 3) r.u = (a.val + c0)[l];
   return r;
+}
+
+// The C values of a lane's particle times its x weight, 0 on lanes without one, and whether
+// sums of 64 such values times further weights stay finite.
+template <int C>
+__device__ __forceinline__ bool chunk_values(const PaintArgs& a, const RawChunk<C>& r, int ox,
+                                             bool ok, float (&val)[C]) {
+  const float wx = ox ? r.f.x : 1.f - r.f.x;
+  float mag = r.f.y + r.f.z;  // in [0, 2], or NaN
+  if constexpr (C == 1) {
+    val[0] = (ok ? a.mass : 0.f) * wx;
+  } else {
+    val[0] = (ok ? r.u.x : 0.f) * wx;
+    val[1] = (ok ? r.u.y : 0.f) * wx;
+    val[2] = (ok ? r.u.z : 0.f) * wx;
+  }
+#pragma unroll
+  for (int c = 0; c < C; ++c) mag += fabsf(val[c]);
+  return mag < 0x1p120f;
 }
 
 // One 64-particle chunk of a source run: per lane the four (oy, oz) weights of each channel.
@@ -93,7 +192,8 @@ template <int C>
 struct Chunk {
   uint32_t key;
   int sy, iz;
-  bool ok;
+  uint64_t ok;
+  bool tame;
   float v[4 * C];
 };
 
@@ -102,35 +202,21 @@ __device__ __forceinline__ void weigh_chunk(const PaintArgs& a, const RawChunk<C
                                             Chunk<C>& ch) {
   const int lane = threadIdx.x & 63;
   const int nm = a.nm;
+  const bool ok = __builtin_amdgcn_inverse_ballot_w64(r.ok);
+  const Vec3 f = r.f;
   ch.ok = r.ok;
-  ch.key = 0xffffffffu - lane;  // never equal across lanes when invalid
-  ch.sy = 0;
-  ch.iz = 0;
+  ch.key = ok ? r.key : 0xffffffffu - lane;  // never equal across lanes when invalid
+  ch.iz = (int)(r.key & (uint32_t)(nm - 1));
+  ch.sy = (int)((r.key >> a.log_nm) & (uint32_t)(nm - 1));
+  float val[C];
+  ch.tame = chunk_values<C>(a, r, ox, ok, val);
+  const float wy0 = 1.f - f.y, wy1 = f.y, wz0 = 1.f - f.z, wz1 = f.z;
 #pragma unroll
-  for (int q = 0; q < 4 * C; ++q) ch.v[q] = 0.f;
-  if (ch.ok) {
-    const uint32_t key = r.key;
-    const Vec3 f = r.f;
-    ch.key = key;
-    ch.iz = (int)(key & (uint32_t)(nm - 1));
-    ch.sy = (int)((key >> a.log_nm) & (uint32_t)(nm - 1));
-    const float wx = ox ? f.x : 1.f - f.x;
-    float val[C];
-    if constexpr (C == 1) {
-      val[0] = a.mass * wx;
-    } else {
-      val[0] = r.u.x * wx;
-      val[1] = r.u.y * wx;
-      val[2] = r.u.z * wx;
-    }
-    const float wy0 = 1.f - f.y, wy1 = f.y, wz0 = 1.f - f.z, wz1 = f.z;
-#pragma unroll
-    for (int c = 0; c < C; ++c) {
-      ch.v[4 * c + 0] = val[c] * wy0 * wz0;
-      ch.v[4 * c + 1] = val[c] * wy0 * wz1;
-      ch.v[4 * c + 2] = val[c] * wy1 * wz0;
-      ch.v[4 * c + 3] = val[c] * wy1 * wz1;
-    }
+  for (int c = 0; c < C; ++c) {
+    ch.v[4 * c + 0] = val[c] * wy0 * wz0;
+    ch.v[4 * c + 1] = val[c] * wy0 * wz1;
+    ch.v[4 * c + 2] = val[c] * wy1 * wz0;
+    ch.v[4 * c + 3] = val[c] * wy1 * wz1;
   }
 }
 
@@ -150,28 +236,24 @@ __device__ __forceinline__ void weigh_chunk(const PaintArgs& a, const RawChunk<C
 template <bool PAD>
 __device__ __forceinline__ int row_slot(int iz) {
   if constexpr (PAD) {
-    const int k = iz >> 1;
-    return 2 * (k + (k >> 5)) + (iz & 1);
+    return iz + 2 * (iz >> 6);
   }
   return iz;
 }
 
-// acc rows: [TY][C] rows of rp floats each.
+// acc rows: [TY][C] rows of rp floats each; tails: the lanes that end a run.
 template <int C, int TY, bool PAD = false>
-__device__ __forceinline__ void deposit(const Chunk<C>& ch, float* acc, int nm, int iy0, int rp) {
-  const int lane = threadIdx.x & 63;
-  // wave_shl:1
-  const uint32_t kn = (uint32_t)__builtin_amdgcn_mov_dpp((int)ch.key, 0x130, 0xF, 0xF, true);
-  const int ok_next = __builtin_amdgcn_mov_dpp((int)ch.ok, 0x130, 0xF, 0xF, true);
-  const bool tail = ch.ok && (lane == 63 || !ok_next || kn != ch.key);
-  const int iz1 = (ch.iz + 1) & (nm - 1);
+__device__ __forceinline__ void deposit(const Chunk<C>& ch, uint64_t tails, float* acc, int nm,
+                                        int iy0, int rp) {
+  const bool tail = __builtin_amdgcn_inverse_ballot_w64(tails);
+  const int slot[2] = {row_slot<PAD>(ch.iz), row_slot<PAD>((ch.iz + 1) & (nm - 1))};
 #pragma unroll
   for (int ph = 0; ph < 4; ++ph) {
     const int oy = ph >> 1, oz = ph & 1;
-    const int jt = ((ch.sy + oy) & (nm - 1)) - iy0;
+    const uint32_t jt = (uint32_t)(((ch.sy + oy) & (nm - 1)) - iy0);
     PMR_PHASE_FENCE();
-    if (tail && jt >= 0 && jt < TY) {
-      float* row = acc + (size_t)jt * C * rp + row_slot<PAD>(oz ? iz1 : ch.iz);
+    if (tail && jt < (uint32_t)TY) {
+      float* row = acc + __umul24(jt, C * rp) + slot[oz];
 #pragma unroll
       for (int c = 0; c < C; ++c) row[c * rp] = row[c * rp] + ch.v[4 * c + 2 * oy + oz];
     }
@@ -188,7 +270,8 @@ template <int C>
 struct Chunk1 {
   uint32_t key;
   int iz, oy;
-  bool ok;
+  uint64_t ok;
+  bool tame;
   float v[2 * C];
 };
 
@@ -197,51 +280,33 @@ __device__ __forceinline__ void weigh_chunk1(const PaintArgs& a, const RawChunk<
                                              int iy0, Chunk1<C>& ch) {
   const int lane = threadIdx.x & 63;
   const int nm = a.nm;
+  const bool ok = __builtin_amdgcn_inverse_ballot_w64(r.ok);
+  const Vec3 f = r.f;
   ch.ok = r.ok;
-  ch.key = 0xffffffffu - lane;  // never equal across lanes when invalid
-  ch.iz = 0;
-  ch.oy = 0;
+  ch.key = ok ? r.key : 0xffffffffu - lane;  // never equal across lanes when invalid
+  ch.iz = (int)(r.key & (uint32_t)(nm - 1));
+  ch.oy = (int)((r.key >> a.log_nm) & (uint32_t)(nm - 1)) == iy0 ? 0 : 1;
+  float val[C];
+  ch.tame = chunk_values<C>(a, r, ox, ok, val);
+  const float wy = ch.oy ? f.y : 1.f - f.y, wz0 = 1.f - f.z, wz1 = f.z;
 #pragma unroll
-  for (int q = 0; q < 2 * C; ++q) ch.v[q] = 0.f;
-  if (ch.ok) {
-    const uint32_t key = r.key;
-    const Vec3 f = r.f;
-    ch.key = key;
-    ch.iz = (int)(key & (uint32_t)(nm - 1));
-    const int sy = (int)((key >> a.log_nm) & (uint32_t)(nm - 1));
-    ch.oy = sy == iy0 ? 0 : 1;
-    const float wx = ox ? f.x : 1.f - f.x;
-    float val[C];
-    if constexpr (C == 1) {
-      val[0] = a.mass * wx;
-    } else {
-      val[0] = r.u.x * wx;
-      val[1] = r.u.y * wx;
-      val[2] = r.u.z * wx;
-    }
-    const float wy = ch.oy ? f.y : 1.f - f.y, wz0 = 1.f - f.z, wz1 = f.z;
-#pragma unroll
-    for (int c = 0; c < C; ++c) {
-      ch.v[2 * c + 0] = val[c] * wy * wz0;
-      ch.v[2 * c + 1] = val[c] * wy * wz1;
-    }
+  for (int c = 0; c < C; ++c) {
+    ch.v[2 * c + 0] = val[c] * wy * wz0;
+    ch.v[2 * c + 1] = val[c] * wy * wz1;
   }
 }
 
 template <int C, bool PAD = false>
-__device__ __forceinline__ void deposit1(const Chunk1<C>& ch, float* acc, int nm, int rp) {
-  const int lane = threadIdx.x & 63;
-  // wave_shl:1
-  const uint32_t kn = (uint32_t)__builtin_amdgcn_mov_dpp((int)ch.key, 0x130, 0xF, 0xF, true);
-  const int ok_next = __builtin_amdgcn_mov_dpp((int)ch.ok, 0x130, 0xF, 0xF, true);
-  const bool tail = ch.ok && (lane == 63 || !ok_next || kn != ch.key);
-  const int iz1 = (ch.iz + 1) & (nm - 1);
+__device__ __forceinline__ void deposit1(const Chunk1<C>& ch, uint64_t tails, float* acc, int nm,
+                                         int rp) {
+  const bool tail = __builtin_amdgcn_inverse_ballot_w64(tails);
+  const int slot[2] = {row_slot<PAD>(ch.iz), row_slot<PAD>((ch.iz + 1) & (nm - 1))};
 #pragma unroll
   for (int ph = 0; ph < 4; ++ph) {
     const int oy = ph >> 1, oz = ph & 1;
     PMR_PHASE_FENCE();
     if (tail && ch.oy == oy) {
-      float* row = acc + row_slot<PAD>(oz ? iz1 : ch.iz);
+      float* row = acc + slot[oz];
 #pragma unroll
       for (int c = 0; c < C; ++c) row[c * rp] = row[c * rp] + ch.v[2 * c + oz];
     }
@@ -318,13 +383,13 @@ __device__ __forceinline__ void paint_rows(const PaintArgs& a, int item, int ix,
     if constexpr (TY == 1) {
       Chunk1<C> ch;
       weigh_chunk1<C>(a, cur, ox, iy0, ch);
-      seg_scan<2 * C>(ch.v, ch.key);
-      deposit1<C, PAD>(ch, acc, nm, rp);
+      const uint64_t tails = seg_scan<2 * C>(ch.v, ch.key, ch.ok, ch.tame);
+      deposit1<C, PAD>(ch, tails, acc, nm, rp);
     } else {
       Chunk<C> ch;
       weigh_chunk<C>(a, cur, ox, ch);
-      seg_scan<4 * C>(ch.v, ch.key);
-      deposit<C, TY, PAD>(ch, acc, nm, iy0, rp);
+      const uint64_t tails = seg_scan<4 * C>(ch.v, ch.key, ch.ok, ch.tame);
+      deposit<C, TY, PAD>(ch, tails, acc, nm, iy0, rp);
     }
   }
 }
