@@ -403,12 +403,17 @@ void paint_r2c(PaintArgs a, int batch, float2* out, FieldMap om, hipStream_t s) 
     if (want == T) a.group = T;
   TYCASE(1) TYCASE(2) TYCASE(4) TYCASE(8) TYCASE(16)
 #undef TYCASE
-  const int ty = paint_share(a.group, (size_t)batch * N * N);
-#define TYCASE(T)                                                  \
-  if constexpr (paint_r2c_ty_ok<N, C, T>())                        \
-    if (ty == T) {                                                 \
-      paint_r2c_launch<C, T, N>(a, batch, out, om, s);             \
-      return;                                                      \
+  int ty = paint_share(a.group, (size_t)batch * N * N);
+  // Three channels hold three times the LDS rows: beyond 2 per wavefront the workgroups that
+  // this keeps off a CU cost more than the chunks that sharing reads twice (128^3 x 4: 152 us
+  // with 4 rows, 143 with 2; shorter rows fit: 64^3 x 32 145 with 4, 147 with 2).
+  constexpr int MOST = C == 3 && N >= 128 ? 2 : 16;
+  if (ty > MOST) ty = MOST;
+#define TYCASE(T)                                                \
+  if constexpr (T <= MOST && paint_r2c_ty_ok<N, C, T>())         \
+    if (ty == T) {                                               \
+      paint_r2c_launch<C, T, N>(a, batch, out, om, s);           \
+      return;                                                    \
     }
   TYCASE(1) TYCASE(2) TYCASE(4) TYCASE(8) TYCASE(16)
 #undef TYCASE
