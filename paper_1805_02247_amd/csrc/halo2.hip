@@ -8,8 +8,10 @@
 //   mass = pos * m.
 // Adjoint (weights frozen): with Mbar the mass adjoint, ybar = Mbar m a pos (1 - pos) and
 // mbar = Mbar pos are pushed back through the layers; the position network's input adjoint
-// u (81 per voxel) belongs to the neighbours, so it is written out and a second kernel sums,
-// for each voxel, the 27 entries that point at it: fbar_c(y) = sum_o u_{c,o}(y - d_o).
+// u (81 per voxel) belongs to the neighbours, fbar_c(y) = sum_o u_{c,o}(y - d_o). A wavefront
+// holds u of 16 voxels along z, so it sums the three z offsets itself and writes 27 values per
+// voxel (and what belongs to the voxels on either side of the 16); a second kernel sums, for
+// each voxel, the nine (x, y) offsets.
 //
 // The position network's four products (forward 81 -> 50 -> 30, adjoint 30 -> 50 -> 81) run
 // on the matrix cores in FP32; the forward keeps pos and the ReLU signs for the adjoint, so
@@ -24,6 +26,7 @@ namespace {
 
 constexpr int TB = 256;
 constexpr int NP1 = 50, NP2 = 30, NF = 81, NM1 = 20, NM2 = 10;
+constexpr int NT = HALO2_TRIPLES;  // (field, x offset, y offset)
 
 // Prepared weight block (floats): the position network's biases and output row, the mass
 // network, then the matrix-core operand fragments of the position network's four products
@@ -62,6 +65,15 @@ static_assert(H2::SIZE == HALO2_WEIGHT_FLOATS, "prepared weight block size");
 // tiles, K 64); adjoint (3) a1bar = W2^T a2bar (4 tiles, K 32); (4) u = W1^T a1bar (81 -> 6
 // tiles, K 64). Padding rows and columns are zero in the fragments.
 __host__ __device__ constexpr int mx_slot(int kb, int g) { return 16 * (kb >> 2) + 4 * g + (kb & 3); }
+
+// Feature of row r of tile mt of product (4), NF and beyond: none. Lane group g = r / 4 holds
+// rows 4 g + i of each tile: 24 slots 4 mt + i, which take the three z offsets of its triples
+// (field, x offset, y offset) p = 4 j + g one after another, so that the sum over z needs moves
+// between neighbouring lanes only. Features are numbered 3 p + (z offset).
+__host__ __device__ constexpr int mx_feature(int mt, int r) {
+  const int s = 4 * mt + (r & 3), p = 4 * (s / 3) + (r >> 2);
+  return p < 27 ? 3 * p + s % 3 : NF;
+}
 
 // Packed user blocks -> prepared block (zero padding).
 __global__ void halo2_prepare_kernel(const float* __restrict__ nnp, const float* __restrict__ nnm,
@@ -110,8 +122,8 @@ __global__ void halo2_prepare_kernel(const float* __restrict__ nnp, const float*
       if (m < NP1 && k < NP2) v = nnp[pW2 + k * NP1 + m];
     } else if (i >= H2::F4) {
       const int e = i - H2::F4, l = e & 63, kb = (e >> 6) % 16, mt = (e >> 6) / 16;
-      const int m = 16 * mt + (l & 15), k = mx_slot(kb, l >> 4);  // m: feature, k: layer-1
-      if (m < NF && k < NP1) v = nnp[pW1 + k * NF + m];
+      const int f = mx_feature(mt, l & 15), k = mx_slot(kb, l >> 4);  // k: layer-1
+      if (f < NF && k < NP1) v = nnp[pW1 + k * NF + f];
     }
     w[i] = v;
   }
@@ -209,26 +221,50 @@ __global__ __launch_bounds__(TB) void halo2_nnm_kernel(const float* __restrict__
   }
 }
 
-// fbar_c(y) = sum_o u_{c,o}(y - d_o), added to (g0, g12, g2).
+// fbar_c(y) = sum_o u_{c,o}(y - d_o), added to (g0, g12, g2), from the sums over z and the
+// edges that halo2_mx_bwd_kernel wrote. A thread takes 4 voxels along z: the first and last
+// thread of a 16-voxel group add the neighbour group's edge to their outer voxel. Bound by the
+// read of U (27 sums and 27 / 8 edges per voxel).
 __global__ __launch_bounds__(TB) void halo2_stencil_adj_kernel(const float* __restrict__ U,
                                                                int log_n, size_t total,
                                                                float* __restrict__ g0,
                                                                float* __restrict__ g12,
                                                                float* __restrict__ g2) {
-  const size_t v = (size_t)blockIdx.x * TB + threadIdx.x;
+  const size_t v = ((size_t)blockIdx.x * TB + threadIdx.x) * 4;
   if (v >= total) return;
+  const float* edges = U + total * NT;
   const Vox p = vox(v, log_n);
-  float s[3] = {0.f, 0.f, 0.f};
+  const int in = p.iz & 15;  // 0, 4, 8, 12
+  const bool first = in == 0, last = in == 12;
+  float4 s[3];
 #pragma unroll
-  for (int o = 0; o < 27; ++o) {
-    const size_t q = nbr(p, log_n, 1 - o / 9, 1 - (o / 3) % 3, 1 - o % 3);
-    const float* uq = U + (q >> 4) * NF * 16 + (q & 15);
+  for (int c = 0; c < 3; ++c) s[c] = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-    for (int c = 0; c < 3; ++c) s[c] += uq[(c * 27 + o) * 16];
+  for (int o = 0; o < 9; ++o) {
+    const int dx = 1 - o / 3, dy = 1 - o % 3;
+    const size_t q = nbr(p, log_n, dx, dy, 0);
+    const float* uq = U + (q >> 4) * (NT * 16) + in;
+    // the group before owes its last voxel's z = +1 entry, the group after its first's z = -1
+    const size_t e = nbr(p, log_n, dx, dy, last ? 4 : -1);
+    const float* eq = edges + (e >> 4) * (NT * 2) + (last ? 0 : 1);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      const float4 t = *reinterpret_cast<const float4*>(uq + (c * 9 + o) * 16);
+      const float b = first || last ? eq[(c * 9 + o) * 2] : 0.f;
+      s[c].x += first ? t.x + b : t.x;
+      s[c].y += t.y;
+      s[c].z += t.z;
+      s[c].w += last ? t.w + b : t.w;
+    }
   }
-  g0[v] += s[0];
-  g12[v] += s[1] + s[2];
-  g2[v] += s[2];
+  float4* h0 = reinterpret_cast<float4*>(g0 + v);
+  float4* h12 = reinterpret_cast<float4*>(g12 + v);
+  float4* h2 = reinterpret_cast<float4*>(g2 + v);
+  const float4 a0 = *h0, a12 = *h12, a2 = *h2;
+  *h0 = make_float4(a0.x + s[0].x, a0.y + s[0].y, a0.z + s[0].z, a0.w + s[0].w);
+  *h12 = make_float4(a12.x + (s[1].x + s[2].x), a12.y + (s[1].y + s[2].y),
+                     a12.z + (s[1].z + s[2].z), a12.w + (s[1].w + s[2].w));
+  *h2 = make_float4(a2.x + s[2].x, a2.y + s[2].y, a2.z + s[2].z, a2.w + s[2].w);
 }
 
 typedef float floatx4_t __attribute__((ext_vector_type(4)));
@@ -339,8 +375,12 @@ __global__ __launch_bounds__(64 * MX_WAVES) void halo2_mx_fwd_kernel(
 }
 
 // Position network, adjoint: from Mbar (mbar), pos and m (aux, aux + total) and the stored
-// ReLU signs, u = W1^T ([a1 > 0] W2^T ([a2 > 0] W3 ybar)) with ybar = Mbar m a pos (1 - pos),
-// written to U [B n^3 / 16][81][16] (per 16-voxel group, feature-major: one 5 KB block).
+// ReLU signs, u = W1^T ([a1 > 0] W2^T ([a2 > 0] W3 ybar)) with ybar = Mbar m a pos (1 - pos).
+// Written to U, per group of 16 voxels along z: for each triple (field, x, y offset) the sums
+// over the z offsets [27][16] and, behind those of all groups, the two entries that belong to
+// the voxels before and after the group [27][2]. (With u itself written, 81 floats per voxel,
+// and gathered by the stencil kernel the two took 342 and 168 us at 128^3; now 315 and 76.
+// The four products alone need about 225 us at the card's FP32 matrix rate.)
 __global__ __launch_bounds__(64 * MX_WAVES) void halo2_mx_bwd_kernel(
     int log_n, size_t groups, size_t total, const float* __restrict__ w,
     const double* __restrict__ prm, const float* __restrict__ mbar,
@@ -396,14 +436,24 @@ __global__ __launch_bounds__(64 * MX_WAVES) void halo2_mx_bwd_kernel(
 #pragma unroll
       for (int mt = 0; mt < 6; ++mt)
         u[mt] = mx(f4g[(mt * 16 + kb) * 64 + l], a1b[kb >> 2][kb & 3], u[mt]);
-    float* uo = U + G * NF * 16 + n;  // [group][feature][16]: one 5 KB block per group
+    float* uo = U + G * (NT * 16) + n;
+    float* eo = U + total * NT + G * (NT * 2) + (n == 0 ? 0 : 1);
 #pragma unroll
-    for (int mt = 0; mt < 6; ++mt)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int f = 16 * mt + 4 * g + i;
-        if (f < NF) uo[f * 16] = u[mt][i];
+    for (int j = 0; j < 7; ++j) {
+      const int t = 4 * j + g;
+      const float up = u[(3 * j) >> 2][(3 * j) & 3];  // for the voxel before
+      const float at = u[(3 * j + 1) >> 2][(3 * j + 1) & 3];
+      const float dn = u[(3 * j + 2) >> 2][(3 * j + 2) & 3];  // for the voxel after
+      // row_shl:1, row_shr:1 over the 16 lanes of a group; beyond its ends 0
+      const float nx = __int_as_float(
+          __builtin_amdgcn_mov_dpp(__float_as_int(up), 0x101, 0xF, 0xF, true));
+      const float pv = __int_as_float(
+          __builtin_amdgcn_mov_dpp(__float_as_int(dn), 0x111, 0xF, 0xF, true));
+      if (t < NT) {
+        uo[t * 16] = nx + at + pv;
+        if (n == 0 || n == 15) eo[t * 2] = n == 0 ? up : dn;
       }
+    }
   }
 }
 
@@ -441,8 +491,8 @@ void launch_halo2_bwd(const float* d0, const float* d1, const float* d2, int log
 
 void launch_halo2_stencil_adj(const float* U, int log_n, size_t total, float* g0, float* g12,
                               float* g2, hipStream_t s) {
-  halo2_stencil_adj_kernel<<<(unsigned)((total + TB - 1) / TB), TB, 0, s>>>(U, log_n, total, g0,
-                                                                            g12, g2);
+  halo2_stencil_adj_kernel<<<(unsigned)((total / 4 + TB - 1) / TB), TB, 0, s>>>(U, log_n, total,
+                                                                                g0, g12, g2);
 }
 
 }  // namespace pmr

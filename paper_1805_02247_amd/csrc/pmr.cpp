@@ -102,7 +102,7 @@ struct pmr_ctx {
   float* net_y;    // single network: output before the softplus [B][no3]
   char* net_sgn;   // and ReLU signs, for its adjoint
   float* halo2_w;  // prepared weights of the two-network model
-  float* u2;       // its position network's input adjoint [B no3 / 16][81][16]
+  float* u2;       // its position network's input adjoint (halo2_u_floats)
   float* h2aux;    // its position mask and mass-network output [2][B][no3]
   uint32_t* h2sgn; // its position network's ReLU signs [B][no3][4]
   float* target;
@@ -226,7 +226,7 @@ void plan(pmr_ctx* c, Plan& P) {
   c->net_sgn = P.take<char>(keep ? (keep - 4) * B * c->no3 : 0);
   const bool two = c->cfg.halo_model == PMR_HALO_TWO;
   c->halo2_w = P.take<float>(two ? HALO2_WEIGHT_FLOATS : 0);
-  c->u2 = P.take<float>(two ? 81 * B * c->no3 : 0);
+  c->u2 = P.take<float>(two ? halo2_u_floats(B * c->no3) : 0);
   c->h2aux = P.take<float>(two ? 2 * B * c->no3 : 0);
   c->h2sgn = P.take<uint32_t>(two ? 4 * B * c->no3 : 0);
   c->target = P.take<float>(B * c->no3);
@@ -1033,8 +1033,8 @@ int pmr_adjoint(pmr_ctx* c, const double* loss_bar, const float* mass_bar, void*
                          c->halo2_w, c->params, o2, c->h2aux, c->h2sgn, c->u2, o0, o1, dbar_f,
                          s);
       }
-      // compulsory: u (81 floats) read, three adjoint fields read and written, per voxel
-      ProfScope ps(c, PMR_PROF_HALO2_STENCIL, (81.0 * 4 + 24.0) * B * no3);
+      // compulsory: u read, three adjoint fields read and written
+      ProfScope ps(c, PMR_PROF_HALO2_STENCIL, 4.0 * halo2_u_floats(B * no3) + 24.0 * B * no3);
       launch_halo2_stencil_adj(c->u2, c->log_no, (size_t)B * no3, o0, o1, dbar_f, s);
     } else {
       const double Hd = c->H;
