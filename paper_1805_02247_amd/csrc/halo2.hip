@@ -275,6 +275,11 @@ __device__ __forceinline__ floatx4_t mx(float a, float b, floatx4_t c) {
 
 constexpr int MX_WAVES = 8;  // wavefronts per workgroup
 
+// x where bit k of bits is set, else 0.
+__device__ __forceinline__ float keep_if(uint32_t bits, int k, float x) {
+  return __int_as_float(__builtin_amdgcn_sbfe((int)bits, k, 1) & __float_as_int(x));
+}
+
 // LDS base address made to depend on `after`, so that the compiler cannot hoist a later
 // product's operand reads above the product that produces `after` (they would all be live
 // at once and spill).
@@ -288,14 +293,16 @@ __device__ __forceinline__ const float* lds_after(const float* base, float after
 // fragments are staged in LDS once per workgroup (29 KB forward, 32 KB adjoint).
 // Position network, forward: pos = logistic(y, a) to aux[v]; the ReLU signs of the lane's
 // 16 layer-1 and 8 layer-2 neurons (C layout) to bits 0..15 and 16..23 of sgn[v][g], for
-// the adjoint.
+// the adjoint. At 128^3 the products alone need 203 us at the card's FP32 matrix rate; the
+// vector work around them shows on top: 292 us with the 7 neighbour addresses formed from
+// coordinates per voxel and branches at the layers' ends, 274 us now.
 __global__ __launch_bounds__(64 * MX_WAVES) void halo2_mx_fwd_kernel(
     const float* __restrict__ d0, const float* __restrict__ d1, const float* __restrict__ d2,
     int log_n, size_t groups, const float* __restrict__ w, const double* __restrict__ prm,
     float* __restrict__ aux, uint32_t* __restrict__ sgn) {
   constexpr int NFRAG = H2::F3 - H2::F1;
   __shared__ __attribute__((aligned(16))) float sf[NFRAG];
-  __shared__ float sv[H2::M1];  // b1, b2, W3, b3: read per lane group, kept close
+  __shared__ __attribute__((aligned(16))) float sv[H2::M1];  // b1, b2, W3, b3
   for (int i = threadIdx.x; i < NFRAG / 4; i += 64 * MX_WAVES)
     reinterpret_cast<float4*>(sf)[i] = reinterpret_cast<const float4*>(w + H2::F1)[i];
   for (int i = threadIdx.x; i < H2::M1; i += 64 * MX_WAVES) sv[i] = w[i];
@@ -303,27 +310,41 @@ __global__ __launch_bounds__(64 * MX_WAVES) void halo2_mx_fwd_kernel(
   const float* f1 = sf;
   const float* f2 = sf + (H2::F2 - H2::F1);
   const int l = threadIdx.x & 63, g = l >> 4, n = l & 15;
+  // Byte offsets within an item, with the bits of (x, z) and of y each in their own sum, so
+  // that both wrap by a mask: a carry out of z lands in a cleared y bit. The lane's 7 offsets
+  // o = 4 kk + g (beyond the 27th: that one again, against zero weights).
+  const uint32_t my = ((1u << log_n) - 1u) << (log_n + 2);
+  const uint32_t mxz = (((1u << (3 * log_n)) - 1u) << 2) & ~my;
+  uint32_t oxz[7], oy[7];
+#pragma unroll
+  for (int kk = 0; kk < 7; ++kk) {
+    const int o = 4 * kk + g < 27 ? 4 * kk + g : 26;
+    oxz[kk] = (((uint32_t)(o / 9 - 1) << (2 * log_n + 2)) & mxz) |
+              (((uint32_t)(o % 3 - 1) & ((1u << log_n) - 1u)) << 2);
+    oy[kk] = ((uint32_t)((o / 3) % 3 - 1) << (log_n + 2)) & my;
+  }
+  const uint32_t w0 = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const size_t stride = (size_t)gridDim.x * MX_WAVES;
-  for (size_t G = (size_t)xcd_block(blockIdx.x, gridDim.x) * MX_WAVES + (threadIdx.x >> 6);
-       G < groups; G += stride) {
+  for (size_t G = (size_t)xcd_block(blockIdx.x, gridDim.x) * MX_WAVES + w0; G < groups;
+       G += stride) {
     const size_t v = G * 16 + n;
-    const Vox p = vox(v, log_n);
-    const size_t item = v >> (3 * log_n);
+    const size_t item = (G * 16) >> (3 * log_n);
+    const size_t base = item << (3 * log_n);
+    const char* p0 = reinterpret_cast<const char*>(d0 + base);
+    const char* p1 = reinterpret_cast<const char*>(d1 + base);
+    const char* p2 = reinterpret_cast<const char*>(d2 + base);
+    const uint32_t l4 = (uint32_t)(G * 16 - base + n) << 2;
+    const uint32_t lxz = l4 & mxz, ly = l4 & my;
     // B operands of layer 1: the three fields at offsets o = 4 kk + g of this lane's voxel
     float xb[21];
 #pragma unroll
     for (int kk = 0; kk < 7; ++kk) {
-      const int o = 4 * kk + g;
-      float x0 = 0.f, x1 = 0.f, x2 = 0.f;
-      if (o < 27) {
-        const size_t q = nbr(p, log_n, o / 9 - 1, (o / 3) % 3 - 1, o % 3 - 1);
-        x0 = d0[q];
-        x1 = d1[q];
-        x2 = x1 - d2[q];
-      }
+      const uint32_t q = ((lxz + oxz[kk]) & mxz) | ((ly + oy[kk]) & my);
+      const float x0 = *reinterpret_cast<const float*>(p0 + q);
+      const float x1 = *reinterpret_cast<const float*>(p1 + q);
       xb[kk] = x0;
       xb[7 + kk] = x1;
-      xb[14 + kk] = x2;
+      xb[14 + kk] = x1 - *reinterpret_cast<const float*>(p2 + q);
     }
     // (1) a1 = W1 x + b1, h1 = ReLU(a1)
     floatx4_t h1[4];
@@ -333,16 +354,18 @@ __global__ __launch_bounds__(64 * MX_WAVES) void halo2_mx_fwd_kernel(
     for (int kb = 0; kb < 21; ++kb)
 #pragma unroll
       for (int mt = 0; mt < 4; ++mt) h1[mt] = mx(f1[(mt * 21 + kb) * 64 + l], xb[kb], h1[mt]);
+    // (rows beyond the layers' widths have zero weights and biases: never positive, no output)
     uint32_t bits = 0;
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
+    for (int mt = 0; mt < 4; ++mt) {
+      const floatx4_t b1 = *reinterpret_cast<const floatx4_t*>(sv + H2::B1 + 16 * mt + 4 * g);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int m = 16 * mt + 4 * g + i;
-        const float t = m < NP1 ? h1[mt][i] + sv[H2::B1 + m] : 0.f;
+        const float t = h1[mt][i] + b1[i];
         if (t > 0.f) bits |= 1u << (4 * mt + i);
         h1[mt][i] = fmaxf(t, 0.f);
       }
+    }
     // (2) a2 = W2 h1 + b2; y = W3 ReLU(a2) + b3
     floatx4_t a2[2];
 #pragma unroll
@@ -355,16 +378,16 @@ __global__ __launch_bounds__(64 * MX_WAVES) void halo2_mx_fwd_kernel(
         a2[mt] = mx(f2g[(mt * 16 + kb) * 64 + l], h1[kb >> 2][kb & 3], a2[mt]);
     float ys = 0.f;
 #pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
+    for (int mt = 0; mt < 2; ++mt) {
+      const floatx4_t b2 = *reinterpret_cast<const floatx4_t*>(sv + H2::B2 + 16 * mt + 4 * g);
+      const floatx4_t w3 = *reinterpret_cast<const floatx4_t*>(sv + H2::W3 + 16 * mt + 4 * g);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int m = 16 * mt + 4 * g + i;
-        if (m < NP2) {
-          const float t = a2[mt][i] + sv[H2::B2 + m];
-          if (t > 0.f) bits |= 1u << (16 + 4 * mt + i);
-          ys = fmaf(sv[H2::W3 + m], fmaxf(t, 0.f), ys);
-        }
+        const float t = a2[mt][i] + b2[i];
+        if (t > 0.f) bits |= 1u << (16 + 4 * mt + i);
+        ys = fmaf(w3[i], fmaxf(t, 0.f), ys);
       }
+    }
     ys += __shfl_xor(ys, 16, 64);
     ys += __shfl_xor(ys, 32, 64);
     const float y = ys + sv[H2::B3];
@@ -379,7 +402,7 @@ __global__ __launch_bounds__(64 * MX_WAVES) void halo2_mx_fwd_kernel(
 // Written to U, per group of 16 voxels along z: for each triple (field, x, y offset) the sums
 // over the z offsets [27][16] and, behind those of all groups, the two entries that belong to
 // the voxels before and after the group [27][2]. (With u itself written, 81 floats per voxel,
-// and gathered by the stencil kernel the two took 342 and 168 us at 128^3; now 315 and 76.
+// and gathered by the stencil kernel the two took 342 and 168 us at 128^3; now 303 and 76.
 // The four products alone need about 225 us at the card's FP32 matrix rate.)
 __global__ __launch_bounds__(64 * MX_WAVES) void halo2_mx_bwd_kernel(
     int log_n, size_t groups, size_t total, const float* __restrict__ w,
@@ -387,19 +410,22 @@ __global__ __launch_bounds__(64 * MX_WAVES) void halo2_mx_bwd_kernel(
     const float* __restrict__ aux, const uint32_t* __restrict__ sgn, float* __restrict__ U) {
   constexpr int NFRAG = H2::SIZE - H2::F3;
   __shared__ __attribute__((aligned(16))) float sf[NFRAG];
-  __shared__ float sw3[32];  // W3, read per lane group
   for (int i = threadIdx.x; i < NFRAG / 4; i += 64 * MX_WAVES)
     reinterpret_cast<float4*>(sf)[i] = reinterpret_cast<const float4*>(w + H2::F3)[i];
-  if (threadIdx.x < 32) sw3[threadIdx.x] = w[H2::W3 + threadIdx.x];
   __syncthreads();
   const float* f3 = sf;
   const float* f4 = sf + (H2::F4 - H2::F3);
   const int l = threadIdx.x & 63, g = l >> 4, n = l & 15;
+  floatx4_t w3[2];  // this lane group's rows of W3 (0 beyond its 30)
+#pragma unroll
+  for (int mt = 0; mt < 2; ++mt)
+    w3[mt] = *reinterpret_cast<const floatx4_t*>(w + H2::W3 + 16 * mt + 4 * g);
+  const uint32_t w0 = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const size_t stride = (size_t)gridDim.x * MX_WAVES;
-  for (size_t G = (size_t)xcd_block(blockIdx.x, gridDim.x) * MX_WAVES + (threadIdx.x >> 6);
-       G < groups; G += stride) {
+  for (size_t G = (size_t)xcd_block(blockIdx.x, gridDim.x) * MX_WAVES + w0; G < groups;
+       G += stride) {
     const size_t v = G * 16 + n;
-    const size_t item = v >> (3 * log_n);
+    const size_t item = (G * 16) >> (3 * log_n);
     const uint32_t bits = sgn[v * 4 + g];
     const float pos = aux[v];
     const float a = (float)prm[item * NPRM + 6];
@@ -409,10 +435,7 @@ __global__ __launch_bounds__(64 * MX_WAVES) void halo2_mx_bwd_kernel(
 #pragma unroll
     for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int m = 16 * mt + 4 * g + i;
-        a2b[mt][i] = (m < NP2 && ((bits >> (16 + 4 * mt + i)) & 1)) ? sw3[m] * yb : 0.f;
-      }
+      for (int i = 0; i < 4; ++i) a2b[mt][i] = keep_if(bits, 16 + 4 * mt + i, w3[mt][i] * yb);
     floatx4_t a1b[4];
 #pragma unroll
     for (int mt = 0; mt < 4; ++mt) a1b[mt] = floatx4_t{0.f, 0.f, 0.f, 0.f};
@@ -425,7 +448,7 @@ __global__ __launch_bounds__(64 * MX_WAVES) void halo2_mx_bwd_kernel(
 #pragma unroll
     for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) a1b[mt][i] = ((bits >> (4 * mt + i)) & 1) ? a1b[mt][i] : 0.f;
+      for (int i = 0; i < 4; ++i) a1b[mt][i] = keep_if(bits, 4 * mt + i, a1b[mt][i]);
     // (4) u = W1^T a1bar, written per feature
     floatx4_t u[6];
 #pragma unroll
