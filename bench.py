@@ -34,8 +34,8 @@ CLASS_KERNELS = {
     "ypass": r"(ypass(_reg)?_kernel<|xpass(_reg)?_kernel<\d+, 1[34],)", "zpass": r"zpass_",
     "kick_drift": r"kick_drift_kernel",
     "adj_gather": r"adjoint_positions_kernel", "adj_update": r"adjoint_update_kernel",
-    "sort": r"(fill_u32|row_count|scan_reduce|scan_partials|scan_write|bucket|row_sort_wave|"
-            r"row_sort_block)_kernel",
+    "sort": r"(row_count(_loop)?|scan_one|scan_reduce|scan_partials|scan_write|bucket|row_sort)"
+            r"_kernel",
 }
 
 

@@ -306,9 +306,11 @@ int pmr_fft_get_slab(int n, int* columns);
 
 /* Rows per wavefront of the CIC paints on an n^3 mesh with `channels` channels (1: the
  * density, 3: the adjoint's three force channels), process-wide; the autotuner sets it.
- * A wavefront owns `rows` consecutive target rows of one plane and walks the source rows
- * that reach them: more rows read each particle fewer times (2 (rows + 1) / rows walks)
- * but leave fewer wavefronts to share the dense rows of late steps. rows: 0 (the default
+ * The 64-particle chunks are cut as for a wavefront that owns `rows` consecutive target rows
+ * of one plane and walks the source rows that reach them: more rows read each particle fewer
+ * times (2 (rows + 1) / rows walks) but leave fewer wavefronts to share the dense rows of late
+ * steps. Where the launch is short of wavefronts (or of LDS) several share the rows, with the
+ * chunks still cut for all of them, so that the results do not change. rows: 0 (the default
  * rule: 1024 floats of rows per wavefront, at most 8 rows), 1, 2, 4, 8 or 16; a value the
  * size cannot take (LDS, rows per plane) falls back to the default. Each value gives
  * bitwise reproducible results; different values group a cell's deposits differently and

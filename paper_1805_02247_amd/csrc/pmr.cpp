@@ -226,7 +226,9 @@ void plan(pmr_ctx* c, Plan& P) {
   c->net_sgn = P.take<char>(keep ? (keep - 4) * B * c->no3 : 0);
   const bool two = c->cfg.halo_model == PMR_HALO_TWO;
   c->halo2_w = P.take<float>(two ? HALO2_WEIGHT_FLOATS : 0);
-  c->u2 = P.take<float>(two ? halo2_u_floats(B * c->no3) : 0);
+  // (of which halo2_u_floats are used: the planned size of a workspace stays what it was when
+  // the 81 input adjoints of a voxel were kept)
+  c->u2 = P.take<float>(two ? 81 * B * c->no3 : 0);
   c->h2aux = P.take<float>(two ? 2 * B * c->no3 : 0);
   c->h2sgn = P.take<uint32_t>(two ? 4 * B * c->no3 : 0);
   c->target = P.take<float>(B * c->no3);

@@ -127,9 +127,10 @@ struct PaintArgs {
 // Rows per wavefront for a paint whose chunks are cut for `group` rows and whose target rows
 // number `rows` in all: the group, halved while that leaves the launch fewer than 8192
 // wavefronts (256 CUs x 32), since a launch that does not fill the chip lasts as long as its
-// longest walk. 128^3 on 128^3, one item (2048 groups of 8 rows): 56 us with whole groups, 33-36
-// with 2 rows each, 38 with 1; 32^3: 19 -> 10 us. Where the chip is full sharing only adds the
-// chunks read twice: 128^3 x 4 (8192 groups) 80 us whole, 90 with 4 rows each.
+// longest walk. 128^3 on 128^3, one item (2048 groups of 8 rows), one channel: 56 us with whole
+// groups and 33-36 with 2 rows each before the walk was shortened, 28 with 2 rows, 29 with 4 and
+// 33 with 1 since. Where the chip is full sharing only adds the chunks read twice: 128^3 x 4
+// (8192 groups) 69 us whole, 73 with 4 rows each, 82 with 2.
 inline int paint_share(int group, size_t rows) {
   int ty = group;
   while (ty > 1 && rows / (size_t)ty < 8192) ty /= 2;
