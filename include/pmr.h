@@ -246,8 +246,10 @@ enum {
   PMR_PROF_HALO2_STENCIL = 11,    /* two-network model: neighbourhood sum of the position
                                      network's input adjoint */
   PMR_PROF_SORT = 13,             /* every kernel of one cell-key sort and its row index, as
-                                     one launch; an implementation cost that serves the paint
-                                     and the adjoint gathers: its algorithmic bytes are 0 */
+                                     one launch (the segments are counted by the kernels that
+                                     write the keys, in their classes); an implementation cost
+                                     that serves the paint and the adjoint gathers: its
+                                     algorithmic bytes are 0 */
   PMR_PROF_NETWORK = 14           /* the single network's forward and adjoint kernels; their
                                      algorithmic figure is FLOPs: 2 (4H + H^2) per voxel
                                      forward, the same adjoint (the transposed products; at
