@@ -68,3 +68,22 @@ def test_scan_paths(B, nm, shift):
     torch.cuda.synchronize()
     assert int((scratch[need + shift:] != 255).sum()) == 0
     _check(x, nm, box, *out)
+
+
+# 2^25 segments, the most that the kernels writing the keys count, and twice as many (a pass of
+# its own), against torch's stable sort of the same integer keys.
+@pytest.mark.parametrize("B", [8192, 16384])
+def test_both_ways_to_count(B):
+    require_gpu()
+    say(f"sort counts: B={B}")
+    npart, nm, box = 16, 64, 64.0  # one cell per unit length: the corner is the integer part
+    g = torch.Generator(device=DEV).manual_seed(B)
+    x = torch.rand(B, 3, npart ** 3, dtype=torch.float64, device=DEV, generator=g) * box
+    keys, ids, rows = api.cic_sort(x, nm, box)
+    k = x[:, 0].long().mul_(nm).add_(x[:, 1].long()).mul_(nm).add_(x[:, 2].long())
+    k += torch.arange(B, device=DEV)[:, None] * nm ** 3
+    k, order = torch.sort(k.reshape(-1), stable=True)
+    assert torch.equal(keys.long() & 0xFFFFFFFF, k)
+    assert torch.equal(ids.long() & 0xFFFFFFFF, order)
+    row = torch.searchsorted(k // nm, torch.arange(B * nm * nm + 1, device=DEV))
+    assert torch.equal(rows.long() & 0xFFFFFFFF, row)
