@@ -86,8 +86,8 @@ __device__ __forceinline__ void seg_step_fma(float (&v)[NV], uint32_t key) {
   }
 }
 
-// Only the steps the chunk needs run (wave-uniform): bit i of eq says that lane i has the key
-// of lane i - 1. A shift by k inside the rows adds something only where k such bits follow one
+// Only the steps the chunk needs run (wave-uniform): bit i of eq says that lane i continues the
+// run of lane i - 1. A shift by k inside the rows adds something only where k such bits follow one
 // another within a row; the row-crossing steps only where a segment crosses lane 16/48 or 32.
 template <int NV, bool FMA>
 __device__ __forceinline__ void seg_scan_steps(float (&v)[NV], uint32_t key, uint64_t eq) {
@@ -117,14 +117,15 @@ __device__ __forceinline__ void seg_scan_steps(float (&v)[NV], uint32_t key, uin
 }
 
 // Scans v over the runs of equal keys and returns the lanes, of those in `ok`, that end a run
-// (two valid lanes only ever share a key with valid lanes between them). `tame`: this lane's
-// values and all sums of up to 64 like them are finite.
+// (two valid lanes only ever share a key with valid lanes between them; what a lane without a
+// particle adds to a valid one is 0, and those above the run are no valid lane's source).
+// `tame`: this lane's values and all sums of up to 64 like them are finite.
 template <int NV>
 __device__ __forceinline__ uint64_t seg_scan(float (&v)[NV], uint32_t key, uint64_t ok,
                                              bool tame) {
   // wave_shr:1
   const uint32_t kp = (uint32_t)__builtin_amdgcn_mov_dpp((int)key, 0x138, 0xF, 0xF, true);
-  const uint64_t eq = __ballot(kp == key) & ~1ull;
+  const uint64_t eq = run_joins(__ballot(kp == key), ok);
   if (eq != 0) {
     uint64_t wild = __ballot(!tame);
     if (wild == 0) seg_scan_steps<NV, true>(v, key, eq);
@@ -137,7 +138,7 @@ __device__ __forceinline__ uint64_t seg_scan(float (&v)[NV], uint32_t key, uint6
       seg_scan_steps<NV, false>(v, key, eq);
     }
   }
-  return ok & ~(eq >> 1);
+  return run_ends(eq, ok);
 }
 
 // The streams of one 64-particle chunk as they come from memory (one lane's particle).
@@ -205,7 +206,7 @@ __device__ __forceinline__ void weigh_chunk(const PaintArgs& a, const RawChunk<C
   const bool ok = __builtin_amdgcn_inverse_ballot_w64(r.ok);
   const Vec3 f = r.f;
   ch.ok = r.ok;
-  ch.key = ok ? r.key : 0xffffffffu - lane;  // never equal across lanes when invalid
+  ch.key = ok ? r.key : empty_lane_key(lane);
   ch.iz = (int)(r.key & (uint32_t)(nm - 1));
   ch.sy = (int)((r.key >> a.log_nm) & (uint32_t)(nm - 1));
   float val[C];
@@ -283,7 +284,7 @@ __device__ __forceinline__ void weigh_chunk1(const PaintArgs& a, const RawChunk<
   const bool ok = __builtin_amdgcn_inverse_ballot_w64(r.ok);
   const Vec3 f = r.f;
   ch.ok = r.ok;
-  ch.key = ok ? r.key : 0xffffffffu - lane;  // never equal across lanes when invalid
+  ch.key = ok ? r.key : empty_lane_key(lane);
   ch.iz = (int)(r.key & (uint32_t)(nm - 1));
   ch.oy = (int)((r.key >> a.log_nm) & (uint32_t)(nm - 1)) == iy0 ? 0 : 1;
   float val[C];

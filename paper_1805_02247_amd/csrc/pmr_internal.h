@@ -5,6 +5,8 @@
 #include <stdint.h>
 #include <stddef.h>
 
+#include "chunk_masks.h"
+
 #define PMR_WAVE 64
 
 namespace pmr {
