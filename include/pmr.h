@@ -111,7 +111,11 @@ int pmr_destroy(pmr_ctx* ctx);
 int pmr_set_prior(pmr_ctx* ctx, const float* inv_var);
 
 /* Network weights, float32 row-major [out][in]: W1 [H][3], b1 [H], W2 [H][H], b2 [H],
- * W3 [1][H], b3 [1] (Sec. 2.1; frozen). Copied. Required for PMR_LOSS_LOGNORMAL. */
+ * W3 [1][H], b3 [1] (Sec. 2.1; frozen). Copied. Required for PMR_LOSS_LOGNORMAL.
+ * New weights between a forward and its adjoint: the adjoint's network derivative is that of
+ * the new weights at the forward's fields (once a forward has run, each call therefore
+ * evaluates the network on those fields, which costs what the forward's network does; at
+ * H = 8, whose adjoint evaluates it itself, nothing). */
 int pmr_set_mlp(pmr_ctx* ctx, const float* W1, const float* b1, const float* W2,
                 const float* b2, const float* W3, const float* b3);
 

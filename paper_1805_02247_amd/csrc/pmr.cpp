@@ -720,6 +720,14 @@ void refresh_xd(pmr_ctx* c) {
   c->xd_dirty = 0;
 }
 
+// The single network on the fields of the last forward; what its adjoint needs (the outputs and
+// ReLU signs, where it does not recompute them) goes to the context, the masses to `mass`.
+int network_forward(pmr_ctx* c, float* mass) {
+  const size_t n = (size_t)c->B * c->no3;
+  return (c->cfg.precision == PMR_MIXED ? launch_mlp_fwd_mfma : launch_mlp_fwd)(
+      c->H, c->delta_f, c->dR, c->dR + n, n, c->mlp_w, mass, c->net_y, c->net_sgn, c->stream);
+}
+
 // Inverse transform of spectra in the standard layout: the x pass writes `mid` (rows of
 // `pitch` values; `in` itself at the standard pitch), y and z finish from there.
 int c2r_from(int n, int batch, const float2* in, float2* mid, size_t pitch, float* out,
@@ -811,6 +819,10 @@ int pmr_set_mlp(pmr_ctx* c, const float* W1, const float* b1, const float* W2, c
   HIPC(c, hipMemcpyAsync(w + 5 * H + H * H, W3, H * f, hipMemcpyDeviceToDevice, c->stream));
   HIPC(c, hipMemcpyAsync(w + 6 * H + H * H, b3, f, hipMemcpyDeviceToDevice, c->stream));
   if (c->cfg.precision == PMR_MIXED && launch_mlp_prepare_bf16(H, w, c->stream) != 0)
+    return PMR_E_SHAPE;
+  // An adjoint of a forward that has run (or is replayed from a graph) is that of the network with
+  // the new weights: the outputs and signs it reads are taken again, the masses are not kept.
+  if (c->n_forward > 0 && mlp_keep_bytes(H) != 0 && network_forward(c, c->ob) != 0)
     return PMR_E_SHAPE;
   c->have_mlp = 1;
   return check(c);
@@ -972,13 +984,7 @@ int pmr_forward(pmr_ctx* c, const void* modes, float* mass_out, double* loss_out
     } else {
       const double Hd = c->H;
       ProfScope ps(c, PMR_PROF_NETWORK, 2.0 * (4.0 * Hd + Hd * Hd) * B * no3);
-      const int rc = c->cfg.precision == PMR_MIXED
-                         ? launch_mlp_fwd_mfma(c->H, c->delta_f, c->dR, c->dR + (size_t)B * no3,
-                                               (size_t)B * no3, c->mlp_w, c->mass, c->net_y,
-                                               c->net_sgn, s)
-                         : launch_mlp_fwd(c->H, c->delta_f, c->dR, c->dR + (size_t)B * no3,
-                                          (size_t)B * no3, c->mlp_w, c->mass, c->net_y,
-                                          c->net_sgn, s);
+      const int rc = network_forward(c, c->mass);
       if (rc != 0) return PMR_E_SHAPE;
     }
     smooth(c, c->no, c->mass, 3, c->MR, nullptr);
