@@ -291,7 +291,12 @@ int pmr_fft_c2r_work(int n, int batch, const void* in, void* work, float* out, v
  * the butterflies on register images of the tile (radix-8 stages; used where n * columns /
  * threads is a multiple of 8 and n >= 64; LDS only permutes between radix stages), 1 runs
  * every stage on the LDS-staged tile with radix-8 stages (then one radix-4 or radix-2
- * stage), 2 the same with radix-4 stages (then one radix-2 stage). Invalid values return
+ * stage), 2 the same with radix-4 stages (then one radix-2 stage). Up to 128^3 the y and z
+ * transforms of a field, and the three of a force, run plane by plane in one launch where the
+ * strided passes have the planes' butterflies (y pass: radix 4 at 64 and 128, radix 8 below; the
+ * force's derivatives: radix 8 on the LDS tile), with the same results bit for bit; `columns`
+ * and `threads` then apply to the y passes that remain (after the fused paints, and with kz
+ * windows). Invalid values return
  * PMR_E_INVALID and leave the shape unchanged.
  * Defaults: 16 columns, 256 threads, staging 0. Not synchronised with work in flight: set it
  * before enqueueing. */

@@ -18,7 +18,22 @@ int log2i(int n) {
   while ((1 << l) < n) ++l;
   return l;
 }
+
+// Radix of the stages that a strided pass runs with its current tile: 8 or 4 on the LDS tile, 0
+// for register images (radix 8 too, but the inverse takes the radices in reverse order).
+int strided_radix(int n, int pass) {
+  const TileShape t = g_fft_tile[pass][log2i(n)];
+  const int points = n * t.pc / t.nth;  // per thread
+  if (t.staging == 0 && n >= 64 && points >= 8 && points % 8 == 0) return 0;
+  return t.staging == 2 ? 4 : 8;
+}
 }  // namespace
+
+bool plane_passes(int n) { return n <= PLANE_MAX && strided_radix(n, 0) == plane_radix(n); }
+
+bool plane_force(int n, int items) {
+  return plane_passes(n) && strided_radix(n, 1) == 8 && (n < 128 || (size_t)items * n >= 256);
+}
 
 void fft_zr2c_16(int, const float*, FieldMap, const float*, float, float, const double*, float2*,
                FieldMap, hipStream_t);

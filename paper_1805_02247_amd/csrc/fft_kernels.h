@@ -571,17 +571,16 @@ __global__ __launch_bounds__(NT) void zpass_c2r3_kernel(const float2* __restrict
 // to memory and back between them, and two or three launches become one. The plane is kept
 // in the z pass's padded rows; the y stages run over its columns with consecutive threads on
 // consecutive columns. Every line goes through the same stages and operators as in the
-// separate passes (radix-4 y stages at 64 and 128, as those are tuned), so the results are
-// the same bit for bit.
+// separate passes whose tiles have these radices (the only ones it stands in for: plane_passes,
+// plane_force), so the results are the same bit for bit.
 template <int N>
 struct Plane {
   static constexpr int H = N / 2, NH = H + 1;
   static constexpr int P = ZTile<N>::PITCH;  // row pitch in LDS (complex); slot of column l: zk(l)
   static constexpr int NTH = N >= 128 ? 1024 : N >= 64 ? 512 : 256;
-  static constexpr int YR = N >= 64 ? 4 : 8;  // radix of the plain y stages
+  static constexpr int YR = plane_radix(N);  // radix of the plain y stages
   static constexpr int PAIRS = (NH + 1) / 2;  // column pairs of a row
 };
-constexpr int PLANE_MAX = 128;
 
 // One Stockham stage (see stockham_stage) along y over the NH columns of the plane.
 template <int N, int R, int PREV, int DIR>

@@ -214,16 +214,20 @@ void launch_paint_r2c(int n, int channels, const PaintArgs& a, int batch, float2
 void launch_zpass_c2r3(int n, int items, const float2* in, FieldMap im, Vec3* out,
                        size_t out_item_stride, hipStream_t s);
 // The y and z transforms together: plane by plane in one launch up to 128^3 (plane_passes),
-// else the separate passes (the c2r then runs the inverse y pass in place on `in`).
-inline bool plane_passes(int n) { return n <= 128; }
-// The force mesh plane by plane: three transforms in turn in each workgroup, so it wants a plane
-// for every CU (256), except below 128^3, where the launches it saves are worth more. 128^3, one
-// item (128 planes): 35 us against 32 in three launches; four items 83 against 91; 64^3 x 32: 74
-// against 98. (The passes over one field at 128^3, one item: 14-16 us either way, in one launch
-// instead of two.)
-inline bool plane_force(int n, int items) {
-  return plane_passes(n) && (n < 128 || (size_t)items * n >= 256);
-}
+// else the separate passes (the c2r then runs the inverse y pass in place on `in`). The planes
+// stand in for y passes with the same butterflies only: radix-4 stages at 64 and 128, radix-8
+// below, as those are tuned. So which of the two ran (the batch, the kz windows) never shows in
+// a result, and a y tile with other butterflies runs as it is set.
+constexpr int PLANE_MAX = 128;
+constexpr int plane_radix(int n) { return n >= 64 ? 4 : 8; }
+bool plane_passes(int n);
+// The force mesh plane by plane (its y and z derivatives with radix-8 stages, so the x pass's
+// tile, which holds for that pass, has to have them): three transforms in turn in each
+// workgroup, so it wants a plane for every CU (256), except below 128^3, where the launches it
+// saves are worth more. 128^3, one item (128 planes): 35 us against 32 in three launches; four
+// items 83 against 91; 64^3 x 32: 74 against 98. (The passes over one field at 128^3, one item:
+// 14-16 us either way, in one launch instead of two.)
+bool plane_force(int n, int items);
 void launch_zy_r2c(int n, int fields, const float* in, FieldMap im, const float* in2, float a1,
                    float a2, const double* scale_dev, float2* out, FieldMap om, hipStream_t s);
 void launch_yz_c2r(int n, int fields, float2* in, FieldMap im, float* out, FieldMap om,
