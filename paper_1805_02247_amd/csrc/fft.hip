@@ -94,17 +94,9 @@ void fft_zy_r2c_128(int, const float*, FieldMap, const float*, float, float, con
                  FieldMap, hipStream_t);
 void fft_yz_c2r_128(int, const float2*, FieldMap, float*, FieldMap, const float*, hipStream_t);
 void fft_yz_c2r3_128(int, const float2*, FieldMap, Vec3*, size_t, double, hipStream_t);
-void fft_zy_r2c_256(int, const float*, FieldMap, const float*, float, float, const double*, float2*,
-                 FieldMap, hipStream_t);
-void fft_yz_c2r_256(int, const float2*, FieldMap, float*, FieldMap, const float*, hipStream_t);
-void fft_yz_c2r3_256(int, const float2*, FieldMap, Vec3*, size_t, double, hipStream_t);
-void fft_zy_r2c_512(int, const float*, FieldMap, const float*, float, float, const double*, float2*,
-                 FieldMap, hipStream_t);
-void fft_yz_c2r_512(int, const float2*, FieldMap, float*, FieldMap, const float*, hipStream_t);
-void fft_yz_c2r3_512(int, const float2*, FieldMap, Vec3*, size_t, double, hipStream_t);
 
-#define PMR_FOR_N(MACRO) \
-  MACRO(16) MACRO(32) MACRO(64) MACRO(128) MACRO(256) MACRO(512)
+#define PMR_FOR_PLANE_N(MACRO) MACRO(16) MACRO(32) MACRO(64) MACRO(128)
+#define PMR_FOR_N(MACRO) PMR_FOR_PLANE_N(MACRO) MACRO(256) MACRO(512)
 
 void launch_zpass_r2c(int n, int fields, const float* in, FieldMap im, const float* in2, float a1,
                       float a2, const double* scale_dev, float2* out, FieldMap om, hipStream_t s) {
@@ -149,7 +141,7 @@ void launch_zy_r2c(int n, int fields, const float* in, FieldMap im, const float*
   switch (n) {
 #define CASE(NN) \
   case NN: fft_zy_r2c_##NN(fields, in, im, in2, a1, a2, scale_dev, out, om, s); break;
-    PMR_FOR_N(CASE)
+    PMR_FOR_PLANE_N(CASE)
 #undef CASE
     default: break;
   }
@@ -165,7 +157,7 @@ void launch_yz_c2r(int n, int fields, float2* in, FieldMap im, float* out, Field
   switch (n) {
 #define CASE(NN) \
   case NN: fft_yz_c2r_##NN(fields, in, im, out, om, add, s); break;
-    PMR_FOR_N(CASE)
+    PMR_FOR_PLANE_N(CASE)
 #undef CASE
     default: break;
   }
@@ -176,7 +168,7 @@ void launch_yz_c2r3(int n, int items, const float2* in, FieldMap im, Vec3* out,
   switch (n) {
 #define CASE(NN) \
   case NN: fft_yz_c2r3_##NN(items, in, im, out, out_item_stride, box, s); break;
-    PMR_FOR_N(CASE)
+    PMR_FOR_PLANE_N(CASE)
 #undef CASE
     default: break;
   }

@@ -1281,28 +1281,24 @@ void zc2r(int fields, const float2* in, FieldMap im, float* out, FieldMap om, co
       in, im, out, om, add, per, ntiles);
 }
 
-// Both transforms of the y and z axes: plane by plane where a plane fits in LDS.
+// Both transforms of the y and z axes plane by plane (N <= PLANE_MAX).
 template <int N>
 void zy_r2c(int fields, const float* in, FieldMap im, const float* in2, float a1, float a2,
             const double* sc, float2* out, FieldMap om, hipStream_t s) {
-  if constexpr (N <= PLANE_MAX)
-    zpass_plane_r2c_kernel<N><<<fields * N, Plane<N>::NTH, 0, s>>>(in, im, in2, a1, a2, sc, out,
-                                                                   om);
+  zpass_plane_r2c_kernel<N><<<fields * N, Plane<N>::NTH, 0, s>>>(in, im, in2, a1, a2, sc, out, om);
 }
 
 template <int N>
 void yz_c2r(int fields, const float2* in, FieldMap im, float* out, FieldMap om, const float* add,
             hipStream_t s) {
-  if constexpr (N <= PLANE_MAX)
-    zpass_plane_c2r_kernel<N><<<fields * N, Plane<N>::NTH, 0, s>>>(in, im, out, om, add);
+  zpass_plane_c2r_kernel<N><<<fields * N, Plane<N>::NTH, 0, s>>>(in, im, out, om, add);
 }
 
 template <int N>
 void yz_c2r3(int items, const float2* in, FieldMap im, Vec3* out, size_t out_item_stride,
              double box, hipStream_t s) {
-  if constexpr (N <= PLANE_MAX)
-    zpass_plane_c2r3_kernel<N><<<items * N, Plane<N>::NTH, 0, s>>>(in, im, out, out_item_stride,
-                                                                   box);
+  zpass_plane_c2r3_kernel<N><<<items * N, Plane<N>::NTH, 0, s>>>(in, im, out, out_item_stride,
+                                                                 box);
 }
 
 int log2i(int n) {

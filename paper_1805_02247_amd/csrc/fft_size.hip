@@ -26,6 +26,7 @@ void PMR_CAT(fft_zc2r3_, PMR_FFT_SIZE)(int items, const float2* in, FieldMap im,
   zc2r3<PMR_FFT_SIZE>(items, in, im, out, out_item_stride, s);
 }
 
+#if PMR_FFT_SIZE <= 128  // PLANE_MAX
 void PMR_CAT(fft_zy_r2c_, PMR_FFT_SIZE)(int fields, const float* in, FieldMap im,
                                         const float* in2, float a1, float a2, const double* sc,
                                         float2* out, FieldMap om, hipStream_t s) {
@@ -41,6 +42,7 @@ void PMR_CAT(fft_yz_c2r3_, PMR_FFT_SIZE)(int items, const float2* in, FieldMap i
                                          size_t out_item_stride, double box, hipStream_t s) {
   yz_c2r3<PMR_FFT_SIZE>(items, in, im, out, out_item_stride, box, s);
 }
+#endif
 
 void PMR_CAT(fft_paint_r2c_, PMR_FFT_SIZE)(int channels, const PaintArgs& a, int batch,
                                            float2* out, FieldMap om, hipStream_t s) {
