@@ -244,6 +244,66 @@ __device__ __forceinline__ const float* gram_vector(const LoopArgs& a, int count
   return h == 0 && v == GRAM_MAX ? a.g : nullptr;
 }
 
+// The same for one or two pairs, on the vector units: the matrix form takes 512 products per
+// element whatever the count, of which one pair needs 4 and two need 12. A direction over 2.1e6
+// elements took 67 and 68 us with it (38 and 68 as the launches of the recursion), now 32 and 37;
+// over 1.7e7 425 and 454 (182 and 328), now 158 and 198. From three pairs on the matrix form is as
+// fast or faster (69 against 98, 459 against 472). Bound by reading the vectors.
+template <int C, class Slot>
+__device__ __forceinline__ void gram_few_body(const LoopArgs& a, Slot slot,
+                                              double* __restrict__ out) {
+  constexpr int WAVES = GRAM_TB / 64, NE = 2 * C * (C + 1);
+  __shared__ double red[WAVES][NE];
+  const size_t n = a.n;
+  const float* p[2 * C + 1];  // y_j, g, s_j
+#pragma unroll
+  for (int j = 0; j < C; ++j) {
+    p[j] = a.Y + slot(j) * n;
+    p[C + 1 + j] = a.S + slot(j) * n;
+  }
+  p[C] = a.g;
+  const bool wide = (n & 3) == 0 && (((uintptr_t)a.S | (uintptr_t)a.Y | (uintptr_t)a.g) & 15) == 0;
+  double acc[2][C][C + 1] = {};
+  const size_t step = (size_t)gridDim.x * GRAM_TB * 4;
+#pragma unroll 2
+  for (size_t e = ((size_t)blockIdx.x * GRAM_TB + threadIdx.x) * 4; e < n; e += step) {
+    float4v v[2 * C + 1];
+#pragma unroll
+    for (int q = 0; q <= 2 * C; ++q) {
+      if (wide) {
+        v[q] = *reinterpret_cast<const float4v*>(p[q] + e);
+      } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[q][i] = e + i < n ? p[q][e + i] : 0.f;
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < C; ++j)
+#pragma unroll
+        for (int k = 0; k <= C; ++k) {
+          acc[0][j][k] = __builtin_fma((double)v[j][i], (double)v[k][i], acc[0][j][k]);
+          acc[1][j][k] = __builtin_fma((double)v[C + 1 + j][i], (double)v[k][i], acc[1][j][k]);
+        }
+  }
+#pragma unroll
+  for (int q = 0; q < NE; ++q) {
+    double s = acc[q / (C * (C + 1))][q / (C + 1) % C][q % (C + 1)];
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) s += __shfl_down(s, d, 64);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6][q] = s;
+  }
+  __syncthreads();
+  if (threadIdx.x < NE) {
+    const int q = threadIdx.x, h = q / (C * (C + 1)), j = q / (C + 1) % C, k = q % (C + 1);
+    double s = 0.0;
+#pragma unroll
+    for (int u = 0; u < WAVES; ++u) s += red[u][q];
+    out[(size_t)blockIdx.x * GRAM_N + h * 256 + j * 16 + (k == C ? GRAM_MAX : k)] = s;
+  }
+}
+
 // Partial Gram matrices. A wavefront takes 64 elements at a time: lane l holds elements
 // 16 q + 4 (l / 16) .. + 3 of vector l % 16 of both blocks, which as operands of
 // v_mfma_f64_16x16x4 (A[m][k], B[k][n]: m, n = l % 16, k = l / 16) give the same element to both
@@ -251,6 +311,9 @@ __device__ __forceinline__ const float* gram_vector(const LoopArgs& a, int count
 template <class Slot>
 __device__ __forceinline__ void gram_body(const LoopArgs& a, int count, Slot slot,
                                           double* __restrict__ out) {
+  if (count == 0) return;  // d = -g, which the combination writes by itself
+  if (count == 1) return gram_few_body<1>(a, slot, out);
+  if (count == 2) return gram_few_body<2>(a, slot, out);
   constexpr int WAVES = GRAM_TB / 64;
   __shared__ double red[WAVES][GRAM_N / 4];
   const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -336,27 +399,39 @@ __device__ __forceinline__ void combine_body(const LoopArgs& a, int count, Slot 
   __shared__ double cg_sh;
   const double* GS = G + 256;
   const int t = threadIdx.x;
-  if (t < 64) {
+  const size_t n = a.n, stride = (size_t)gridDim.x * TB;
+  double acc = 0.0;
+  if (count == 0) {  // bound by the copy: 4 elements in flight per thread
+    for (size_t k0 = (size_t)blockIdx.x * TB + t; k0 < n; k0 += 4 * stride) {
+      float gv[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) gv[u] = k0 + u * stride < n ? a.g[k0 + u * stride] : 0.f;
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (k0 + u * stride < n) {
+          a.d[k0 + u * stride] = -gv[u];
+          acc += (double)gv[u] * (double)-gv[u];
+        }
+    }
+  } else if (t < 64) {
     const int j = t < count ? t : 0;
-    double alpha = 0.0, delta = 0.0, gamma = 1.0;
-    if (count > 0) {
-      const size_t i0 = slot(0);
-      gamma = a.sy[i0] / a.yy[i0];
-      const double sy = a.sy[slot(j)];
-      double sq = GS[16 * j + GRAM_MAX];  // s_j.q
-      for (int k = 0; k < count; ++k) {              // newest to oldest
-        const double ak = __shfl(sq / sy, k, 64);
-        if (t == k) alpha = ak;
-        sq -= ak * GS[16 * j + k];
-      }
-      double yr = G[16 * j + GRAM_MAX];  // y_j.r
-      for (int k = 0; k < count; ++k) yr -= __shfl(alpha, k, 64) * G[16 * j + k];
-      yr *= gamma;
-      for (int k = count - 1; k >= 0; --k) {  // oldest to newest
-        const double dk = __shfl(alpha - yr / sy, k, 64);
-        if (t == k) delta = dk;
-        yr += dk * GS[16 * k + j];
-      }
+    double alpha = 0.0, delta = 0.0;
+    const size_t i0 = slot(0);
+    const double gamma = a.sy[i0] / a.yy[i0];
+    const double sy = a.sy[slot(j)];
+    double sq = GS[16 * j + GRAM_MAX];  // s_j.q
+    for (int k = 0; k < count; ++k) {   // newest to oldest
+      const double ak = __shfl(sq / sy, k, 64);
+      if (t == k) alpha = ak;
+      sq -= ak * GS[16 * j + k];
+    }
+    double yr = G[16 * j + GRAM_MAX];  // y_j.r
+    for (int k = 0; k < count; ++k) yr -= __shfl(alpha, k, 64) * G[16 * j + k];
+    yr *= gamma;
+    for (int k = count - 1; k >= 0; --k) {  // oldest to newest
+      const double dk = __shfl(alpha - yr / sy, k, 64);
+      if (t == k) delta = dk;
+      yr += dk * GS[16 * k + j];
     }
     if (t < count) {
       co[0][t] = gamma * alpha;
@@ -366,10 +441,8 @@ __device__ __forceinline__ void combine_body(const LoopArgs& a, int count, Slot 
   }
   __syncthreads();
   const double cg = cg_sh;
-  const size_t n = a.n, stride = (size_t)gridDim.x * TB;
-  double acc = 0.0;
   constexpr int U = 2;  // elements in flight per thread
-  for (size_t k0 = (size_t)blockIdx.x * TB + t; k0 < n; k0 += U * stride) {
+  for (size_t k0 = (size_t)blockIdx.x * TB + t; count > 0 && k0 < n; k0 += U * stride) {
     double r[U];
     float gv[U], yv[U][GRAM_MAX], sv[U][GRAM_MAX];
 #pragma unroll
@@ -663,8 +736,10 @@ void launch_lbfgs_direction(size_t n, int m, int count, const int* order, const 
   if (count <= GRAM_MAX && m <= GRAM_MAX + 1) {
     const int gb = gram_blocks(n);
     double* total = gram + (size_t)gb * GRAM_N;
-    gram_kernel<<<gb, GRAM_TB, 0, s>>>(a, count, o, gram);
-    gram_sum_kernel<<<GRAM_N / (TB / 64), TB, 0, s>>>(gram, gb, total);
+    if (count > 0) {
+      gram_kernel<<<gb, GRAM_TB, 0, s>>>(a, count, o, gram);
+      gram_sum_kernel<<<GRAM_N / (TB / 64), TB, 0, s>>>(gram, gb, total);
+    }
     combine_kernel<<<nb, TB, 0, s>>>(a, count, o, total);
     return;
   }
@@ -731,7 +806,7 @@ __global__ __launch_bounds__(GRAM_TB) void lb_gram_kernel(const pmr_lbfgs_state*
 __global__ __launch_bounds__(TB) void lb_gram_sum_kernel(const pmr_lbfgs_state* st,
                                                          const double* part, int blocks,
                                                          double* total) {
-  if (!gate_open(st, G_DIR, -1)) return;
+  if (!gate_open(st, G_DIR, 0)) return;
   gram_sum_body(part, blocks, total);
 }
 __global__ __launch_bounds__(TB) void lb_combine_kernel(const pmr_lbfgs_state* st, LoopArgs a,
