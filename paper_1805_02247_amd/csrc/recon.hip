@@ -797,11 +797,15 @@ __global__ __launch_bounds__(TB) void lb_loop_kernel(const pmr_lbfgs_state* st, 
   loop_body(a, st->count, [&](int k) { return (size_t)st->order[k]; });
 }
 
-// The Gram form of the same.
+// The Gram form of the same, for the newest GRAM_MAX pairs: more are held only where the update's
+// m is not the state's, and then the form still keeps to its blocks.
+__device__ __forceinline__ int gram_count(const pmr_lbfgs_state* st) {
+  return st->count < GRAM_MAX ? st->count : GRAM_MAX;
+}
 __global__ __launch_bounds__(GRAM_TB) void lb_gram_kernel(const pmr_lbfgs_state* st, LoopArgs a,
                                                           double* out) {
   if (!gate_open(st, G_DIR, -1)) return;
-  gram_body(a, st->count, [&](int k) { return (size_t)st->order[k]; }, out);
+  gram_body(a, gram_count(st), [&](int k) { return (size_t)st->order[k]; }, out);
 }
 __global__ __launch_bounds__(TB) void lb_gram_sum_kernel(const pmr_lbfgs_state* st,
                                                          const double* part, int blocks,
@@ -812,7 +816,7 @@ __global__ __launch_bounds__(TB) void lb_gram_sum_kernel(const pmr_lbfgs_state* 
 __global__ __launch_bounds__(TB) void lb_combine_kernel(const pmr_lbfgs_state* st, LoopArgs a,
                                                         const double* G) {
   if (!gate_open(st, G_DIR, -1)) return;
-  combine_body(a, st->count, [&](int k) { return (size_t)st->order[k]; }, G);
+  combine_body(a, gram_count(st), [&](int k) { return (size_t)st->order[k]; }, G);
 }
 
 // The candidate pair of an accepted trial, s = xt - x and y = gt - g, into its slot, with the

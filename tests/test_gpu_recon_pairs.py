@@ -1,10 +1,15 @@
 """The L-BFGS direction at the history lengths where its form changes: none, one and two pairs
 (the Gram matrix on the vector units), up to 15 (on the matrix units), more, or buffers of more
 slots (the recursion launch by launch)."""
+import ctypes
+import math
+
 import numpy as np
 import pytest
 import torch
 
+from paper_1805_02247_amd import _lib as L
+from paper_1805_02247_amd import api
 from paper_1805_02247_amd import recon as R
 from _gpu import DEV, rel_l2, require_gpu, say
 
@@ -61,3 +66,53 @@ def test_direction(n, m, count, off):
     # one rounding per element and FP64 inner products, amplified by cancellation along the
     # history (the bound of the directions of other lengths)
     assert rel_l2(d.cpu().numpy(), ref) < (2 * count + 2) * 2e-6
+
+
+def test_update_with_a_shorter_history_than_the_state_holds():
+    """The caller's m is below the state's, which the header forbids and no call can see: a
+    descent direction from the newest 15 pairs, and nothing outside the buffers."""
+    require_gpu()
+    say("L-BFGS update: m below the state's")
+    n, m, guard = 200, 20, 512
+    lib = L.lib()
+    f32 = dict(dtype=torch.float32, device=DEV)
+    f64 = dict(dtype=torch.float64, device=DEV)
+    diag = torch.logspace(0.0, 1.5, n, **f32)
+    x, xt, g, gt, d = (torch.ones(n, **f32) for _ in range(5))
+    S, Y = torch.zeros(m + 1, n, **f32), torch.zeros(m + 1, n, **f32)
+    sy, yy = torch.zeros(m + 1, **f64), torch.zeros(m + 1, **f64)
+    words = int(lib.pmr_vec_work_bytes(n, 0)) // 8
+    work = torch.full((words + guard,), 7.0, **f64)
+    state = torch.zeros(int(lib.pmr_lbfgs_state_bytes(100)) // 8, **f64)
+    loss = torch.zeros(1, **f64)
+
+    def evaluate(at, grad):
+        grad.copy_(diag * at + 0.1 * at ** 3)
+        loss[0] = (0.5 * diag * at ** 2 + 0.025 * at ** 4).double().sum()
+
+    def held():
+        raw = state.view(torch.uint8)[:ctypes.sizeof(L.PmrLbfgsState)].cpu().numpy().tobytes()
+        return L.PmrLbfgsState.from_buffer_copy(raw)
+
+    evaluate(x, g)
+    prm = L.PmrLbfgsParams(m=m, max_iter=100, max_halvings=30, c1=1e-4, curvature_eps=0.0,
+                           rel_tol=0.0, stop_below=-math.inf)
+    p, s = api._ptr, api._stream()
+    L.check(lib.pmr_lbfgs_init(n, ctypes.byref(prm), p(state), p(loss), p(g), p(d), p(S), p(Y), p(sy),
+                               p(yy), p(work), s))
+    for k in range(60):
+        L.check(lib.pmr_lbfgs_trial(n, p(state), p(x), p(d), p(xt), s))
+        evaluate(xt, gt)
+        short = held().count >= 17
+        L.check(lib.pmr_lbfgs_update(n, 10 if short else m, p(state), p(loss), p(x), p(g), p(xt),
+                                     p(gt), p(d), p(S), p(Y), p(sy), p(yy), p(work), s))
+        torch.cuda.synchronize()
+        if short and held().accepted:
+            break
+    st = held()
+    assert st.count >= 17 and st.accepted and st.status == 1
+    assert torch.isfinite(d).all() and float((g.double() @ d.double())) < 0.0
+    assert torch.equal(work[words:], torch.full((guard,), 7.0, **f64))
+    order = list(st.order[:15])
+    ref = _direction64(S.cpu().numpy(), Y.cpu().numpy(), g.cpu().numpy(), order)
+    assert rel_l2(d.cpu().numpy(), ref) < 32 * 2e-6
