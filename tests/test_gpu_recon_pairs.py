@@ -8,8 +8,9 @@ import numpy as np
 import pytest
 import torch
 
+import synth
 from paper_1805_02247_amd import _lib as L
-from paper_1805_02247_amd import api
+from paper_1805_02247_amd import api, cosmo
 from paper_1805_02247_amd import recon as R
 from _gpu import DEV, rel_l2, require_gpu, say
 
@@ -39,6 +40,8 @@ def _direction64(S, Y, g, order):
 # n: below a wavefront's 64 elements, not a multiple of 4 (no 16-byte loads), several blocks;
 # the last digit moves every vector off its 16-byte alignment by that many floats
 @pytest.mark.parametrize("n,m,count,off", [
+    (61, 15, 15, 0), (4099, 15, 15, 0), (61, 16, 15, 0), (4100, 16, 15, 2), (61, 16, 16, 0),
+    (4099, 16, 16, 0), (4099, 17, 15, 0), (61, 17, 16, 0), (4100, 11, 3, 0), (4099, 14, 13, 0),
     (5, 4, 1, 0), (2047, 16, 2, 0), (4100, 2, 2, 1), (300001, 3, 1, 0), (8192, 3, 0, 3), (262148, 2, 1, 0)])
 def test_direction(n, m, count, off):
     require_gpu()
@@ -66,6 +69,39 @@ def test_direction(n, m, count, off):
     # one rounding per element and FP64 inner products, amplified by cancellation along the
     # history (the bound of the directions of other lengths)
     assert rel_l2(d.cpu().numpy(), ref) < (2 * count + 2) * 2e-6
+
+
+# 15: the longest history in the Gram form (16 slots on the host), 16 and more: launch by launch
+@pytest.mark.parametrize("m", [1, 2, 14, 15, 16, 20])
+def test_both_drivers_take_the_same_steps(m):
+    """Enough iterations to fill and turn over the history; the losses and the modes are the same
+    bit for bit."""
+    require_gpu()
+    n, box, iters = 16, 100.0, m + 6
+    say(f"L-BFGS drivers: m={m}")
+    power = cosmo.linear_power(0.8, 0.2)
+    modes = [torch.from_numpy(cosmo.modes_from_white_noise(synth.white_noise(q, n), box, power)
+                              .astype(np.complex64)).reshape(1, -1).to(DEV) for q in (1, 2)]
+
+    def context():
+        pm = api.PMContext(api.Config(batch=1, n_part=n, n_mesh=n, n_out=n, n_steps=2, box=box,
+                                      loss_kind=L.PMR_LOSS_DENSITY_L2), DEV)
+        pm.set_prior(torch.from_numpy(cosmo.prior_inv_variance(n, box, power)))
+        pm.set_target(torch.zeros(1, n ** 3, device=DEV))
+        pm.set_loss(api.LossParams())
+        pm.forward(modes[0], want_mass=False)
+        pm.set_target(pm.debug("delta_f").reshape(1, -1).clone())
+        return pm
+
+    a, b = modes[1].clone(), modes[1].clone()
+    host = R.minimize(context(), a, max_iter=iters, m=m, rel_tol=0.0)
+    D = R.DeviceLBFGS(context(), b, api.LossParams(), m=m, max_iter=iters)
+    dev = D.stage(b, api.LossParams(), rel_tol=0.0)
+    say(f"  {host.iters} iterations, {host.evals} evaluations, {host.reason}")
+    assert host.iters == iters and host.reason == "max_iter"
+    assert (dev.losses, dev.iters, dev.evals, dev.reason) == (host.losses, host.iters, host.evals,
+                                                              host.reason)
+    assert torch.equal(torch.view_as_real(a), torch.view_as_real(b))
 
 
 def test_update_with_a_shorter_history_than_the_state_holds():
