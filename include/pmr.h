@@ -275,7 +275,8 @@ int pmr_fft_c2r(int n, int batch, void* inout, float* out, void* stream);
 
 /* The same from an input that is kept: `work` (16-byte aligned device memory of
  * pmr_fft_c2r_work_bytes(n, batch)) takes the intermediate spectra, so the caller need not
- * copy the input first. PMR_E_INVALID for a null or misaligned pointer. */
+ * copy the input first. PMR_E_INVALID for a null or misaligned pointer, or a work buffer that
+ * overlaps the input (whose rows have another pitch). */
 size_t pmr_fft_c2r_work_bytes(int n, int batch);
 int pmr_fft_c2r_work(int n, int batch, const void* in, void* work, float* out, void* stream);
 

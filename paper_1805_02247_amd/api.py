@@ -326,9 +326,7 @@ def fft_r2c(x):
 def fft_c2r(X):
     """Inverse 3-D real FFT (with 1/n^3) of complex64 [B][n][n][n/2+1] -> float32."""
     B, n = X.shape[0], X.shape[1]
-    X = X.contiguous()
-    if X.is_conj():
-        X = X.resolve_conj()
+    X = X.contiguous().resolve_conj().resolve_neg()  # the kernels read the memory as it is
     work = torch.empty(int(L.lib().pmr_fft_c2r_work_bytes(n, B)), dtype=torch.uint8,
                        device=X.device)
     out = torch.empty(B, n, n, n, dtype=torch.float32, device=X.device)

@@ -1354,6 +1354,9 @@ int pmr_fft_c2r_work(int n, int batch, const void* in, void* work, float* out, v
   if (!in || !out || batch < 1) return PMR_E_INVALID;
   if (!pow2_in(n, 16, 512)) return PMR_E_SHAPE;
   if (!work || ((uintptr_t)work & 15)) return PMR_E_INVALID;
+  const uintptr_t i = (uintptr_t)in, w = (uintptr_t)work;
+  if (i < w + pmr_fft_c2r_work_bytes(n, batch) && w < i + (size_t)batch * cplx(n) * sizeof(float2))
+    return PMR_E_INVALID;
   return c2r_from(n, batch, (const float2*)in, (float2*)work, spec_pitch(n), out,
                   (hipStream_t)stream);
 }

@@ -32,9 +32,9 @@ constexpr int BLOCK_ROW_MAX = 4096;  // tier 2: one workgroup, 16 entries per th
 // Workgroups that take the rows beyond tier 1, as many as fit on the chip: a workgroup sorts the
 // long rows among those it tests one after the other, and in a clustered field they are
 // neighbours. 128^3 particles in a cluster (sigma a tenth of the box) on 256^3: 605 us per sort,
-// 825 with half as many; 64^3 x 8 in tighter ones on 128^3: 1153, and 1836 where half as many workgroups test the
-// same 32 rows at a time. An even field pays nothing that shows (128^3 x 4: 7.03 -> 7.04 ms per
-// gradient).
+// 825 with half as many; 64^3 x 8 in tighter ones on 128^3: 1153, and 1836 where half as many
+// workgroups test the same 32 rows at a time. An even field pays nothing that shows (128^3 x 4:
+// 7.03 -> 7.04 ms per gradient).
 constexpr size_t LONG_BLOCKS = 2048;
 constexpr int SCAN_ITEMS = 16;
 constexpr int SCAN_TILE = TB * SCAN_ITEMS;  // counts per scan block
