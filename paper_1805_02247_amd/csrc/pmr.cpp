@@ -149,12 +149,11 @@ struct pmr_ctx {
   float* dR;       // [2][B][no3]
   float* mass;
   float* MR;
-  float* r;
   float* rs;
   float* xbar;
   float* pbar;
   float* dbar;   // [B][nm3]
-  float* ob;     // [4][B][no3]
+  float* ob;     // [4][B][no3] scratch of the target, the residual and the likelihood adjoint
   double* partial;   // partial sums of the data term [B][reduce_blocks(no^3)]
   double* ppartial;  // and of the prior [B][reduce_blocks(np^2 (np/2 + 1))]
   // event timing of one kernel class (pmr_profile_begin/end)
@@ -221,14 +220,9 @@ void plan(pmr_ctx* c, Plan& P) {
   const size_t B = c->B;
   c->inv_var = P.take<float>(c->cp);
   c->mlp_w = P.take<float>(mlp_weight_floats(c->H > 0 ? c->H : 8));
-  const size_t keep = c->H > 0 ? mlp_keep_bytes(c->H) : 0;
-  c->net_y = P.take<float>(keep ? B * c->no3 : 0);
-  c->net_sgn = P.take<char>(keep ? (keep - 4) * B * c->no3 : 0);
   const bool two = c->cfg.halo_model == PMR_HALO_TWO;
   c->halo2_w = P.take<float>(two ? HALO2_WEIGHT_FLOATS : 0);
-  // (of which halo2_u_floats are used: the planned size of a workspace stays what it was when
-  // the 81 input adjoints of a voxel were kept)
-  c->u2 = P.take<float>(two ? 81 * B * c->no3 : 0);
+  c->u2 = P.take<float>(two ? halo2_u_floats(B * c->no3) : 0);
   c->h2aux = P.take<float>(two ? 2 * B * c->no3 : 0);
   c->h2sgn = P.take<uint32_t>(two ? 4 * B * c->no3 : 0);
   c->target = P.take<float>(B * c->no3);
@@ -272,6 +266,14 @@ void plan(pmr_ctx* c, Plan& P) {
   c->cA = P.take<float2>(B * c->cmax);
   c->cB = P.take<float2>(B * 3 * c->cmax);
   c->psi = P.take<float>(B * 3 * c->np3);
+  // What the network's adjoint reads of the forward: the signs, in the place of the displacements
+  // (dead once the particles are set up) where they fit, and the outputs.
+  const size_t keep = c->H > 0 ? mlp_keep_bytes(c->H) : 0;
+  const size_t sgn = keep ? (keep - sizeof(float)) * B * c->no3 : 0;
+  const bool in_psi = sgn <= B * 3 * c->np3 * sizeof(float);
+  char* own = P.take<char>(in_psi ? 0 : sgn);
+  c->net_sgn = in_psi ? reinterpret_cast<char*>(c->psi) : own;
+  c->net_y = P.take<float>(keep ? B * c->no3 : 0);
   const size_t l2 = c->cfg.ic_order == 2 ? B * c->np3 : 0;
   c->psi2 = P.take<float>(3 * l2);
   c->phi = P.take<float>(6 * l2);
@@ -280,7 +282,6 @@ void plan(pmr_ctx* c, Plan& P) {
   c->dR = P.take<float>(2 * B * c->no3);
   c->mass = P.take<float>(B * c->no3);
   c->MR = P.take<float>(B * c->no3);
-  c->r = P.take<float>(B * c->no3);
   c->rs = P.take<float>(B * c->no3);
   c->xbar = P.take<float>(B * 3 * c->np3);
   c->pbar = P.take<float>(B * 3 * c->np3);
@@ -989,8 +990,8 @@ int pmr_forward(pmr_ctx* c, const void* modes, float* mass_out, double* loss_out
     }
     smooth(c, c->no, c->mass, 3, c->MR, nullptr);
     launch_residual(c->MR, c->xd, no3, B, c->params, c->noise_k ? c->noise_mu : nullptr,
-                    c->noise_k ? c->noise_w : nullptr, c->r, s);
-    smooth(c, c->no, c->r, 4, c->rs, nullptr);
+                    c->noise_k ? c->noise_w : nullptr, c->ob, s);  // r
+    smooth(c, c->no, c->ob, 4, c->rs, nullptr);
     launch_sumsq(c->rs, nullptr, no3, B, c->partial, s);
     if (mass_out) HIPC(c, hipMemcpyAsync(mass_out, c->mass, B * no3 * sizeof(float), hipMemcpyDeviceToDevice, s));
   }
@@ -1394,8 +1395,12 @@ int pmr_fft_get_tile(int n, int pass, int* columns, int* threads, int* staging) 
 
 size_t pmr_sort_scratch_bytes(int n_total, int n_mesh, int batch) {
   if (n_total < 1 || !pow2_in(n_mesh, 16, 512) || batch < 1) return 0;
+  // the keys, the counters and the sort's own scratch
+  const size_t rows = (size_t)batch * n_mesh * n_mesh;
+  const int log_nm = ilog2((size_t)n_mesh);
   return align256((size_t)n_total * sizeof(uint32_t)) +
-         cell_sort_scratch_bytes(n_total, (size_t)batch * n_mesh * n_mesh, ilog2((size_t)n_mesh));
+         cell_sort_segments(n_total, rows, log_nm) * sizeof(uint32_t) +
+         cell_sort_scratch_bytes(n_total, rows, log_nm);
 }
 
 int pmr_cic_sort(int n_part, int n_mesh, int batch, double box, const double* x,

@@ -625,9 +625,8 @@ int cell_sort_split(int n, size_t rows, int shift) {
 size_t cell_sort_scratch_bytes(int n, size_t rows, int shift) {
   const size_t segs = rows << cell_sort_split(n, rows, shift);
   const size_t nb = (segs + SCAN_TILE - 1) / SCAN_TILE;
-  // counts (of callers without counters of their own), cursors, segment starts, scan
-  // partials, buckets, radix scratch (hi, lo)
-  return (3 * segs + 1 + nb + 64 + 3 * (size_t)n) * sizeof(uint32_t) + 4 * 256;
+  // cursors, segment starts, scan partials, buckets, radix scratch (hi, lo)
+  return (2 * segs + 1 + nb + 64 + 3 * (size_t)n) * sizeof(uint32_t) + 4 * 256;
 }
 
 size_t cell_sort_segments(int n, size_t rows, int shift) {
