@@ -522,8 +522,7 @@ unsigned stream_grid(size_t n) {
 }
 
 // ---------------------------------------------------------------- binned spectra
-constexpr int PS_SLOTS = 2048;   // partial sums per shell the work buffer has room for
-constexpr int PS_BLOCKS = 1024;   // of them used: workgroups at most
+constexpr int PS_BLOCKS = 1024;  // workgroups at most: partial sums per shell
 constexpr int PS_ROWS = 8;       // rows (ix, iy) that share their shells: (+-i, +-j), (+-j, +-i)
 
 // Highest shell that holds a mode: floor(sqrt(3) n / 2).
@@ -677,7 +676,7 @@ __global__ __launch_bounds__(TB) void power_partial_kernel(int n, const float2* 
       for (int q = 0; q < 3; ++q) v[q + 1] += ps_lds[((size_t)u * 3 + q) * shells + k];
     }
 #pragma unroll
-    for (int q = 0; q < 4; ++q) work[((size_t)q * nbins + k) * PS_SLOTS + blockIdx.x] = v[q];
+    for (int q = 0; q < 4; ++q) work[((size_t)q * nbins + k) * PS_BLOCKS + blockIdx.x] = v[q];
   }
 }
 
@@ -691,7 +690,7 @@ __global__ __launch_bounds__(TB) void power_reduce_kernel(const double* __restri
   double s[4];
   for (int q = 0; q < 4; ++q) {
     double acc = 0.0;
-    const double* src = work + ((size_t)q * nbins + bin) * PS_SLOTS;
+    const double* src = work + ((size_t)q * nbins + bin) * PS_BLOCKS;
     if (bin < shells)
       for (int t = threadIdx.x; t < blocks; t += TB) acc += src[t];
     s[q] = block_sum(acc, sh);
@@ -1043,7 +1042,7 @@ void launch_lbfgs_update(size_t n, int m, pmr_lbfgs_state* st, const double* los
   lb_direction(st, n, m, g, d, S, Y, sy, yy, work, s);
 }
 
-size_t power_work_doubles(int nbins) { return (size_t)4 * nbins * PS_SLOTS; }
+size_t power_work_doubles(int nbins) { return (size_t)4 * nbins * PS_BLOCKS; }
 
 void launch_power_bins(int n, double box, const float2* a, const float2* b, int nbins,
                        double* out, double* work, hipStream_t s) {
