@@ -9,7 +9,8 @@ on the current GPU.
     python -m paper_1805_02247_amd.tune --workload 256 512 256 10 1 64 [--write]
 
 The first form times a batched forward + inverse 3-D real FFT through the library for every
-supported shape. The second times whole gradient evaluations (forward + adjoint) of a
+supported shape (for the y pass up to 128^3, which these transforms run plane by plane where
+its butterflies are the planes', every staging of the current shape). The second times whole gradient evaluations (forward + adjoint) of a
 workload given as n_part n_mesh n_out n_steps batch hidden [precision], tuning each pass of
 each mesh size it uses in turn with the others held fixed, which also ranks the operator
 passes (force, force adjoint, smoothing) by their real cost, and then the kz-slab width of
@@ -50,6 +51,18 @@ def candidates(n):
             for st in ((0, 1, 2) if register_capable(n, pc, nth) else (1, 2)):
                 out.append((pc, nth, st))
     return out
+
+
+PLANE_MAX = 128  # largest mesh whose y and z transforms run plane by plane
+
+
+def fft_candidates(n, p):
+    """What the stand-alone transforms can tell apart for pass p: up to PLANE_MAX only the
+    y pass's butterflies, not its shape, which the y passes inside the model still take."""
+    if p != "y" or n > PLANE_MAX:
+        return candidates(n)
+    pc, nth, _ = _get(n, PASSES[p])
+    return [c for c in candidates(n) if c[:2] == (pc, nth)]
 
 
 def _key(c):
@@ -116,15 +129,15 @@ def _gradient_step(n_part, n_mesh, n_out, n_steps, batch, hidden, precision):
     return step
 
 
-def _tune_passes(step, sizes, reps, log):
-    """Coordinate search: each (size, pass) in turn over all candidates, the others fixed at
+def _tune_passes(step, sizes, reps, log, choices=lambda n, p: candidates(n)):
+    """Coordinate search: each (size, pass) in turn over its choices, the others fixed at
     their current best."""
     best = {n: {p: _get(n, pid) for p, pid in PASSES.items()} for n in sizes}
     all_ms = {}
     for n in sizes:
         for p, pid in PASSES.items():
             times = {}
-            for c in candidates(n):
+            for c in choices(n, p):
                 _set(n, pid, c)
                 times[c] = _timer(step, reps)
                 log(f"n={n} pass={p} columns={c[0]} threads={c[1]} "
@@ -149,7 +162,8 @@ def tune(sizes, write=False, log=print):
     result = {}
     for n in sizes:
         batch = max(1, (256 // n) ** 3 // 8) if n < 256 else 1
-        result.update(_tune_passes(_fft_step(n, batch), [n], 20 if n <= 256 else 5, log))
+        result.update(_tune_passes(_fft_step(n, batch), [n], 20 if n <= 256 else 5, log,
+                                   fft_candidates))
     if write:
         _write(result)
     return result
@@ -173,11 +187,17 @@ def _tune_slab(step, n, reps, log):
 PAINT_ROWS = (1, 2, 4, 8, 16)
 
 
+def paint_candidates(n, channels):
+    """Three channels on 128^3 and larger meshes have at most 2 rows per wavefront: more only
+    cut the chunks elsewhere."""
+    return PAINT_ROWS[:2] if channels == 3 and n >= 128 else PAINT_ROWS
+
+
 def _tune_paint(step, n, channels, reps, log):
     """Rows per wavefront of the paint with `channels` channels on the n^3 mesh."""
     import ctypes
     times = {}
-    for rows in PAINT_ROWS:
+    for rows in paint_candidates(n, channels):
         L.check(L.lib().pmr_paint_set_rows(n, channels, rows))
         c = ctypes.c_int()
         L.check(L.lib().pmr_paint_get_rows(n, channels, ctypes.byref(c)))
