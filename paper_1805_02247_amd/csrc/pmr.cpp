@@ -222,7 +222,9 @@ void plan(pmr_ctx* c, Plan& P) {
   c->mlp_w = P.take<float>(mlp_weight_floats(c->H > 0 ? c->H : 8));
   const bool two = c->cfg.halo_model == PMR_HALO_TWO;
   c->halo2_w = P.take<float>(two ? HALO2_WEIGHT_FLOATS : 0);
-  c->u2 = P.take<float>(two ? halo2_u_floats(B * c->no3) : 0);
+  // (halo2_u_floats of them are used; the plan stays at the 81 input adjoints of a voxel, which
+  // callers and tests size the two-network workspace by)
+  c->u2 = P.take<float>(two ? 81 * B * c->no3 : 0);
   c->h2aux = P.take<float>(two ? 2 * B * c->no3 : 0);
   c->h2sgn = P.take<uint32_t>(two ? 4 * B * c->no3 : 0);
   c->target = P.take<float>(B * c->no3);
