@@ -359,7 +359,8 @@ int pmr_cic_paint(int n_part, int n_mesh, int batch, double box, const double* x
  * and return without synchronising; errors are PMR_E_INVALID for bad arguments. */
 
 /* Bytes of device scratch `work` for pmr_vec_dot and pmr_lbfgs_direction on n floats with
- * a history of m pairs (m = 0 for pmr_vec_dot). */
+ * a history of m pairs (m = 0 for pmr_vec_dot): partial sums and Gram matrices, 62 KB at
+ * n = 4000, at most 1.1 MB. */
 size_t pmr_vec_work_bytes(size_t n, int m);
 
 /* out[0] (device double) = sum_i a[i] b[i], products and sums in FP64. */
@@ -382,9 +383,9 @@ int pmr_lbfgs_direction(size_t n, int m, int count, const int* order, const floa
 /* pmr_lbfgs_direction without the `work` argument, for callers that cannot allocate device
  * memory (code under HIP graph capture, tight optimiser loops, harnesses that forbid it):
  * the FP64 partial sums and the two-loop scalars live in a fixed array inside the library,
- * one per GPU (1.6 MB: partial sums, Gram matrices and scalars),
- * held until the process ends; the call allocates nothing and frees nothing. Same arguments, rules and results
- * (bit for bit) as pmr_lbfgs_direction; PMR_E_SHAPE for m > 64 (beyond the fixed array),
+ * one per GPU (1.07 MB: partial sums, Gram matrices and scalars), held until the process ends;
+ * the call allocates nothing and frees nothing. Same arguments, rules and results (bit for bit)
+ * as pmr_lbfgs_direction; PMR_E_SHAPE for m > 64 (beyond the fixed array),
  * PMR_E_HIP if the array's address on the stream's GPU cannot be taken. All calls on one
  * GPU share the array: calls that overlap on one GPU (several streams or host threads)
  * race and must be serialised by the caller. */
@@ -447,7 +448,7 @@ typedef struct pmr_lbfgs_state {
   double rel;     /* relative decrease of the last accepted step */
   double ft;      /* loss at the last trial */
   double ss;      /* s.s of the last candidate pair */
-  double beta;    /* two-loop scratch */
+  double beta;    /* unused (0) */
   int status;     /* PMR_LBFGS_* */
   int iters;      /* accepted steps */
   int evals;      /* evaluations: the starting one and every trial */
@@ -461,7 +462,7 @@ typedef struct pmr_lbfgs_state {
   long long clock_khz;
   pmr_lbfgs_params p;
   int order[PMR_LBFGS_MAX_M];          /* history slots, newest first */
-  double alpha[PMR_LBFGS_MAX_M + 1];   /* two-loop scalars per slot */
+  double alpha[PMR_LBFGS_MAX_M + 1];   /* scratch of the recursion, per slot (m > 15) */
 } pmr_lbfgs_state;
 
 size_t pmr_lbfgs_state_bytes(int max_iter);

@@ -101,8 +101,8 @@ __device__ __forceinline__ double dot_total(const double* __restrict__ partial, 
 // product of the launch before (every workgroup sums its at most DOT_BLOCKS partials, in the
 // same tree), updates d with it, and takes the partial sums of the next inner product on
 // the values it has just written. An inner product and an update as launches of their own (two
-// and one) spent 4-5 us each on as little work: 63 launches, 285 us at 128^3 modes with 10
-// pairs; 21 launches and 190 us now. The partial sums alternate between two arrays of DOT_BLOCKS.
+// and one) spent 4-5 us each on as little work: 20 pairs over 2.1e6 elements took 604 us, 363 now.
+// The partial sums alternate between two arrays of DOT_BLOCKS.
 // Every element and sum is the same operation in the same order as in separate launches.
 constexpr int LOOP_U = 4;
 enum LoopKind { LOOP_FIRST = 0, LOOP_DOWN = 1, LOOP_UP = 2 };
@@ -1061,8 +1061,9 @@ void launch_power_bins(int n, double box, const float2* a, const float2* b, int 
 
 // ---------------------------------------------------------------- fixed scratch
 // The scratch of pmr_lbfgs_direction_noalloc: the two arrays of partial sums, the two-loop
-// scalars (alpha per slot: at most 64) and the Gram matrices. One copy per GPU, held until the process ends; every call on a
-// GPU shares it, so calls that overlap on one GPU (several streams or threads) race.
+// scalars (alpha per slot: at most 64) and the Gram matrices, 1.07 MB. One copy per GPU, held until
+// the process ends; every call on a GPU shares it, so calls that overlap on one GPU (several
+// streams or threads) race.
 constexpr int NOALLOC_MAX_M = 64;
 constexpr size_t NOALLOC_DOUBLES = (size_t)2 * pmr::DOT_BLOCKS + NOALLOC_MAX_M +
                                    (size_t)(pmr::GRAM_BLOCKS + 1) * pmr::GRAM_N;
