@@ -4,6 +4,7 @@ Every call forwards to the C ABI of include/pmr.h with the tensors' device point
 torch's current stream; nothing here computes any step of the forward model or gradient.
 """
 import ctypes
+import gc
 from dataclasses import dataclass, field
 
 import torch
@@ -402,8 +403,16 @@ class GradientGraph:
         torch.cuda.current_stream().wait_stream(s)
         torch.cuda.synchronize()
         self.graph = torch.cuda.CUDAGraph()
-        with torch.cuda.graph(self.graph):
-            self._enqueue()
+        # No cyclic garbage collection while capturing: a graph that is collected then waits for
+        # the device when it is destroyed, which a capture forbids, and the process aborts.
+        collecting = gc.isenabled()
+        gc.disable()
+        try:
+            with torch.cuda.graph(self.graph):
+                self._enqueue()
+        finally:
+            if collecting:
+                gc.enable()
         torch.cuda.synchronize()
 
     def set_params(self, params):

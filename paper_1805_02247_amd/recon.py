@@ -186,6 +186,10 @@ class _IterationGraph(GradientGraph):
     def __init__(self, opt, pm, modes, params):
         self.opt = opt
         super().__init__(pm, modes, warmup=1, params=params)
+        # the buffers the graph reads and writes, but not their owner, which holds this graph: in a
+        # reference cycle both would stay until the garbage collector comes by
+        self.opt = None
+        self.kept = (opt.state, opt.x, opt.g, opt.d, opt.S, opt.Y, opt.sy, opt.yy, opt.work)
 
     def _enqueue(self):
         o = self.opt

@@ -2,6 +2,8 @@
 is that of the new weights at the forward's fields. With a mass cotangent alone the gradient
 passes through nothing else that depends on the weights, so it equals, bit for bit, the one
 of a forward with the new weights."""
+import gc
+
 import numpy as np
 import pytest
 import torch
@@ -45,6 +47,7 @@ def test_adjoint_after_new_weights(H, mixed):
     pm.set_mlp(new)
     assert torch.equal(torch.view_as_real(pm.adjoint(zero, mbar)), ref["new"])
     assert torch.equal(torch.view_as_real(pm.adjoint(zero, mbar)), ref["new"])
+    gc.collect()  # nothing of earlier tests goes away during the capture
     # a captured adjoint: the weights of the moment of each replay
     grad = torch.empty(B, pm.n_modes, dtype=torch.complex64, device=DEV)
     graph = torch.cuda.CUDAGraph()
