@@ -118,7 +118,8 @@ __device__ __forceinline__ void seg_scan_steps(float (&v)[NV], uint32_t key, uin
 
 // Scans v over the runs of equal keys and returns the lanes, of those in `ok`, that end a run
 // (two valid lanes only ever share a key with valid lanes between them; what a lane without a
-// particle adds to a valid one is 0, and those above the run are no valid lane's source).
+// particle, whose key is its neighbour's, adds to a valid one is 0, and those above the run are no
+// valid lane's source).
 // `tame`: this lane's values and all sums of up to 64 like them are finite.
 template <int NV>
 __device__ __forceinline__ uint64_t seg_scan(float (&v)[NV], uint32_t key, uint64_t ok,
@@ -201,12 +202,11 @@ struct Chunk {
 template <int C>
 __device__ __forceinline__ void weigh_chunk(const PaintArgs& a, const RawChunk<C>& r, int ox,
                                             Chunk<C>& ch) {
-  const int lane = threadIdx.x & 63;
   const int nm = a.nm;
   const bool ok = __builtin_amdgcn_inverse_ballot_w64(r.ok);
   const Vec3 f = r.f;
   ch.ok = r.ok;
-  ch.key = ok ? r.key : empty_lane_key(lane);
+  ch.key = r.key;
   ch.iz = (int)(r.key & (uint32_t)(nm - 1));
   ch.sy = (int)((r.key >> a.log_nm) & (uint32_t)(nm - 1));
   float val[C];
@@ -279,12 +279,11 @@ struct Chunk1 {
 template <int C>
 __device__ __forceinline__ void weigh_chunk1(const PaintArgs& a, const RawChunk<C>& r, int ox,
                                              int iy0, Chunk1<C>& ch) {
-  const int lane = threadIdx.x & 63;
   const int nm = a.nm;
   const bool ok = __builtin_amdgcn_inverse_ballot_w64(r.ok);
   const Vec3 f = r.f;
   ch.ok = r.ok;
-  ch.key = ok ? r.key : empty_lane_key(lane);
+  ch.key = r.key;
   ch.iz = (int)(r.key & (uint32_t)(nm - 1));
   ch.oy = (int)((r.key >> a.log_nm) & (uint32_t)(nm - 1)) == iy0 ? 0 : 1;
   float val[C];
