@@ -29,13 +29,7 @@ namespace {
 constexpr int TB = 256;
 constexpr int WAVE_ROW_MAX = 256;    // tier 1: one wavefront, 4 entries per lane
 constexpr int BLOCK_ROW_MAX = 4096;  // tier 2: one workgroup, 16 entries per thread in LDS
-// Workgroups that take the rows beyond tier 1, as many as fit on the chip: a workgroup sorts the
-// long rows among those it tests one after the other, and in a clustered field they are
-// neighbours. 128^3 particles in a cluster (sigma a tenth of the box) on 256^3: 605 us per sort,
-// 825 with half as many; 64^3 x 8 in tighter ones on 128^3: 1153, and 1836 where half as many
-// workgroups test the same 32 rows at a time. An even field pays nothing that shows (128^3 x 4:
-// 7.03 -> 7.04 ms per gradient).
-constexpr size_t LONG_BLOCKS = 2048;
+constexpr size_t LONG_BLOCKS = 1024;  // workgroups that take the rows beyond tier 1
 constexpr int SCAN_ITEMS = 16;
 constexpr int SCAN_TILE = TB * SCAN_ITEMS;  // counts per scan block
 constexpr int SCAN1_TB = 1024;              // threads of the one-launch scan
@@ -472,30 +466,36 @@ __device__ void block_radix_pass(const uint32_t* shi, const uint32_t* slo, uint3
 
 // Tier 2 (rows of 257..4096 entries: bitonic sort in LDS) and tier 3 (larger rows: stable
 // LSD radix passes in global memory over the digits that vary in the row). A workgroup
-// takes block_rows consecutive rows at a time (blocks strided over the row range); its
-// threads test those rows' lengths together and the workgroup then sorts the long ones one
-// after the other (rows are independent, so the order in which they are done does not
-// matter).
+// tests the lengths of block_rows rows together and then sorts the long ones one after the
+// other (rows are independent, so the order in which they are done does not matter). In a
+// clustered field the long rows are neighbours and a workgroup that tests neighbours sorts them
+// all in a row, so the rows of a workgroup come from places far apart, RUN consecutive ones from
+// each. 128^3 particles in a cluster (sigma a tenth of the box) per sort: 823 us with
+// neighbours, 490 with runs of 16, 465 with 8 on 256^3, 1130, 848 and 663 on 128^3; tighter (a
+// fiftieth) 3480, 2590 and 2210. An even field has no long rows: 270 and 271.
+constexpr int RUN = 8;
 __device__ __forceinline__ void sort_long_rows(const RowSortArgs& a, uint32_t* s, uint32_t* found,
                                                int* nfound) {
   __shared__ uint32_t red[2][TB / 64];
   uint32_t* base = s;  // tier 3 has no use for the LDS tile itself
   uint32_t(*wcnt)[256] = reinterpret_cast<uint32_t(*)[256]>(s + 256);
   const int t = threadIdx.x;
-  const size_t br = (size_t)a.block_rows;
-  for (size_t r0 = (size_t)blockIdx.x * br; r0 < a.rows; r0 += (size_t)a.long_blocks * br) {
+  const uint32_t rows = (uint32_t)a.rows;  // at most 2^31 segments
+  const uint32_t apart = (uint32_t)a.long_blocks * RUN;
+  for (uint32_t r0 = blockIdx.x * RUN; r0 < rows; r0 += (uint32_t)a.long_blocks * a.block_rows) {
     if (t == 0) *nfound = 0;
     __syncthreads();
-    if ((size_t)t < br && r0 + t < a.rows &&
-        a.row_start[r0 + t + 1] - a.row_start[r0 + t] > WAVE_ROW_MAX)
-      found[atomicAdd(nfound, 1)] = (uint32_t)t;
+    const uint32_t mine = r0 + (uint32_t)t / RUN * apart + (uint32_t)t % RUN;
+    if (t < a.block_rows && mine < rows &&
+        a.row_start[mine + 1] - a.row_start[mine] > WAVE_ROW_MAX)
+      found[atomicAdd(nfound, 1)] = mine;
     __syncthreads();
     const int nf = *nfound;
     for (int f = 0; f < nf; ++f) {
-      const size_t r = r0 + found[f];
+      const uint32_t r = found[f];
       const uint32_t start = a.row_start[r];
       const uint32_t c = a.row_start[r + 1] - start;
-      const uint32_t row = (uint32_t)r;
+      const uint32_t row = r;
       if (c <= BLOCK_ROW_MAX) {
         uint32_t p2 = 512;
         while (p2 < c) p2 <<= 1;
