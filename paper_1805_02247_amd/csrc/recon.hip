@@ -246,8 +246,8 @@ __device__ __forceinline__ const float* gram_vector(const LoopArgs& a, int count
 
 // The same for one or two pairs, on the vector units: the matrix form takes 512 products per
 // element whatever the count, of which one pair needs 4 and two need 12. A direction over 2.1e6
-// elements took 67 and 68 us with it (38 and 68 as the launches of the recursion), now 32 and 37;
-// over 1.7e7 425 and 454 (182 and 328), now 158 and 198. From three pairs on the matrix form is as
+// elements took 67 and 68 us with it (38 and 68 as the launches of the recursion), now 33 and 38;
+// over 1.7e7 424 and 453 (184 and 329), now 164 and 202. From three pairs on the matrix form is as
 // fast or faster (69 against 98, 459 against 472). Bound by reading the vectors.
 template <int C, class Slot>
 __device__ __forceinline__ void gram_few_body(const LoopArgs& a, Slot slot,
@@ -311,7 +311,7 @@ __device__ __forceinline__ void gram_few_body(const LoopArgs& a, Slot slot,
 template <class Slot>
 __device__ __forceinline__ void gram_body(const LoopArgs& a, int count, Slot slot,
                                           double* __restrict__ out) {
-  if (count == 0) return;  // d = -g, which the combination writes by itself
+  if (count == 0) return;  // d = -g, which needs none
   if (count == 1) return gram_few_body<1>(a, slot, out);
   if (count == 2) return gram_few_body<2>(a, slot, out);
   constexpr int WAVES = GRAM_TB / 64;
@@ -399,39 +399,27 @@ __device__ __forceinline__ void combine_body(const LoopArgs& a, int count, Slot 
   __shared__ double cg_sh;
   const double* GS = G + 256;
   const int t = threadIdx.x;
-  const size_t n = a.n, stride = (size_t)gridDim.x * TB;
-  double acc = 0.0;
-  if (count == 0) {  // bound by the copy: 4 elements in flight per thread
-    for (size_t k0 = (size_t)blockIdx.x * TB + t; k0 < n; k0 += 4 * stride) {
-      float gv[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) gv[u] = k0 + u * stride < n ? a.g[k0 + u * stride] : 0.f;
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (k0 + u * stride < n) {
-          a.d[k0 + u * stride] = -gv[u];
-          acc += (double)gv[u] * (double)-gv[u];
-        }
-    }
-  } else if (t < 64) {
+  if (t < 64) {
     const int j = t < count ? t : 0;
-    double alpha = 0.0, delta = 0.0;
-    const size_t i0 = slot(0);
-    const double gamma = a.sy[i0] / a.yy[i0];
-    const double sy = a.sy[slot(j)];
-    double sq = GS[16 * j + GRAM_MAX];  // s_j.q
-    for (int k = 0; k < count; ++k) {   // newest to oldest
-      const double ak = __shfl(sq / sy, k, 64);
-      if (t == k) alpha = ak;
-      sq -= ak * GS[16 * j + k];
-    }
-    double yr = G[16 * j + GRAM_MAX];  // y_j.r
-    for (int k = 0; k < count; ++k) yr -= __shfl(alpha, k, 64) * G[16 * j + k];
-    yr *= gamma;
-    for (int k = count - 1; k >= 0; --k) {  // oldest to newest
-      const double dk = __shfl(alpha - yr / sy, k, 64);
-      if (t == k) delta = dk;
-      yr += dk * GS[16 * k + j];
+    double alpha = 0.0, delta = 0.0, gamma = 1.0;
+    if (count > 0) {
+      const size_t i0 = slot(0);
+      gamma = a.sy[i0] / a.yy[i0];
+      const double sy = a.sy[slot(j)];
+      double sq = GS[16 * j + GRAM_MAX];  // s_j.q
+      for (int k = 0; k < count; ++k) {              // newest to oldest
+        const double ak = __shfl(sq / sy, k, 64);
+        if (t == k) alpha = ak;
+        sq -= ak * GS[16 * j + k];
+      }
+      double yr = G[16 * j + GRAM_MAX];  // y_j.r
+      for (int k = 0; k < count; ++k) yr -= __shfl(alpha, k, 64) * G[16 * j + k];
+      yr *= gamma;
+      for (int k = count - 1; k >= 0; --k) {  // oldest to newest
+        const double dk = __shfl(alpha - yr / sy, k, 64);
+        if (t == k) delta = dk;
+        yr += dk * GS[16 * k + j];
+      }
     }
     if (t < count) {
       co[0][t] = gamma * alpha;
@@ -441,8 +429,10 @@ __device__ __forceinline__ void combine_body(const LoopArgs& a, int count, Slot 
   }
   __syncthreads();
   const double cg = cg_sh;
+  const size_t n = a.n, stride = (size_t)gridDim.x * TB;
+  double acc = 0.0;
   constexpr int U = 2;  // elements in flight per thread
-  for (size_t k0 = (size_t)blockIdx.x * TB + t; count > 0 && k0 < n; k0 += U * stride) {
+  for (size_t k0 = (size_t)blockIdx.x * TB + t; k0 < n; k0 += U * stride) {
     double r[U];
     float gv[U], yv[U][GRAM_MAX], sv[U][GRAM_MAX];
 #pragma unroll
@@ -505,6 +495,13 @@ __global__ __launch_bounds__(TB) void gram_sum_kernel(const double* part, int bl
 __global__ __launch_bounds__(TB) void combine_kernel(LoopArgs a, int count, LoopOrder o,
                                                      const double* G) {
   combine_body(a, count, [&](int k) { return (size_t)o.slot[k]; }, G);
+}
+
+// d = -g, the combination without pairs.
+__global__ __launch_bounds__(TB) void negate_kernel(size_t n, const float* __restrict__ g,
+                                                    float* __restrict__ d) {
+  const size_t stride = (size_t)gridDim.x * TB;
+  for (size_t i = (size_t)blockIdx.x * TB + threadIdx.x; i < n; i += stride) d[i] = -g[i];
 }
 
 // The Gram matrix and its partials in a work buffer, after the partial sums of inner products.
@@ -733,12 +730,14 @@ void launch_lbfgs_direction(size_t n, int m, int count, const int* order, const 
   LoopOrder o{};
   for (int j = 0; j < count; ++j) o.slot[j] = (unsigned char)order[j];
   if (count <= GRAM_MAX && m <= GRAM_MAX + 1) {
+    if (count == 0) {
+      negate_kernel<<<stream_grid(n), TB, 0, s>>>(n, g, d);
+      return;
+    }
     const int gb = gram_blocks(n);
     double* total = gram + (size_t)gb * GRAM_N;
-    if (count > 0) {
-      gram_kernel<<<gb, GRAM_TB, 0, s>>>(a, count, o, gram);
-      gram_sum_kernel<<<GRAM_N / (TB / 64), TB, 0, s>>>(gram, gb, total);
-    }
+    gram_kernel<<<gb, GRAM_TB, 0, s>>>(a, count, o, gram);
+    gram_sum_kernel<<<GRAM_N / (TB / 64), TB, 0, s>>>(gram, gb, total);
     combine_kernel<<<nb, TB, 0, s>>>(a, count, o, total);
     return;
   }
