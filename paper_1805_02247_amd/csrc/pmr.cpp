@@ -275,7 +275,6 @@ void plan(pmr_ctx* c, Plan& P) {
   const bool in_psi = sgn <= B * 3 * c->np3 * sizeof(float);
   char* own = P.take<char>(in_psi ? 0 : sgn);
   c->net_sgn = in_psi ? reinterpret_cast<char*>(c->psi) : own;
-  c->net_y = P.take<float>(keep ? B * c->no3 : 0);
   const size_t l2 = c->cfg.ic_order == 2 ? B * c->np3 : 0;
   c->psi2 = P.take<float>(3 * l2);
   c->phi = P.take<float>(6 * l2);
@@ -284,6 +283,7 @@ void plan(pmr_ctx* c, Plan& P) {
   c->dR = P.take<float>(2 * B * c->no3);
   c->mass = P.take<float>(B * c->no3);
   c->MR = P.take<float>(B * c->no3);
+  c->net_y = P.take<float>(keep ? B * c->no3 : 0);
   c->rs = P.take<float>(B * c->no3);
   c->xbar = P.take<float>(B * 3 * c->np3);
   c->pbar = P.take<float>(B * 3 * c->np3);
